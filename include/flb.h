@@ -173,7 +173,8 @@ int flb_get_sample_overlap(flb_t *h);
  * timed; each timed launch keeps its event pair until it is read.
  * flb_get_launch_timing_kinds reads the same records split by the steps a
  * launch took: launches[q] and total_ms[q] (caller arrays of three) for the
- * launches of q + 1 steps. */
+ * launches of q + 1 steps; q = 2 also holds the launches of four and five
+ * steps of the library's own grouping (flb_set_time_blocking). */
 int flb_set_launch_timing(flb_t *h, int on);
 int flb_get_launch_timing(flb_t *h, int64_t *launches, double *total_ms);
 int flb_get_launch_timing_kinds(flb_t *h, int64_t launches[3], double total_ms[3]);
@@ -342,7 +343,12 @@ int flb_get_step_config(flb_t *h, int *tile_w, int *sites, int *nontemporal);
  * one-step kernel if fewer than four steps are enqueued, else the last
  * three-step launch and it become two two-step launches.  Every site sees the same arithmetic, noise counters and storage
  * rounding as with one step per launch: results do not depend on it.
- * steps_per_launch = 1 (default) turns it off.  FLB_EINVAL for other values.
+ * steps_per_launch = 1 turns it off.  FLB_EINVAL for other values.
+ * Until this call, flb_set_lattice_tiles, flb_set_step_config or a tuning
+ * call chooses a shape, the library groups the steps itself, by the
+ * lattices' sizes and the storage format, up to five per launch;
+ * flb_get_time_blocking then reports steps_per_launch = 1 (as it does when
+ * a tuning call finds that grouping the fastest).
  * flb_get_time_blocking reports tile_w = 0 while each lattice has its own
  * tile (flb_set_lattice_tiles). */
 int flb_set_time_blocking(flb_t *h, int steps_per_launch, int tile_w);

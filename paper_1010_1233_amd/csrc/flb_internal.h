@@ -152,6 +152,13 @@ bool step2_tile_supported(int tw);
 // 128, the same items).
 hipError_t launch_step3(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
                         uint32_t step_add, bool nontemporal, bool noise, hipStream_t s);
+// Four or five steps per launch by waves marching along y: strips of
+// march_cols(steps) columns, segments of `rows` rows; item tile = strip +
+// segment * strips, items in groups of kMarchWaves (one block each).
+constexpr int kMarchWaves = 4;
+constexpr int march_cols(int steps) { return 64 - 2 * (steps - 1); }
+hipError_t launch_march(const DeviceView &v, const StepItem *items, int nitems, int steps,
+                        int rows, uint32_t step_add, bool noise, hipStream_t s);
 hipError_t launch_advance_step(uint32_t *step, uint32_t n, hipStream_t s);
 hipError_t launch_init(const DeviceView &v, int lattice, int64_t plane, hipStream_t s);
 hipError_t launch_get(const DeviceView &v, int lattice, int nx, int ny, double *out_dev,

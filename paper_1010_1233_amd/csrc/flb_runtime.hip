@@ -103,13 +103,19 @@ struct flb {
     bool nontemporal = false;
     StepItem *d_items = nullptr;
     int nitems = 0;
-    // time blocking: steps per launch (1, 2 or 3) and the two- and
+    // time blocking: steps per launch (1, 2 or 3; 0 while no shape was set
+    // or tuned: the library's own choice, see launch_plan) and the two- and
     // three-step kernels' tile width; tile2 = 0: each lattice has its own,
     // log2 of it in ltile (5 or 6)
-    int tblock = 1, tile2 = 64;
+    int tblock = 0, tile2 = 64;
     std::vector<int8_t> ltile;
     StepItem *d_items2 = nullptr;
     int nitems2 = 0;
+    // marching launches of 4 and 5 steps ([0], [1]), with tblock = 0 and
+    // lattices large enough for them
+    bool march = false;
+    StepItem *d_march[2] = {nullptr, nullptr};
+    int n_march[2] = {0, 0}, march_rows[2] = {0, 0};
     int64_t t = 0;
 
     // correlators
@@ -359,6 +365,129 @@ std::vector<StepItem> step2_items(const flb_t *h, const std::vector<int8_t> *lt,
     return xcd_order(items, StepItem{-1, 0});
 }
 
+// Rows per wave of a marching launch: the fewest rows whose waves fill the
+// SIMDs w deep, for the w (4 is what the registers let be resident) with the
+// smallest w (rows + steps - 1), the rows a SIMD works through.
+int march_rows(const flb_t *h, int steps, int nsimd)
+{
+    const int W = march_cols(steps);
+    int maxy = 1;
+    for (const LatticeParams &P : h->params) maxy = std::max(maxy, (int)P.ny);
+    auto waves = [&](int rows) {
+        int64_t n = 0;
+        for (const LatticeParams &P : h->params)
+            n += (int64_t)((P.nx + W - 1) / W) * ((P.ny + rows - 1) / rows);
+        return n;
+    };
+    int best = 0;
+    int64_t cost = 0;
+    for (int w : {4, 5, 6, 8, 12, 16}) {
+        int lo = 1, hi = maxy;  // waves(rows) falls with rows
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (waves(mid) <= (int64_t)w * nsimd) hi = mid;
+            else lo = mid + 1;
+        }
+        const int64_t depth = std::max<int64_t>(w, (waves(lo) + nsimd - 1) / nsimd);
+        const int64_t c = depth * (lo + steps - 1);
+        if (!best || c < cost) {
+            best = lo;
+            cost = c;
+        }
+    }
+    return best;
+}
+
+// Work items of a marching launch, strips along x first, in blocks of
+// kMarchWaves consecutive items in XCD order.
+std::vector<StepItem> march_items(const flb_t *h, int steps, int rows)
+{
+    struct Block {
+        StepItem w[kMarchWaves];
+    };
+    const int W = march_cols(steps);
+    Block idle;
+    for (StepItem &w : idle.w) w = StepItem{-1, 0};
+    std::vector<Block> blocks;
+    int fill = kMarchWaves;
+    for (size_t l = 0; l < h->params.size(); ++l) {
+        const LatticeParams &P = h->params[l];
+        const int n = ((P.nx + W - 1) / W) * ((P.ny + rows - 1) / rows);
+        for (int t = 0; t < n; ++t) {
+            if (fill == kMarchWaves) {
+                blocks.push_back(idle);
+                fill = 0;
+            }
+            blocks.back().w[fill++] = StepItem{(int32_t)l, t};
+        }
+    }
+    std::vector<StepItem> out;
+    for (const Block &b : xcd_order(blocks, idle)) out.insert(out.end(), b.w, b.w + kMarchWaves);
+    return out;
+}
+
+// Collisions per update of a marching launch of `steps` steps: the halo
+// columns and rows, and the lanes past a lattice's last column.
+double march_overhead(const flb_t *h, int steps, int rows)
+{
+    const int W = march_cols(steps);
+    double work = 0, sites = 0;
+    for (const LatticeParams &P : h->params) {
+        const int segs = (P.ny + rows - 1) / rows;
+        work += 64.0 * ((P.nx + W - 1) / W) * (P.ny + segs * (steps - 1.0));
+        sites += (double)P.nx * P.ny;
+    }
+    return work / sites;
+}
+
+// The same for tiles of 64 x 16 sites, averaged over the launches of a
+// period of ten steps: 3 + 3 + 2 + 2 (1.163 and 1.080 collisions per
+// update), 16-bit storage pairs only.
+double tile_overhead(const flb_t *h)
+{
+    double work = 0, sites = 0;
+    for (const LatticeParams &P : h->params) {
+        work += 1024.0 * ((P.nx + 63) / 64) * ((P.ny + 15) / 16);
+        sites += (double)P.nx * P.ny;
+    }
+    return work / sites * (h->storage == kF32 ? 1.13 : 1.08);
+}
+
+// How much faster the marching form gets through a collision than the
+// tiles, from 4096^2 (GLUPS x collisions per update): FP32 166 x 1.20
+// against 142 x 1.13, 16-bit 156 x 1.15 against 154 x 1.08; without noise
+// both wait for HBM, which the marching form's 14 bytes per update load
+// less (244 against 157 GLUPS).  Where the line lies: 2048^2 146 against
+// 139 GLUPS (marching taken), 1800^2 145 against 150 (not), 64 x 256^2 131
+// against 135 (not), 500 x 100^2 132 against 103 (taken), 512 x 64^2 86
+// against 141 (not).
+double march_gain(const flb_t *h)
+{
+    return !h->noise ? 1.8 : h->storage == kF32 ? 1.24 : 1.08;
+}
+// fewer rows a wave are a launch too small to fill the device
+constexpr int kMarchMinRows = 12;
+
+int build_march_items(flb_t *h)
+{
+    h->march = false;
+    if (h->tblock != 0) return FLB_OK;
+    int ncu = 0;
+    FLB_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
+    for (int q = 0; q < 2; ++q) {
+        const int steps = 4 + q, rows = march_rows(h, steps, 4 * ncu);
+        if (rows < kMarchMinRows) return FLB_OK;
+        if (q == (h->storage == kF32) && march_overhead(h, steps, rows) > march_gain(h) * tile_overhead(h))
+            return FLB_OK;
+        h->march_rows[q] = rows;
+        const std::vector<StepItem> items = march_items(h, steps, rows);
+        h->n_march[q] = (int)items.size();
+        if (int rc = upload(&h->d_march[q], items)) return rc;
+    }
+    h->march = true;
+    return FLB_OK;
+}
+
 int build_step_items(flb_t *h)
 {
     const int TH = kThreads / h->tile_w;
@@ -382,15 +511,71 @@ int build_step_items(flb_t *h)
         step2_items(h, h->tile2 == 0 ? &h->ltile : nullptr, h->tile2, nullptr);
     h->nitems2 = (int)items2.size();
     if ((rc = upload(&h->d_items2, items2))) return rc;
+    if ((rc = build_march_items(h))) return rc;
     return upload(&h->d_params, h->params);
 }
 
-// Kernel launches for n steps (the buffer parity flips once per launch).
-int64_t step_launches(const flb_t *h, int64_t n)
+// The launches n steps are issued as: how many of each number of steps,
+// the longest first.
+struct LaunchPlan {
+    int64_t of[6] = {0, 0, 0, 0, 0, 0};  // [steps of the launch]
+    int64_t launches() const { return of[1] + of[2] + of[3] + of[4] + of[5]; }
+};
+
+LaunchPlan launch_plan(const flb_t *h, int64_t n)
 {
-    if (h->tblock == 3) return n / 3 + (n % 3 ? 1 : 0);  // a remainder of 2 takes one launch
-    return h->tblock == 2 ? n / 2 + n % 2 : n;
+    LaunchPlan p;
+    // launches of three and two steps: a remainder of one step after at
+    // least three goes as two launches of two (3 + 1 -> 2 + 2), as one step
+    // per launch costs a whole HBM round trip
+    auto threes = [&](int64_t m) {
+        p.of[3] = m % 3 == 1 && m >= 4 ? m / 3 - 1 : m / 3;
+        m -= 3 * p.of[3];
+        p.of[2] = m / 2;
+        p.of[1] = m % 2;
+    };
+    auto twos = [&](int64_t m) {
+        p.of[2] = m / 2;
+        p.of[1] = m % 2;
+    };
+    if (h->tblock == 1) {
+        p.of[1] = n;
+    } else if (h->tblock == 2) {
+        twos(n);
+    } else if (h->tblock == 3) {
+        threes(n);
+    } else if (h->storage != kF32) {
+        // 16-bit storage moves half the bytes: four steps a launch are the
+        // fastest, two in tiles next (4096^2 BF16: 157 and 153 GLUPS; five
+        // steps 149, three in tiles 144)
+        p.of[4] = h->march ? n / 4 : 0;
+        if (p.of[4] && n % 4 == 1) {  // 4 + 1 -> 3 + 2
+            p.of[4] -= 1;
+            p.of[3] = p.of[2] = 1;
+        } else if (p.of[4] && n % 4 == 3) {
+            p.of[3] = 1;
+        } else {
+            twos(n - 4 * p.of[4]);
+        }
+    } else if (!h->march) {
+        threes(n);
+    } else {
+        // fives, as many as leave whole fours; what neither covers (1, 2, 3,
+        // 6, 7 or 11 steps, or that many left) ends in tiles of three and two
+        const int64_t r = (5 - n % 5) % 5;  // r fours and (n - 4 r) / 5 fives make n
+        if (n >= 4 * r) {
+            p.of[4] = r;
+            p.of[5] = (n - 4 * r) / 5;
+        } else {
+            p.of[4] = n == 11 ? 2 : n == 7 ? 1 : 0;
+            threes(n - 4 * p.of[4]);
+        }
+    }
+    return p;
 }
+
+// Kernel launches for n steps (the buffer parity flips once per launch).
+int64_t step_launches(const flb_t *h, int64_t n) { return launch_plan(h, n).launches(); }
 
 void clear_graphs(flb_t *h)
 {
@@ -825,8 +1010,7 @@ int flush_pending(flb_t *h)
 }
 
 // n steps from the device counter value; the counter is advanced afterwards.
-// With time blocking, pairs of steps go through the two-step kernel and an
-// odd last step through the one-step kernel. When wait_before_second is
+// launch_plan says how the steps are grouped. When wait_before_second is
 // given, the second launch (the first to write the buffer that held the
 // state at the start) waits for it.
 int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_second = nullptr)
@@ -861,33 +1045,27 @@ int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_sec
         if (timing) FLB_HIP(hipEventRecord(stop, s));
         return FLB_OK;
     };
-    int rc;
-    // three steps per launch: a remainder of one step after at least three
-    // goes as two launches of two steps (3 + 1 -> 2 + 2), as one step per
-    // launch costs a whole HBM round trip
-    const int64_t n3 = h->tblock == 3 ? (n % 3 == 1 && n >= 4 ? n / 3 - 1 : n / 3) : 0;
-    for (; k < 3 * n3; k += 3) {
-        if ((rc = before_launch(3))) return rc;
-        FLB_HIP(launch_step3(h->view(), h->d_items2, h->nitems2, h->tile2, (uint32_t)k,
-                             h->nontemporal, h->noise, s));
-        if ((rc = after_launch())) return rc;
-        h->cur ^= 1;
-    }
-    if (h->tblock >= 2)
-        for (; k + 2 <= n; k += 2) {
-            if ((rc = before_launch(2))) return rc;
-            FLB_HIP(launch_step2(h->view(), h->d_items2, h->nitems2, h->tile2, (uint32_t)k,
-                                 h->nontemporal, h->noise, s));
-            if ((rc = after_launch())) return rc;
+    const LaunchPlan plan = launch_plan(h, n);
+    for (int steps = 5; steps >= 1; --steps)
+        for (int64_t i = 0; i < plan.of[steps]; ++i, k += steps) {
+            if (int rc = before_launch(steps)) return rc;
+            const DeviceView v = h->view();
+            const uint32_t add = (uint32_t)k;
+            if (steps >= 4)
+                FLB_HIP(launch_march(v, h->d_march[steps - 4], h->n_march[steps - 4], steps,
+                                     h->march_rows[steps - 4], add, h->noise, s));
+            else if (steps == 3)
+                FLB_HIP(launch_step3(v, h->d_items2, h->nitems2, h->tile2, add, h->nontemporal,
+                                     h->noise, s));
+            else if (steps == 2)
+                FLB_HIP(launch_step2(v, h->d_items2, h->nitems2, h->tile2, add, h->nontemporal,
+                                     h->noise, s));
+            else
+                FLB_HIP(launch_step(v, h->d_items, h->nitems, h->tile_w, h->sites, add,
+                                    h->nontemporal, h->noise, s));
+            if (int rc = after_launch()) return rc;
             h->cur ^= 1;
         }
-    for (; k < n; ++k) {
-        if ((rc = before_launch(1))) return rc;
-        FLB_HIP(launch_step(h->view(), h->d_items, h->nitems, h->tile_w, h->sites, (uint32_t)k,
-                            h->nontemporal, h->noise, s));
-        if ((rc = after_launch())) return rc;
-        h->cur ^= 1;
-    }
     if (n > 0) FLB_HIP(launch_advance_step(h->d_step, (uint32_t)n, s));
     return FLB_OK;
 }
@@ -1114,7 +1292,8 @@ void flb_destroy(flb_t *h)
                     h->d_plans, h->d_tables, h->d_spec, h->d_acc, h->d_rows, h->d_cols,
                     h->d_accum, h->d_cols_l, h->d_fld, h->d_fields,
                     h->d_csum_part, h->d_csum, h->d_cols_lm, h->d_cols_m, h->d_rows_m,
-                    h->d_rows_blue, h->d_stash, h->d_flush, h->d_items2, h->d_cols_blue};
+                    h->d_rows_blue, h->d_stash, h->d_flush, h->d_items2, h->d_cols_blue,
+                    h->d_march[0], h->d_march[1]};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto &set : h->pipe)
@@ -1217,7 +1396,7 @@ int flb_get_launch_timing_kinds(flb_t *h, int64_t launches[3], double total_ms[3
     for (size_t i = 0; i < h->timed.size(); ++i) {
         float ms = 0.0f;
         FLB_HIP(hipEventElapsedTime(&ms, h->timed[i].first, h->timed[i].second));
-        const int q = h->timed_steps[i] - 1;
+        const int q = std::min(h->timed_steps[i], 3) - 1;
         launches[q] += 1;
         total_ms[q] += ms;
     }
@@ -1591,6 +1770,7 @@ int flb_set_step_config(flb_t *h, int tile_w, int sites, int nontemporal)
     h->tile_w = tile_w;
     h->sites = sites;
     h->nontemporal = nontemporal != 0;
+    if (h->tblock == 0) h->tblock = 1;  // the shape asked for, not the library's
     clear_graphs(h);
     return build_step_items(h);
 }
@@ -1611,7 +1791,7 @@ int flb_set_time_blocking(flb_t *h, int steps_per_launch, int tile_w)
 int flb_get_time_blocking(flb_t *h, int *steps_per_launch, int *tile_w)
 {
     if (check_handle(h)) return FLB_EINVAL;
-    if (steps_per_launch) *steps_per_launch = h->tblock;
+    if (steps_per_launch) *steps_per_launch = std::max(1, h->tblock);
     if (tile_w) *tile_w = h->tile2;
     return FLB_OK;
 }
@@ -1655,7 +1835,8 @@ int flb_get_step_config(flb_t *h, int *tile_w, int *sites, int *nontemporal)
 }  // extern "C"
 
 // A step launch shape: one-step tile width, sites per thread, streaming
-// accesses, steps per launch (1, 2 or 3), two- and three-step tile width
+// accesses, steps per launch (1, 2 or 3; 0 the library's own grouping, see
+// launch_plan), two- and three-step tile width
 // (0: per lattice, log2 of each lattice's in lt).
 struct StepShape {
     int tw, sv, nt, tb, t2;
@@ -1717,7 +1898,7 @@ static bool cached_shape(const char *cache, const std::string &key, size_t nlat,
             x.t2 = atoi(t2s.c_str());
             if (!step2_tile_supported(x.t2)) continue;
         }
-        if (step_tile_supported(x.tw, x.sv) && x.tb >= 1 && x.tb <= 3) {
+        if (step_tile_supported(x.tw, x.sv) && x.tb >= 0 && x.tb <= 3) {
             found = true;
             c = x;
             ms = t;
@@ -1796,7 +1977,7 @@ static int time_shapes(flb_t *h, int nsteps, const std::vector<StepShape> &shape
         for (int round = 0; round < kRounds && e == hipSuccess && rc == FLB_OK; ++round)
             for (size_t i = 0; i < shapes.size() && e == hipSuccess && rc == FLB_OK; ++i) {
                 apply_shape(hh, shapes[i]);
-                const int tb = shapes[i].tb;  // whole launches
+                const int tb = std::max(1, shapes[i].tb);  // whole launches
                 const int n = (nsteps + tb - 1) / tb * tb;
                 if ((rc = build_step_items(hh)) != FLB_OK) break;
                 if ((rc = enqueue_steps(hh, 2, hh->stream)) != FLB_OK) break;
@@ -1826,6 +2007,7 @@ static int time_every_shape(flb_t *h, int nsteps, std::vector<std::pair<float, S
     for (int tb : {2, 3})
         for (int t2 : {32, 64, 128})
             for (int nt = 0; nt < 2; ++nt) shapes.push_back({h->tile_w, h->sites, nt, tb, t2, {}});
+    for (int nt = 0; nt < 2; ++nt) shapes.push_back({h->tile_w, h->sites, nt, 0, 64, {}});
     std::vector<float> best;
     if (int rc = time_shapes(h, nsteps, shapes, best)) return rc;
     out.clear();

@@ -9,6 +9,8 @@
 // wave's loads and stores are contiguous 64-site runs of one plane.  There is
 // no dense contraction here: the 9x9 transforms are written out using the
 // sign structure of Eq. (9), about forty adds each way.
+#include <type_traits>
+
 #include "flb_device.h"
 
 namespace flbdev {
@@ -175,6 +177,20 @@ struct StepArgs {
     uint32_t step_add;
     uint32_t key0, key1;
 };
+
+static StepArgs step_args(const DeviceView &v, const StepItem *items, uint32_t step_add)
+{
+    StepArgs a;
+    a.src = v.pops[v.cur];
+    a.dst = v.pops[v.cur ^ 1];
+    a.params = v.params;
+    a.items = items;
+    a.step = v.step;
+    a.step_add = step_add;
+    a.key0 = (uint32_t)(v.seed & 0xFFFFFFFFu);
+    a.key1 = (uint32_t)(v.seed >> 32);
+    return a;
+}
 
 // Collision of one site, including its noise draw, on working values
 // (Work<S>).
@@ -347,15 +363,7 @@ bool step_tile_supported(int tx, int v)
 hipError_t launch_step(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
                        int sites, uint32_t step_add, bool nontemporal, bool noise, hipStream_t s)
 {
-    StepArgs a;
-    a.src = v.pops[v.cur];
-    a.dst = v.pops[v.cur ^ 1];
-    a.params = v.params;
-    a.items = items;
-    a.step = v.step;
-    a.step_add = step_add;
-    a.key0 = (uint32_t)(v.seed & 0xFFFFFFFFu);
-    a.key1 = (uint32_t)(v.seed >> 32);
+    const StepArgs a = step_args(v, items, step_add);
 #define FLB_SEL(S_)                                                                              \
     if (v.storage == S_) {                                                                       \
         if (nontemporal)                                                                         \
@@ -634,15 +642,7 @@ bool step2_tile_supported(int tw) { return tw == 32 || tw == 64 || tw == 128; }
 hipError_t launch_step2(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
                         uint32_t step_add, bool nontemporal, bool noise, hipStream_t s)
 {
-    StepArgs a;
-    a.src = v.pops[v.cur];
-    a.dst = v.pops[v.cur ^ 1];
-    a.params = v.params;
-    a.items = items;
-    a.step = v.step;
-    a.step_add = step_add;
-    a.key0 = (uint32_t)(v.seed & 0xFFFFFFFFu);
-    a.key1 = (uint32_t)(v.seed >> 32);
+    const StepArgs a = step_args(v, items, step_add);
 #define FLB_SEL(S_)                                                                              \
     if (v.storage == S_) {                                                                       \
         if (nontemporal)                                                                         \
@@ -904,15 +904,7 @@ static hipError_t launch_step3_tiles(const StepArgs &a, int nitems, int tw, hipS
 hipError_t launch_step3(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
                         uint32_t step_add, bool nontemporal, bool noise, hipStream_t s)
 {
-    StepArgs a;
-    a.src = v.pops[v.cur];
-    a.dst = v.pops[v.cur ^ 1];
-    a.params = v.params;
-    a.items = items;
-    a.step = v.step;
-    a.step_add = step_add;
-    a.key0 = (uint32_t)(v.seed & 0xFFFFFFFFu);
-    a.key1 = (uint32_t)(v.seed >> 32);
+    const StepArgs a = step_args(v, items, step_add);
 #define FLB_SEL(S_)                                                                              \
     if (v.storage == S_) {                                                                       \
         if (nontemporal)                                                                         \
@@ -925,6 +917,205 @@ hipError_t launch_step3(const DeviceView &v, const StepItem *items, int nitems, 
     FLB_SEL(kBF16)
     FLB_SEL(kF16)
 #undef FLB_SEL
+    return hipErrorInvalidValue;
+}
+
+// ---------------------------------------------------------------------
+// T = 4 or 5 steps per launch, marching along y without LDS or barriers.
+// A wave owns a strip of W = 64 - 2 (T - 1) columns and `rows` rows; its
+// lanes are the strip and T - 1 halo columns on either side.  It walks down
+// the strip one row at a time and holds T time levels at once: while level
+// 1 (t) collides row y, pulled from HBM, level k + 1 (t + k) collides row
+// y - k from what level k left in registers.  A population moving along y
+// reaches its next row in the same lane; one moving along x comes from the
+// neighbour lane (wave shift).  So a level keeps nine values per lane
+// (planes 0, 1, 3 of its last row, planes 2, 5, 6 of its last two), the
+// other populations of a row are used at once, and nothing else is kept.
+// The outermost columns of a wave go stale by one a level; they are the
+// halo, which the neighbouring strips compute again.  Values pass from one
+// level to the next rounded to the storage format, so the results are the
+// bits of T one-step launches.
+//
+// What bounds it: VALU issue (160 instructions per collision, of which the
+// noise is half).  Collisions per update: 64 / W for the halo columns times
+// 1 + (T - 1) / rows for the halo rows, 1.20 at 4096^2 with T = 5 (75 rows
+// a wave), against 1.16 of the three-step tiles (two barriers a step, 204
+// instructions per update); HBM moves 72 / T bytes per update.  At 4096^2
+// FP32: 166-174 GLUPS with T = 5, 166-173 with T = 4, tiles of three steps
+// 148-153, of two 125-130 (T = 2 and 3 of this form 106 and 146).  BF16:
+// T = 4 157, T = 5 149, two-step tiles 153.  Stores are ordinary: with the
+// streaming hint a wave's 240-byte rows, whose ends share lines with the
+// next strip, cost T = 4 12 %.
+//
+// The loop takes two rows a turn, so that the two rows kept of planes 2, 5,
+// 6 swap names instead of registers, and its first rows run through the same
+// code with the levels not yet fed skipped: peeled rows in front of the
+// loop (25 KB more code, fetched cold by every launch) cost a quarter.
+// ---------------------------------------------------------------------
+
+// a working value as the next level reads it back from storage
+template <int S> __device__ __forceinline__ float stored(float x)
+{
+    if constexpr (S == kF32) return x;
+    else return Work<S>::in(Work<S>::out(x));
+}
+
+// the value of the lane at x - 1 (wave shift right) or x + 1 (left); the
+// wave's end lanes get 0
+__device__ __forceinline__ float from_left(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float from_right(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+
+// `base` plus a byte offset
+template <typename U> __device__ __forceinline__ const U *bytes_at(const U *base, uint32_t off)
+{
+    return reinterpret_cast<const U *>(reinterpret_cast<const char *>(base) + off);
+}
+template <typename U> __device__ __forceinline__ U *bytes_at(U *base, uint32_t off)
+{
+    return reinterpret_cast<U *>(reinterpret_cast<char *>(base) + off);
+}
+
+// item: lattice and strip + segment * strips of the lattice; a block's waves
+// take consecutive items (neighbouring strips, which share lines)
+template <int S, bool NOISE, int T>
+__global__ __launch_bounds__(64 * kMarchWaves)
+__attribute__((amdgpu_waves_per_eu(4))) void march_kernel(StepArgs g, int rows)
+{
+    using E = typename Codec<S>::T;
+    constexpr int W = march_cols(T);
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const StepItem it = g.items[blockIdx.x * kMarchWaves + wv];
+    if (it.lattice < 0) return;
+    const LatticeParams &P = g.params[it.lattice];
+    const int nx = P.nx, ny = P.ny;
+    const int64_t px = P.px, plane = P.plane;
+    const int nstrips = (nx + W - 1) / W;
+    const int seg = it.tile / nstrips, strip = it.tile - seg * nstrips;
+    const int y0 = seg * rows, h = min(rows, ny - y0);
+    const int lane = (int)threadIdx.x & 63;
+    const uint32_t t = *g.step + g.step_add;
+
+    int x = strip * W - (T - 1) + lane;
+    const bool own = lane >= T - 1 && lane < 64 - (T - 1) && x < nx;
+    while (x < 0) x += nx;
+    while (x >= nx) x -= nx;
+    const uint32_t sx = (uint32_t)x;
+    // byte offsets of the columns x, x - 1, x + 1
+    uint32_t o0 = sx * sizeof(E), om = (uint32_t)(x == 0 ? nx - 1 : x - 1) * sizeof(E);
+    uint32_t op = (uint32_t)(x == nx - 1 ? 0 : x + 1) * sizeof(E);
+    const E *__restrict__ src = (const E *)g.src + P.base;
+    E *__restrict__ dst = (E *)g.dst + P.base;
+
+    int y = y0 - (T - 1);  // level 1's next row
+    while (y < 0) y += ny;
+    E nxt[9];
+    auto load = [&]() {
+        const int ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
+        const E *rc = src + y * px, *rm = src + ym * px, *rp = src + yp * px;
+        // (opaque here, so that each access is a scalar base and a 32-bit
+        // offset: widened outside the loop they become 64-bit adds)
+        asm("" : "+v"(o0), "+v"(om), "+v"(op));
+        nxt[0] = *bytes_at(rc, o0);
+        nxt[1] = *bytes_at(rc + plane, om);
+        nxt[2] = *bytes_at(rm + 2 * plane, o0);
+        nxt[3] = *bytes_at(rc + 3 * plane, op);
+        nxt[4] = *bytes_at(rp + 4 * plane, o0);
+        nxt[5] = *bytes_at(rm + 5 * plane, om);
+        nxt[6] = *bytes_at(rm + 6 * plane, op);
+        nxt[7] = *bytes_at(rp + 7 * plane, op);
+        nxt[8] = *bytes_at(rp + 8 * plane, om);
+    };
+    load();
+    // A[k]: planes 0, 1, 3 of level k's last row; B[k][i & 1]: planes 2, 5, 6
+    // of the row before it, B[k][~i & 1] of the last row; all as level k + 1
+    // reads them, at the sites they stream to
+    float A[T][3] = {}, B[T][2][3] = {};
+    int yk[T] = {};  // each level's row
+    // row i: level k + 1 joins in with row 2 k, when its first row's
+    // neighbours are there
+    auto row = [&](int i, auto parity) {
+        constexpr int p = decltype(parity)::value;
+        float d[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) d[q] = Work<S>::in(nxt[q]);
+#pragma unroll
+        for (int k = T - 1; k > 0; --k) yk[k] = yk[k - 1];
+        yk[0] = y;
+        y = y == ny - 1 ? 0 : y + 1;
+        load();  // the next row's, under this row's collisions
+        update_site<NOISE, S>(d, P, (uint32_t)(yk[0] * nx) + sx, t, g.key0, g.key1);
+#pragma unroll
+        for (int k = 1; k < T; ++k) {
+            if (i < 2 * k - 2) break;
+            float e[9];
+            e[0] = A[k][0];
+            e[1] = A[k][1];
+            e[3] = A[k][2];
+            e[2] = B[k][p][0];
+            e[5] = B[k][p][1];
+            e[6] = B[k][p][2];
+            e[4] = stored<S>(d[4]);
+            e[7] = from_right(stored<S>(d[7]));
+            e[8] = from_left(stored<S>(d[8]));
+            A[k][0] = stored<S>(d[0]);
+            A[k][1] = from_left(stored<S>(d[1]));
+            A[k][2] = from_right(stored<S>(d[3]));
+            B[k][p][0] = stored<S>(d[2]);
+            B[k][p][1] = from_left(stored<S>(d[5]));
+            B[k][p][2] = from_right(stored<S>(d[6]));
+            if (i < 2 * k) break;
+            update_site<NOISE, S>(e, P, (uint32_t)(yk[k] * nx) + sx, t + k, g.key0, g.key1);
+#pragma unroll
+            for (int q = 0; q < 9; ++q) d[q] = e[q];
+            if (k == T - 1 && own) {
+                asm("" : "+v"(o0));
+                E *out = dst + yk[k] * px;
+#pragma unroll
+                for (int q = 0; q < 9; ++q) *bytes_at(out + q * plane, o0) = Work<S>::out(d[q]);
+            }
+        }
+    };
+    const int n = h + 2 * (T - 1);
+    for (int i = 0; i < n; i += 2) {
+        row(i, std::integral_constant<int, 0>());
+        if (i + 1 >= n) break;
+        row(i + 1, std::integral_constant<int, 1>());
+    }
+}
+
+template <int S>
+static hipError_t launch_march_s(const StepArgs &a, int nblocks, int steps, int rows, bool noise,
+                                 hipStream_t s)
+{
+    const dim3 grid(nblocks), block(64 * kMarchWaves);
+    if (steps == 5 && noise)
+        hipLaunchKernelGGL((march_kernel<S, true, 5>), grid, block, 0, s, a, rows);
+    else if (steps == 5)
+        hipLaunchKernelGGL((march_kernel<S, false, 5>), grid, block, 0, s, a, rows);
+    else if (steps == 4 && noise)
+        hipLaunchKernelGGL((march_kernel<S, true, 4>), grid, block, 0, s, a, rows);
+    else if (steps == 4)
+        hipLaunchKernelGGL((march_kernel<S, false, 4>), grid, block, 0, s, a, rows);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_march(const DeviceView &v, const StepItem *items, int nitems, int steps,
+                        int rows, uint32_t step_add, bool noise, hipStream_t s)
+{
+    if (rows < 1 || nitems % kMarchWaves) return hipErrorInvalidValue;
+    const StepArgs a = step_args(v, items, step_add);
+    const int nb = nitems / kMarchWaves;
+    if (v.storage == kF32) return launch_march_s<kF32>(a, nb, steps, rows, noise, s);
+    if (v.storage == kBF16) return launch_march_s<kBF16>(a, nb, steps, rows, noise, s);
+    if (v.storage == kF16) return launch_march_s<kF16>(a, nb, steps, rows, noise, s);
     return hipErrorInvalidValue;
 }
 

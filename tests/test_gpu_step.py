@@ -573,3 +573,28 @@ def test_empty_calls_change_nothing(flb):
     a.step(0)  # a waiting sample stays waiting through no steps
     acc, ns = a.read_correlators()
     assert ns == 1 and acc.any()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("sides", [[(2311, 1803)], [(2050, 2049)],
+                                   [(1000, 2200), (57, 9000), (4100, 901), (56, 58), (3, 2)]])
+@pytest.mark.parametrize("theta", [1e-4, 0.0])
+def test_library_grouping_equals_one_step_launches(flb, storage, sides, theta):
+    """The library's own grouping of the steps (marching launches of four and
+    five steps on lattices this large, ragged strips and segments) gives the
+    bits of one step per launch, for every remainder."""
+    note("own grouping", storage, sides, theta)
+    specs = [dict(nx=nx, ny=ny, tau=workloads.tau_vector(0.7, 1.1, 0.9), theta=theta,
+                  u0=(0.04, -0.02), stream_id=7 + i) for i, (nx, ny) in enumerate(sides)]
+    a = flb.Lattice.batch(specs, seed=11, storage=storage)
+    b = flb.Lattice.batch(specs, seed=11, storage=storage)
+    b.set_time_blocking(1, 64)
+    f = workloads.perturbed(a.get_populations()[:, 0, 0], *sides[0], 1e-3, 5)
+    for g in (a, b):
+        g.thermalize()
+        g.set_populations(f)
+    for n in (1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 13):
+        a.step(n)
+        b.step(n)
+    for i in range(len(sides)):
+        assert np.array_equal(a.get_populations(i), b.get_populations(i)), i
