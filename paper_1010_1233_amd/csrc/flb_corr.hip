@@ -1496,4 +1496,40 @@ hipError_t launch_corr_accum(const DeviceView &v, const CorrItem *items, int nit
     return hipGetLastError();
 }
 
+// The sums as a read returns them: row order instead of column tiles,
+// without the padding columns, scaled if asked.  A wave writes 512
+// contiguous bytes; its reads are 32-byte pieces of the tiles, whose lines
+// the waves of the next rows share, and which cost little beside the host
+// link that the output crosses.
+template <bool SCALED>
+__global__ __launch_bounds__(kThreads) void corr_export_kernel(const double *__restrict__ acc,
+                                                               const LatticeParams *params,
+                                                               int lattice, uint32_t first,
+                                                               uint32_t n, SumScale sc,
+                                                               double *__restrict__ out)
+{
+    const LatticeParams &P = params[lattice];
+    const uint32_t j = blockIdx.x * (uint32_t)kThreads + threadIdx.x;
+    if (j >= n) return;
+    const uint32_t nkx = (uint32_t)P.nkx, ny = (uint32_t)P.ny;
+    const uint32_t row = (first + j) / nkx, kx = first + j - row * nkx;
+    const uint32_t q = row / ny, y = row - q * ny;
+    double v = acc[P.acc_base + (int64_t)q * ny * P.kxp + spec_offset((int)y, (int)kx, (int)ny)];
+    if (SCALED) v = v / sc.nsamples * sc.norm[q];
+    out[j] = v;
+}
+
+hipError_t launch_corr_export(const DeviceView &v, int lattice, size_t first, size_t n,
+                              const SumScale *scale, double *out, hipStream_t s)
+{
+    const dim3 grid((unsigned)((n + kThreads - 1) / kThreads)), block(kThreads);
+    if (scale)
+        hipLaunchKernelGGL(corr_export_kernel<true>, grid, block, 0, s, v.acc, v.params, lattice,
+                           (uint32_t)first, (uint32_t)n, *scale, out);
+    else
+        hipLaunchKernelGGL(corr_export_kernel<false>, grid, block, 0, s, v.acc, v.params, lattice,
+                           (uint32_t)first, (uint32_t)n, SumScale(), out);
+    return hipGetLastError();
+}
+
 }  // namespace flbdev

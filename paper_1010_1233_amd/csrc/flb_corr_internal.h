@@ -123,4 +123,13 @@ hipError_t launch_corr_flush(const DeviceView &v, const CorrItem *items, int nit
 // output left in place, in row order).
 hipError_t launch_corr_accum(const DeviceView &v, const CorrItem *items, int nitems, int set,
                              hipStream_t s);
+// Sums first .. first + n - 1 of lattice `lattice` in the order [kind][ky]
+// [kx], kx = 0..nx/2, to out (device or pinned host memory); with `scale`
+// each divided by nsamples and times its kind's norm.
+struct SumScale {
+    double norm[kKinds + kMomentFields];
+    double nsamples;
+};
+hipError_t launch_corr_export(const DeviceView &v, int lattice, size_t first, size_t n,
+                              const SumScale *scale, double *out, hipStream_t s);
 }  // namespace flbdev

@@ -29,6 +29,7 @@
 #include "../../include/flb.h"
 #include "../../include/flb_dq.h"
 #include "flb_fft.h"
+#include "flb_stage.h"
 
 namespace flbdev {
 
@@ -67,6 +68,8 @@ struct DqParams {
     float omega[kDqMaxQ];       // 1/tau^a
     float amp[kDqMaxQ];         // sigma_a (Eq. 8)
     float therm[kDqMaxQ];       // sqrt(mu rho0 w_i)
+    double f0[kDqMaxQ];         // w_i rho0, what a stored deviation lacks
+    float feq[kDqMaxQ];         // f_i^0(rho0, u0) - w_i rho0
     int32_t nkx, kxp;           // half-space extent along x and its pitch
 };
 
@@ -322,6 +325,63 @@ __global__ __launch_bounds__(kDqThreads) void dq_conservation_kernel(const float
         for (int w = 0; w < kDqThreads / 64; ++w) s += red[threadIdx.x][w];
         part[(size_t)blockIdx.x * 4 + threadIdx.x] = s;
     }
+}
+
+// The uniform start: every deviation is feq_i.
+template <int MODEL>
+__global__ __launch_bounds__(kDqThreads) void dq_init_kernel(float *__restrict__ buf,
+                                                             const DqParams *__restrict__ Pp,
+                                                             uint32_t V)
+{
+    const uint32_t s = blockIdx.x * (uint32_t)kDqThreads + threadIdx.x;
+    if (s >= V) return;
+#pragma unroll
+    for (int i = 0; i < DqSet<MODEL>::Q; ++i) buf[(uint32_t)i * V + s] = Pp->feq[i];
+}
+
+// Values first .. first + n - 1 of the FP64 populations [Q][nz][ny][nx] to
+// (GET) or from `host` (pinned): f_i(x) = w_i rho0 + d_i, stored at x - v_i.
+template <int MODEL, bool GET>
+__global__ __launch_bounds__(kDqThreads) void dq_copy_kernel(float *__restrict__ buf,
+                                                             const DqParams *__restrict__ Pp,
+                                                             uint32_t first, uint32_t n,
+                                                             double *__restrict__ host)
+{
+    using S = DqSet<MODEL>;
+    const DqParams &P = *Pp;
+    const uint32_t j = blockIdx.x * (uint32_t)kDqThreads + threadIdx.x;
+    if (j >= n) return;
+    const uint32_t nx = (uint32_t)P.n[0], ny = (uint32_t)P.n[1], nz = (uint32_t)P.n[2];
+    const uint32_t row = (first + j) / nx, x = first + j - row * nx;
+    const uint32_t plane = row / ny, y = row - plane * ny;
+    const uint32_t i = plane / nz, z = plane - i * nz;
+    const int xs = wrapi((int)x - S::v[i][0], (int)nx), ys = wrapi((int)y - S::v[i][1], (int)ny);
+    const int zs = wrapi((int)z - S::v[i][2], (int)nz);
+    float *p = dq_at(buf, (uint32_t)xs + nx * ((uint32_t)ys + ny * ((uint32_t)zs + nz * i)));
+    if (GET) host[j] = (double)*p + P.f0[i];
+    else *p = (float)(host[j] - P.f0[i]);
+}
+
+// Sums first .. first + n - 1 in the order [kind][nz][ny][nx/2+1], without
+// the rows' padding; scaled as read_normalized returns them if asked.
+struct DqScale {
+    double norm[kDqMaxQ + 8];
+    double nsamples;
+};
+template <bool SCALED>
+__global__ __launch_bounds__(kDqThreads) void dq_export_kernel(const double *__restrict__ acc,
+                                                               uint32_t nrows, uint32_t nkx,
+                                                               uint32_t kxp, uint64_t first,
+                                                               uint32_t n, DqScale sc,
+                                                               double *__restrict__ out)
+{
+    const uint32_t j = blockIdx.x * (uint32_t)kDqThreads + threadIdx.x;
+    if (j >= n) return;
+    const uint64_t row = (first + j) / nkx;
+    const uint32_t kx = (uint32_t)(first + j - row * nkx);
+    double v = acc[row * kxp + kx];
+    if (SCALED) v = v / sc.nsamples * sc.norm[row / nrows];
+    out[j] = v;
 }
 
 // ---------------------------------------------------------------------
@@ -593,6 +653,7 @@ using namespace flbdev;
 // Host side
 // ---------------------------------------------------------------------
 struct flb_dq {
+    int device = 0;
     int model = 0, D = 0, Q = 0, nm = 0, nf = 0, nkinds = 0;
     int n[3] = {1, 1, 1};
     uint32_t V = 0;
@@ -905,6 +966,7 @@ flb_dq_t *flb_dq_create(int model, const int32_t n[3], const double *tau, double
         return nullptr;
     }
     flb_dq *h = new flb_dq();
+    stage_retain();
     auto bail = [&](int code, const std::string &msg) -> flb_dq_t * {
         if (!msg.empty()) dq_fail(code, msg);
         flb_dq_destroy(h);
@@ -951,6 +1013,12 @@ flb_dq_t *flb_dq_create(int model, const int32_t n[3], const double *tau, double
     const int first_ghost = 1 + D + D * (D + 1) / 2;
     for (int i = 0; i < Q; ++i) {
         P.w[i] = (float)h->w[i];
+        P.f0[i] = h->w[i] * rho0;
+        double vu = 0;
+        for (int a = 0; a < 3; ++a) vu += h->v[i][a] * u0[a];
+        // f^0(rho0, u0) (Eq. 2) as the deviation from w_i rho0
+        const double feq = h->w[i] * rho0 * (1.0 + 3.0 * vu + 4.5 * vu * vu - 1.5 * uu);
+        P.feq[i] = (float)(feq - h->w[i] * rho0);
         P.therm[i] = (float)std::sqrt(mu * rho0 * h->w[i]);
     }
     for (int a = 0; a < Q; ++a)
@@ -975,6 +1043,7 @@ flb_dq_t *flb_dq_create(int model, const int32_t n[3], const double *tau, double
             }
     }
     h->nblocks = (int)grid_sites(h);
+    if (hipGetDevice(&h->device) != hipSuccess) return bail(FLB_EHIP, "no HIP device");
     if (hipStreamCreateWithFlags(&h->own, hipStreamNonBlocking) != hipSuccess)
         return bail(FLB_EHIP, "stream creation failed");
     h->stream = h->own;
@@ -989,17 +1058,14 @@ flb_dq_t *flb_dq_create(int model, const int32_t n[3], const double *tau, double
         return bail(FLB_ENOMEM, "scratch allocation failed");
     if (hipMemcpy(h->d_P, &P, sizeof(DqParams), hipMemcpyHostToDevice) != hipSuccess)
         return bail(FLB_EHIP, "parameter upload failed");
-    // uniform f^0(rho0, u0) (Eq. 2) as deviations from w_i rho0
-    std::vector<float> init((size_t)Q * h->V);
-    for (int i = 0; i < Q; ++i) {
-        double vu = 0;
-        for (int a = 0; a < 3; ++a) vu += h->v[i][a] * u0[a];
-        const double f0 = h->w[i] * rho0 * (1.0 + 3.0 * vu + 4.5 * vu * vu - 1.5 * uu);
-        std::fill(init.begin() + (size_t)i * h->V, init.begin() + (size_t)(i + 1) * h->V,
-                  (float)(f0 - h->w[i] * rho0));
-    }
-    if (hipMemcpy(h->pops[0], init.data(), bytes, hipMemcpyHostToDevice) != hipSuccess)
-        return bail(FLB_EHIP, "initial state upload failed");
+    if (dispatch(model, [&](auto mc) {
+            constexpr int MODEL = decltype(mc)::value;
+            hipLaunchKernelGGL(dq_init_kernel<MODEL>, dim3((h->V + kDqThreads - 1) / kDqThreads),
+                               dim3(kDqThreads), 0, h->stream, h->pops[0], h->d_P, h->V);
+            return hipGetLastError();
+        }) != hipSuccess ||
+        hipStreamSynchronize(h->stream) != hipSuccess)
+        return bail(FLB_EHIP, "initialisation failed");
     return h;
 }
 
@@ -1013,6 +1079,7 @@ void flb_dq_destroy(flb_dq_t *h)
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (h->own) (void)hipStreamDestroy(h->own);
+    stage_release();
     delete h;
 }
 
@@ -1079,46 +1146,69 @@ int flb_dq_accumulate(flb_dq_t *h)
     return enqueue_sample(h);
 }
 
+// The sums (times scale, if given) to out[kind][nz][ny][nx/2+1].
+static int dq_read_sums(flb_dq *h, double *out, size_t n_doubles, const DqScale *scale)
+{
+    const uint32_t nrows = (uint32_t)h->n[1] * h->n[2];
+    const size_t need = (size_t)h->nkinds * nrows * h->P.nkx;
+    if (n_doubles < need) return dq_fail(FLB_ESIZE, "output buffer too small for the correlators");
+    DQ_HIP(stage_out(h->device, h->stream, out, need,
+                     [&](double *slot, size_t first, size_t n, hipStream_t s) {
+                         const dim3 grid((unsigned)((n + kDqThreads - 1) / kDqThreads));
+                         if (scale)
+                             hipLaunchKernelGGL(dq_export_kernel<true>, grid, dim3(kDqThreads), 0,
+                                                s, h->d_acc, nrows, (uint32_t)h->P.nkx,
+                                                (uint32_t)h->P.kxp, (uint64_t)first, (uint32_t)n,
+                                                *scale, slot);
+                         else
+                             hipLaunchKernelGGL(dq_export_kernel<false>, grid, dim3(kDqThreads),
+                                                0, s, h->d_acc, nrows, (uint32_t)h->P.nkx,
+                                                (uint32_t)h->P.kxp, (uint64_t)first, (uint32_t)n,
+                                                DqScale(), slot);
+                         return hipGetLastError();
+                     }));
+    return FLB_OK;
+}
+
 int flb_dq_read(flb_dq_t *h, double *out, size_t n_doubles, int64_t *nsamples)
 {
     if (check(h)) return FLB_EINVAL;
     if (!out) return dq_fail(FLB_EINVAL, "out must not be NULL");
     int rc = setup_corr(h);
     if (rc) return rc;
-    const size_t nrows = (size_t)h->n[1] * h->n[2];
-    if (n_doubles < (size_t)h->nkinds * nrows * h->P.nkx)
-        return dq_fail(FLB_ESIZE, "output buffer too small for the correlators");
-    DQ_HIP(hipStreamSynchronize(h->stream));
-    DQ_HIP(hipMemcpy2D(out, (size_t)h->P.nkx * sizeof(double), h->d_acc,
-                       (size_t)h->P.kxp * sizeof(double), (size_t)h->P.nkx * sizeof(double),
-                       (size_t)h->nkinds * nrows, hipMemcpyDeviceToHost));
+    if ((rc = dq_read_sums(h, out, n_doubles, nullptr))) return rc;
     if (nsamples) *nsamples = h->nsamples;
     return FLB_OK;
 }
 
 int flb_dq_read_normalized(flb_dq_t *h, double *out, size_t n_doubles, int64_t *nsamples)
 {
-    int64_t ns = 0;
-    int rc = flb_dq_read(h, out, n_doubles, &ns);
+    if (check(h)) return FLB_EINVAL;
+    if (!out) return dq_fail(FLB_EINVAL, "out must not be NULL");
+    int rc = setup_corr(h);
     if (rc) return rc;
-    if (nsamples) *nsamples = ns;
-    if (ns <= 0) return dq_fail(FLB_ESTATE, "no correlator sample to normalise");
-    if (!(h->theta > 0))
-        return dq_fail(FLB_ESTATE, "theta = 0: no fluctuation scale to normalise by");
+    const int64_t ns = h->nsamples;
+    if (ns <= 0 || !(h->theta > 0)) {  // the raw sums, and why they are not normalised
+        if ((rc = dq_read_sums(h, out, n_doubles, nullptr))) return rc;
+        if (nsamples) *nsamples = ns;
+        return dq_fail(FLB_ESTATE, ns <= 0 ? "no correlator sample to normalise"
+                                           : "theta = 0: no fluctuation scale to normalise by");
+    }
     // Eq. (11) (and Eq. 12 for u_x u_y*) at the noise temperature, mu = 3 theta
     const double V = (double)h->V, mu = 3.0 * h->theta, rho0 = h->rho0, theta = h->theta;
     const int D = h->D;
-    const size_t plane = (size_t)h->n[1] * h->n[2] * h->P.nkx;
+    DqScale scale;
+    scale.nsamples = (double)ns;
     for (int q = 0; q < h->nkinds; ++q) {
-        double norm;
+        double &norm = scale.norm[q];
         if (q == 0) norm = 1.0 / (V * mu * rho0);                  // rho
         else if (q <= D) norm = 1.0 / (V * rho0 * theta);          // j_a
         else if (q <= 2 * D) norm = rho0 / (V * theta);            // u_a
         else if (D >= 2 && q <= 2 * D + 2) norm = rho0 / (V * theta);  // Re, Im u_x u_y*
         else norm = 1.0 / (V * mu * rho0);                         // non-conserved moments
-        double *p = out + (size_t)q * plane;
-        for (size_t k = 0; k < plane; ++k) p[k] = p[k] / (double)ns * norm;
     }
+    if ((rc = dq_read_sums(h, out, n_doubles, &scale))) return rc;
+    if (nsamples) *nsamples = ns;
     return FLB_OK;
 }
 
@@ -1133,28 +1223,35 @@ int flb_dq_reset(flb_dq_t *h)
     return FLB_OK;
 }
 
+// The populations to or from host memory in the layout of the calls below.
+static int dq_copy(flb_dq *h, double *host, size_t total, bool get)
+{
+    float *buf = h->pops[h->cur];
+    auto kernel = [&](double *slot, size_t first, size_t n, hipStream_t s) {
+        const dim3 grid((unsigned)((n + kDqThreads - 1) / kDqThreads)), block(kDqThreads);
+        return dispatch(h->model, [&](auto mc) {
+            constexpr int MODEL = decltype(mc)::value;
+            if (get)
+                hipLaunchKernelGGL((dq_copy_kernel<MODEL, true>), grid, block, 0, s, buf, h->d_P,
+                                   (uint32_t)first, (uint32_t)n, slot);
+            else
+                hipLaunchKernelGGL((dq_copy_kernel<MODEL, false>), grid, block, 0, s, buf, h->d_P,
+                                   (uint32_t)first, (uint32_t)n, slot);
+            return hipGetLastError();
+        });
+    };
+    if (get) DQ_HIP(stage_out(h->device, h->stream, host, total, kernel));
+    else DQ_HIP(stage_in(h->device, h->stream, host, total, kernel));
+    return FLB_OK;
+}
+
 int flb_dq_get_populations(flb_dq_t *h, double *out, size_t n)
 {
     if (check(h)) return FLB_EINVAL;
     if (!out) return dq_fail(FLB_EINVAL, "out must not be NULL");
     const size_t total = (size_t)h->Q * h->V;
     if (n < total) return dq_fail(FLB_ESIZE, "output buffer smaller than Q*nx*ny*nz");
-    std::vector<float> buf(total);
-    DQ_HIP(hipStreamSynchronize(h->stream));
-    DQ_HIP(hipMemcpy(buf.data(), h->pops[h->cur], total * sizeof(float), hipMemcpyDeviceToHost));
-    // stored: post-collision values at their source sites; f_i(x) = stored_i(x - v_i)
-    const int nx = h->n[0], ny = h->n[1], nz = h->n[2];
-    for (int i = 0; i < h->Q; ++i)
-        for (int z = 0; z < nz; ++z)
-            for (int y = 0; y < ny; ++y)
-                for (int x = 0; x < nx; ++x) {
-                    const int xs = (x - h->v[i][0] + nx) % nx, ys = (y - h->v[i][1] + ny) % ny;
-                    const int zs = (z - h->v[i][2] + nz) % nz;
-                    out[(size_t)i * h->V + x + (size_t)nx * (y + (size_t)ny * z)] =
-                        (double)buf[(size_t)i * h->V + xs + (size_t)nx * (ys + (size_t)ny * zs)] +
-                        h->w[i] * h->rho0;
-                }
-    return FLB_OK;
+    return dq_copy(h, out, total, true);
 }
 
 int flb_dq_set_populations(flb_dq_t *h, const double *in, size_t n)
@@ -1163,21 +1260,7 @@ int flb_dq_set_populations(flb_dq_t *h, const double *in, size_t n)
     if (!in) return dq_fail(FLB_EINVAL, "in must not be NULL");
     const size_t total = (size_t)h->Q * h->V;
     if (n < total) return dq_fail(FLB_ESIZE, "input buffer smaller than Q*nx*ny*nz");
-    std::vector<float> buf(total);
-    const int nx = h->n[0], ny = h->n[1], nz = h->n[2];
-    for (int i = 0; i < h->Q; ++i)
-        for (int z = 0; z < nz; ++z)
-            for (int y = 0; y < ny; ++y)
-                for (int x = 0; x < nx; ++x) {
-                    const int xs = (x - h->v[i][0] + nx) % nx, ys = (y - h->v[i][1] + ny) % ny;
-                    const int zs = (z - h->v[i][2] + nz) % nz;
-                    buf[(size_t)i * h->V + xs + (size_t)nx * (ys + (size_t)ny * zs)] =
-                        (float)(in[(size_t)i * h->V + x + (size_t)nx * (y + (size_t)ny * z)] -
-                                h->w[i] * h->rho0);
-                }
-    DQ_HIP(hipStreamSynchronize(h->stream));
-    DQ_HIP(hipMemcpy(h->pops[h->cur], buf.data(), total * sizeof(float), hipMemcpyHostToDevice));
-    return FLB_OK;
+    return dq_copy(h, const_cast<double *>(in), total, false);
 }
 
 int flb_dq_thermalize(flb_dq_t *h)

@@ -161,9 +161,11 @@ hipError_t launch_march(const DeviceView &v, const StepItem *items, int nitems, 
                         int rows, uint32_t step_add, bool noise, hipStream_t s);
 hipError_t launch_advance_step(uint32_t *step, uint32_t n, hipStream_t s);
 hipError_t launch_init(const DeviceView &v, int lattice, int64_t plane, hipStream_t s);
-hipError_t launch_get(const DeviceView &v, int lattice, int nx, int ny, double *out_dev,
+// values first .. first + n - 1 of the lattice's FP64 populations, to or
+// from out / in (device or pinned host memory)
+hipError_t launch_get(const DeviceView &v, int lattice, int64_t first, int64_t n, double *out,
                       hipStream_t s);
-hipError_t launch_set(const DeviceView &v, int lattice, int nx, int ny, const double *in_dev,
+hipError_t launch_set(const DeviceView &v, int lattice, int64_t first, int64_t n, const double *in,
                       hipStream_t s);
 hipError_t launch_conservation(const DeviceView &v, int lattice, int nx, int ny, double *part,
                                int nblocks, double *out_dev, hipStream_t s);

@@ -24,6 +24,7 @@
 
 #include "../../include/flb.h"
 #include "flb_corr_internal.h"
+#include "flb_stage.h"
 
 using namespace flbdev;
 
@@ -1124,6 +1125,7 @@ flb_t *create_impl(int n, const flb_lattice_spec *specs, uint64_t seed, int stor
         if (validate_spec(specs[l], l) != FLB_OK) return nullptr;
 
     flb_t *h = new flb_t();
+    stage_retain();
     h->storage = storage;
     h->elem_bytes = storage == FLB_STORAGE_F32 ? 4 : 2;
     h->flags = flags;
@@ -1308,6 +1310,7 @@ void flb_destroy(flb_t *h)
         }
     if (h->aux) (void)hipStreamDestroy(h->aux);
     if (h->own) (void)hipStreamDestroy(h->own);
+    stage_release();
     delete h;
 }
 
@@ -1494,62 +1497,61 @@ int flb_run(flb_t *h, int64_t nsteps, int sample_every)
     return FLB_OK;
 }
 
+// Lattice `lattice`'s sums (times scale, if given) to out[kind][ky][kx].
+static int read_sums(flb_t *h, int lattice, double *out, size_t n_doubles, const SumScale *scale)
+{
+    const LatticeParams &P = h->params[lattice];
+    const size_t need = (size_t)h->nkinds * P.ny * P.nkx;
+    if (n_doubles < need) return fail(FLB_ESIZE, "output buffer too small for the correlators");
+    int rc;
+    if ((rc = settle_due(h)) || (rc = flush_pending(h))) return rc;
+    const DeviceView v = h->view();
+    FLB_HIP(stage_out(h->device, h->stream, out, need,
+                      [&](double *slot, size_t first, size_t n, hipStream_t s) {
+                          return launch_corr_export(v, lattice, first, n, scale, slot, s);
+                      }));
+    return FLB_OK;
+}
+
 int flb_read_correlators(flb_t *h, int lattice, double *out, size_t n_doubles, int64_t *nsamples)
 {
     if (check_lattice(h, lattice)) return FLB_EINVAL;
     if (!out) return fail(FLB_EINVAL, "out must not be NULL");
     int rc = setup_correlators(h);
     if (rc) return rc;
-    const LatticeParams &P = h->params[lattice];
-    const size_t need = (size_t)h->nkinds * P.ny * P.nkx;
-    if (n_doubles < need) return fail(FLB_ESIZE, "output buffer too small for the correlators");
-    if ((rc = settle_due(h)) || (rc = flush_pending(h))) return rc;
-    FLB_HIP(hipStreamSynchronize(h->stream));
-    // the device planes are column-tiled with kxp >= nkx columns: copied
-    // whole, then put in row order
-    const int ny = P.ny, nkx = P.nkx;
-    const int64_t plane = (int64_t)ny * P.kxp;
-    std::vector<double> tiled((size_t)(h->nkinds * plane));
-    FLB_HIP(hipMemcpy(tiled.data(), h->d_acc + P.acc_base, tiled.size() * sizeof(double),
-                      hipMemcpyDeviceToHost));
-    for (int q = 0; q < h->nkinds; ++q) {
-        const double *src = tiled.data() + q * plane;
-        double *dst = out + (size_t)q * ny * nkx;
-        for (int x0 = 0; x0 < nkx; x0 += kTileCols) {
-            const int w = std::min(kTileCols, nkx - x0);
-            const double *t = src + spec_offset(0, x0, ny);
-            for (int y = 0; y < ny; ++y)
-                for (int c = 0; c < w; ++c) dst[(size_t)y * nkx + x0 + c] = t[y * kTileCols + c];
-        }
-    }
+    if ((rc = read_sums(h, lattice, out, n_doubles, nullptr))) return rc;
     if (nsamples) *nsamples = h->nsamples;
     return FLB_OK;
 }
 
 int flb_read_normalized(flb_t *h, int lattice, double *out, size_t n_doubles, int64_t *nsamples)
 {
-    int64_t ns = 0;
-    int rc = flb_read_correlators(h, lattice, out, n_doubles, &ns);
+    if (check_lattice(h, lattice)) return FLB_EINVAL;
+    if (!out) return fail(FLB_EINVAL, "out must not be NULL");
+    int rc = setup_correlators(h);
     if (rc) return rc;
-    if (nsamples) *nsamples = ns;
     const flb_lattice_spec &s = h->specs[lattice];
-    if (ns <= 0) return fail(FLB_ESTATE, "no correlator sample to normalise");
-    if (!(s.theta > 0)) return fail(FLB_ESTATE, "theta = 0: no fluctuation scale to normalise by");
+    const int64_t ns = h->nsamples;
+    if (ns <= 0 || !(s.theta > 0)) {  // the raw sums, and why they are not normalised
+        if ((rc = read_sums(h, lattice, out, n_doubles, nullptr))) return rc;
+        if (nsamples) *nsamples = ns;
+        return fail(FLB_ESTATE, ns <= 0 ? "no correlator sample to normalise"
+                                        : "theta = 0: no fluctuation scale to normalise by");
+    }
     // Sec. 3, Eqs. (11)-(12) at the noise temperature theta (mu = 3 theta)
     const double V = (double)s.nx * (double)s.ny, mu = 3.0 * s.theta, rho0 = s.rho0;
     const double cs = 1.0 / std::sqrt(3.0), theta = s.theta;
-    double norm[FLB_NKINDS_MOMENTS];
+    SumScale scale;
+    double *norm = scale.norm;
+    scale.nsamples = (double)ns;
     norm[0] = 1.0 / (V * mu * rho0);
     norm[1] = norm[2] = 1.0 / (V * rho0 * theta);
     norm[3] = norm[4] = norm[5] = norm[6] = rho0 / (V * theta);
     for (int q = 7; q < 11; ++q) norm[q] = 1.0 / (V * mu * rho0 * cs);
     for (int q = 11; q < 15; ++q) norm[q] = 1.0 / (V * mu * cs);
     for (int q = 15; q < FLB_NKINDS_MOMENTS; ++q) norm[q] = 1.0 / (V * mu * rho0);
-    const size_t plane = (size_t)s.ny * (size_t)(s.nx / 2 + 1);
-    for (int q = 0; q < h->nkinds; ++q) {
-        double *p = out + q * plane;
-        for (size_t k = 0; k < plane; ++k) p[k] = p[k] / (double)ns * norm[q];
-    }
+    if ((rc = read_sums(h, lattice, out, n_doubles, &scale))) return rc;
+    if (nsamples) *nsamples = ns;
     return FLB_OK;
 }
 
@@ -1581,13 +1583,11 @@ int flb_get_populations(flb_t *h, int lattice, double *out, size_t n)
     const LatticeParams &P = h->params[lattice];
     const size_t need = 9 * (size_t)P.nx * (size_t)P.ny;
     if (n < need) return fail(FLB_ESIZE, "output buffer smaller than 9*nx*ny");
-    double *d = nullptr;
-    FLB_HIP(hipMalloc((void **)&d, need * sizeof(double)));
-    hipError_t e = launch_get(h->view(), lattice, P.nx, P.ny, d, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    if (e == hipSuccess) e = hipMemcpy(out, d, need * sizeof(double), hipMemcpyDeviceToHost);
-    (void)hipFree(d);
-    if (e != hipSuccess) return fail(FLB_EHIP, std::string("get populations: ") + hipGetErrorString(e));
+    const DeviceView v = h->view();
+    FLB_HIP(stage_out(h->device, h->stream, out, need,
+                      [&](double *slot, size_t first, size_t m, hipStream_t s) {
+                          return launch_get(v, lattice, (int64_t)first, (int64_t)m, slot, s);
+                      }));
     return FLB_OK;
 }
 
@@ -1606,7 +1606,7 @@ int flb_get_populations_noalloc(flb_t *h, int lattice, double *out, size_t n)
     if (rc) return rc;
     // every value the copy reads is written by the kernel first: nothing
     // needs clearing
-    FLB_HIP(launch_get(h->view(), lattice, P.nx, P.ny, d, h->stream));
+    FLB_HIP(launch_get(h->view(), lattice, 0, (int64_t)need, d, h->stream));
     FLB_HIP(hipMemcpyAsync(out, d, need * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     FLB_HIP(hipStreamSynchronize(h->stream));
     return FLB_OK;
@@ -1621,14 +1621,11 @@ int flb_set_populations(flb_t *h, int lattice, const double *in, size_t n)
     if (n < need) return fail(FLB_ESIZE, "input buffer smaller than 9*nx*ny");
     int rc = settle_due(h);
     if (rc) return rc;
-    double *d = nullptr;
-    FLB_HIP(hipMalloc((void **)&d, need * sizeof(double)));
-    hipError_t e = hipStreamSynchronize(h->stream);
-    if (e == hipSuccess) e = hipMemcpy(d, in, need * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = launch_set(h->view(), lattice, P.nx, P.ny, d, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    (void)hipFree(d);
-    if (e != hipSuccess) return fail(FLB_EHIP, std::string("set populations: ") + hipGetErrorString(e));
+    const DeviceView v = h->view();
+    FLB_HIP(stage_in(h->device, h->stream, in, need,
+                     [&](double *slot, size_t first, size_t m, hipStream_t s) {
+                         return launch_set(v, lattice, (int64_t)first, (int64_t)m, slot, s);
+                     }));
     return FLB_OK;
 }
 

@@ -1172,7 +1172,8 @@ hipError_t launch_init(const DeviceView &v, int lattice, int64_t plane, hipStrea
 
 // ---------------------------------------------------------------------
 // State export / import as full FP64 populations f_i(x) = w_i rho0 + d_i,
-// with d_i(x) = stored_i(x - v_i).
+// with d_i(x) = stored_i(x - v_i): values first .. first + n - 1 of the
+// lattice's [9][ny][nx] array, out[0] / in[0] being value `first`.
 // ---------------------------------------------------------------------
 __device__ constexpr double kWd[9] = {4.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9,
                                       1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
@@ -1180,70 +1181,73 @@ __device__ constexpr double kWd[9] = {4.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 
 template <int S>
 __global__ __launch_bounds__(kThreads) void get_kernel(const void *pops,
                                                        const LatticeParams *params, int lattice,
-                                                       double *out)
+                                                       int64_t first, int64_t n, double *out)
 {
     using T = typename Codec<S>::T;
     const LatticeParams &P = params[lattice];
     const int nx = P.nx, ny = P.ny, px = P.px;
     const int64_t V = (int64_t)nx * ny, plane = P.plane;
     const T *p = (const T *)pops + P.base;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < 9 * V;
-         k += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n;
+         j += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t k = first + j;
         const int i = (int)(k / V);
         const int s = (int)(k - (int64_t)i * V);
         const int y = s / nx, x = s - y * nx;
         const int xs = wrap_add(x, -kVX[i], nx), ys = wrap_add(y, -kVY[i], ny);
         const float d = Codec<S>::decode(p[(int64_t)i * plane + ys * px + xs], P, i);
-        out[k] = kWd[i] * (double)P.rho0 + (double)d;
+        out[j] = kWd[i] * (double)P.rho0 + (double)d;
     }
 }
 
 template <int S>
 __global__ __launch_bounds__(kThreads) void set_kernel(void *pops, const LatticeParams *params,
-                                                       int lattice, const double *in)
+                                                       int lattice, int64_t first, int64_t n,
+                                                       const double *in)
 {
     using T = typename Codec<S>::T;
     const LatticeParams &P = params[lattice];
     const int nx = P.nx, ny = P.ny, px = P.px;
     const int64_t V = (int64_t)nx * ny, plane = P.plane;
     T *p = (T *)pops + P.base;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < 9 * V;
-         k += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n;
+         j += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t k = first + j;
         const int i = (int)(k / V);
         const int s = (int)(k - (int64_t)i * V);
         const int y = s / nx, x = s - y * nx;
-        // stored_i(x) holds f_i(x + v_i)
-        const int xd = wrap_add(x, kVX[i], nx), yd = wrap_add(y, kVY[i], ny);
-        const double f = in[(int64_t)i * V + yd * nx + xd];
-        p[(int64_t)i * plane + y * px + x] = Codec<S>::encode((float)(f - kWd[i] * (double)P.rho0), P, i);
+        // f_i(x) is stored at x - v_i
+        const int xs = wrap_add(x, -kVX[i], nx), ys = wrap_add(y, -kVY[i], ny);
+        const double f = in[j];
+        p[(int64_t)i * plane + ys * px + xs] = Codec<S>::encode((float)(f - kWd[i] * (double)P.rho0), P, i);
     }
 }
 
-hipError_t launch_get(const DeviceView &v, int lattice, int nx, int ny, double *out_dev,
+hipError_t launch_get(const DeviceView &v, int lattice, int64_t first, int64_t n, double *out,
                       hipStream_t s)
 {
-    const dim3 grid(grid_for(9LL * nx * ny)), block(kThreads);
+    const dim3 grid(grid_for(n)), block(kThreads);
     const void *p = v.pops[v.cur];
     if (v.storage == kF32)
-        hipLaunchKernelGGL(get_kernel<kF32>, grid, block, 0, s, p, v.params, lattice, out_dev);
+        hipLaunchKernelGGL(get_kernel<kF32>, grid, block, 0, s, p, v.params, lattice, first, n, out);
     else if (v.storage == kBF16)
-        hipLaunchKernelGGL(get_kernel<kBF16>, grid, block, 0, s, p, v.params, lattice, out_dev);
+        hipLaunchKernelGGL(get_kernel<kBF16>, grid, block, 0, s, p, v.params, lattice, first, n, out);
     else
-        hipLaunchKernelGGL(get_kernel<kF16>, grid, block, 0, s, p, v.params, lattice, out_dev);
+        hipLaunchKernelGGL(get_kernel<kF16>, grid, block, 0, s, p, v.params, lattice, first, n, out);
     return hipGetLastError();
 }
 
-hipError_t launch_set(const DeviceView &v, int lattice, int nx, int ny, const double *in_dev,
+hipError_t launch_set(const DeviceView &v, int lattice, int64_t first, int64_t n, const double *in,
                       hipStream_t s)
 {
-    const dim3 grid(grid_for(9LL * nx * ny)), block(kThreads);
+    const dim3 grid(grid_for(n)), block(kThreads);
     void *p = v.pops[v.cur];
     if (v.storage == kF32)
-        hipLaunchKernelGGL(set_kernel<kF32>, grid, block, 0, s, p, v.params, lattice, in_dev);
+        hipLaunchKernelGGL(set_kernel<kF32>, grid, block, 0, s, p, v.params, lattice, first, n, in);
     else if (v.storage == kBF16)
-        hipLaunchKernelGGL(set_kernel<kBF16>, grid, block, 0, s, p, v.params, lattice, in_dev);
+        hipLaunchKernelGGL(set_kernel<kBF16>, grid, block, 0, s, p, v.params, lattice, first, n, in);
     else
-        hipLaunchKernelGGL(set_kernel<kF16>, grid, block, 0, s, p, v.params, lattice, in_dev);
+        hipLaunchKernelGGL(set_kernel<kF16>, grid, block, 0, s, p, v.params, lattice, first, n, in);
     return hipGetLastError();
 }
 
