@@ -11,7 +11,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ["flb_runtime.hip", "flb_step.hip", "flb_corr.hip", "flb_dq.hip",
-           "flb_stage.hip"]
+           "flb_small.hip", "flb_stage.hip"]
 LIB = os.path.join(HERE, "libflb.so")
 ARCH = "gfx950"
 

@@ -46,6 +46,7 @@ struct alignas(16) LatticeParams {
     int32_t nkx;              // nx/2 + 1
     int32_t tiles_x;          // step tiles along x
     int32_t px;               // storage row pitch: nx rounded up to 4
+    int32_t roots_x, roots_y; // tables of exp(-2 pi i j / n), small lattices only
     int32_t pad1;
     int64_t base;             // element offset of population 0 in pops[]
     int64_t plane;            // px*ny
@@ -189,6 +190,8 @@ struct LineTables {
     std::map<int, int> plan_of;
     LineTables();
     int plan_for(int n);  // index of the plan of length n (built on first use)
+    std::map<int, int> roots_of;
+    int roots_for(int n);  // offset of exp(-2 pi i j / n), j < n (built on first use)
 };
 // Lengths the LDS line transforms support: powers of two up to 4096, other
 // lengths up to 2048.

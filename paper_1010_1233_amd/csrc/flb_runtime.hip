@@ -24,6 +24,7 @@
 
 #include "../../include/flb.h"
 #include "flb_corr_internal.h"
+#include "flb_small.h"
 #include "flb_stage.h"
 
 using namespace flbdev;
@@ -112,6 +113,14 @@ struct flb {
     std::vector<int8_t> ltile;
     StepItem *d_items2 = nullptr;
     int nitems2 = 0;
+    // lattices small enough for one block each (flb_small.h): all of them
+    // are (then they step and sample resident in LDS while tblock = 0), and
+    // the threads and LDS of a block, stepping alone and with samples
+    int32_t *d_small = nullptr;
+    int n_small = 0, small_threads = 0;
+    int small_lds[3] = {0, 0, 0};  // steps only, samples, samples and their sums
+    bool small_keep = false;       // launches of several samples keep the sums in LDS
+    bool all_small() const { return n_small == (int)params.size(); }
     // marching launches of 4 and 5 steps ([0], [1]), with tblock = 0 and
     // lattices large enough for them
     bool march = false;
@@ -584,6 +593,43 @@ void clear_graphs(flb_t *h)
     h->graphs.clear();
 }
 
+// The list of small lattices and the block they need.
+int build_small_items(flb_t *h)
+{
+    std::vector<int32_t> items;
+    int threads = 0;
+    for (int &b : h->small_lds) b = 0;
+    for (size_t l = 0; l < h->params.size(); ++l) {
+        const LatticeParams &P = h->params[l];
+        if (!small_lattice(P.nx, P.ny)) continue;
+        items.push_back((int32_t)l);
+        threads = std::max(threads, (P.nx * P.ny + 63) / 64 * 64);
+        for (int q = 0; q < 3; ++q)
+            h->small_lds[q] = std::max(h->small_lds[q],
+                                       small_lds_bytes(P.nx, P.ny, q > 0, h->moments, q > 1));
+    }
+    // the sums in LDS where two blocks still share a compute unit, or the
+    // lattices need no sharing
+    int ncu = 0;
+    FLB_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
+    h->small_keep = h->small_lds[2] <= ((int)items.size() > ncu ? kLdsPerCu / 2 : kLdsPerCu);
+    h->n_small = (int)items.size();
+    h->small_threads = threads;
+    return upload(&h->d_small, items);
+}
+
+// The resident kernel: nsteps steps of lattices that are all small, the
+// samples inside (see launch_small).
+hipError_t launch_resident(flb_t *h, uint32_t step_add, uint32_t nsteps, uint32_t every,
+                           bool sample_first, hipStream_t s)
+{
+    const bool sampled = every || sample_first;
+    const bool keep = h->small_keep && every && nsteps >= 2 * every;
+    return launch_small(h->view(), h->d_small, h->n_small, h->small_threads,
+                        h->small_lds[sampled ? (keep ? 2 : 1) : 0], step_add, nsteps, every,
+                        sample_first, keep, h->noise, h->moments, s);
+}
+
 int is_pow2(int n) { return n > 0 && (n & (n - 1)) == 0; }
 
 int log2i(int n)
@@ -629,6 +675,19 @@ flbdev::LineTables::LineTables() : tables(kTwN / 2)
         const double ang = -2.0 * M_PI * k / kTwN;
         tables[k] = make_float2((float)std::cos(ang), (float)std::sin(ang));
     }
+}
+
+int flbdev::LineTables::roots_for(int n)
+{
+    auto it = roots_of.find(n);
+    if (it != roots_of.end()) return it->second;
+    const int off = (int)tables.size();
+    for (int j = 0; j < n; ++j) {
+        const double ang = -2.0 * M_PI * j / n;
+        tables.push_back(make_float2((float)std::cos(ang), (float)std::sin(ang)));
+    }
+    roots_of[n] = off;
+    return off;
 }
 
 int flbdev::LineTables::plan_for(int n)
@@ -749,9 +808,20 @@ int setup_correlators(flb_t *h)
     int nparts = 0;
     h->rows_lds = h->cols_lds = h->cols_l_lds = 0;
     for (auto &P : h->params) {
+        P.kxp = (P.nkx + 15) / 16 * 16;
+        P.spec_base = spec;
+        P.acc_base = acc;
+        acc += (int64_t)h->nkinds * P.ny * P.kxp;
+        if (small_lattice(P.nx, P.ny)) {  // transformed in LDS: no spectra
+            P.roots_x = lt.roots_for(P.nx);
+            P.roots_y = lt.roots_for(P.ny);
+            P.fld_part0 = nparts;
+            P.fld_nparts = 1;
+            nparts += 1;
+            continue;
+        }
         P.line_x = plan_for(P.nx);
         P.line_y = plan_for(P.ny);
-        P.kxp = (P.nkx + 15) / 16 * 16;
         // columns per block of the column kernel: at most 16, lines of at most
         // kColsElems LDS elements per block (kColsLargeElems for power-of-two
         // lengths from kColsLargeMin on, which take the large blocks)
@@ -762,10 +832,7 @@ int setup_correlators(flb_t *h)
         const int e = my << P.col_lgcb;  // padded like the row kernels' lines
         int &lds = P.col_large ? h->cols_l_lds : h->cols_lds;
         lds = std::max(lds, (e + (e >> 4) + (e >> 8) + 1) * (int)sizeof(float2));
-        P.spec_base = spec;
-        P.acc_base = acc;
         spec += (int64_t)h->nfld * P.ny * P.kxp;
-        acc += (int64_t)h->nkinds * P.ny * P.kxp;
         // FP32 moment planes, only with the moment spectra
         P.fld_base = fld;
         if (h->moments) fld += ((int64_t)kMomentFields * P.nx * P.ny + 63) / 64 * 64;
@@ -790,6 +857,7 @@ int setup_correlators(flb_t *h)
     std::map<int, std::vector<CorrItem>> pipe_full[2], pipe_part[2];  // per field set and lg
     for (size_t l = 0; l < h->params.size(); ++l) {
         const LatticeParams &P = h->params[l];
+        if (small_lattice(P.nx, P.ny)) continue;
         if (h->moments) {
             const int ntiles = P.fld_tiles_x * ((P.ny + kFieldRows - 1) / kFieldRows);
             for (int t = 0; t < ntiles; ++t) flds.push_back({(int32_t)l, t, 0, 0});
@@ -944,7 +1012,7 @@ int setup_correlators(flb_t *h)
         (rc = upload(&h->d_plans, h->plans)) ||
         (rc = upload(&h->d_tables, lt.tables)) || (rc = upload(&h->d_params, h->params)))
         return rc;
-    FLB_HIP(hipMalloc((void **)&h->d_spec, spec * sizeof(float2)));
+    if (spec > 0) FLB_HIP(hipMalloc((void **)&h->d_spec, spec * sizeof(float2)));
     FLB_HIP(hipMalloc((void **)&h->d_acc, acc * sizeof(double)));
     if (fld > 0) FLB_HIP(hipMalloc((void **)&h->d_fields, fld * sizeof(float)));
     if (h->defer)
@@ -965,6 +1033,11 @@ int setup_correlators(flb_t *h)
 int enqueue_sample(flb_t *h, hipStream_t s, hipEvent_t ev_read = nullptr)
 {
     const DeviceView v = h->view();
+    if (h->n_small) FLB_HIP(launch_resident(h, 0, 0, 0, true, s));
+    if (h->all_small()) {
+        if (ev_read) FLB_HIP(hipEventRecord(ev_read, s));
+        return FLB_OK;
+    }
     // the moment planes first, so that all reads of the state come first
     if (h->moments) FLB_HIP(launch_corr_moment_fields(v, h->d_fld, h->n_fld, s));
     for (int set = 0; set < (h->moments ? 2 : 1); ++set) {
@@ -1010,6 +1083,30 @@ int flush_pending(flb_t *h)
     return FLB_OK;
 }
 
+// With launch timing on (and no graph being captured), records the first
+// event of a launch of `steps` steps; stop is the one to record after it.
+int begin_timed(flb_t *h, int steps, hipStream_t s, hipEvent_t &stop)
+{
+    stop = nullptr;
+    if (!h->timing || h->capturing) return FLB_OK;
+    std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
+    if (!h->spare_events.empty()) {
+        ev = h->spare_events.back();
+        h->spare_events.pop_back();
+    } else {
+        FLB_HIP(hipEventCreate(&ev.first));
+        if (hipEventCreate(&ev.second) != hipSuccess) {
+            (void)hipEventDestroy(ev.first);
+            return fail(FLB_EHIP, "timing event creation failed");
+        }
+    }
+    h->timed.push_back(ev);
+    h->timed_steps.push_back(steps);
+    FLB_HIP(hipEventRecord(ev.first, s));
+    stop = ev.second;
+    return FLB_OK;
+}
+
 // n steps from the device counter value; the counter is advanced afterwards.
 // launch_plan says how the steps are grouped. When wait_before_second is
 // given, the second launch (the first to write the buffer that held the
@@ -1018,32 +1115,14 @@ int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_sec
 {
     int64_t k = 0;
     int launches = 0;
-    const bool timing = h->timing && !h->capturing;
     hipEvent_t stop = nullptr;
     auto before_launch = [&](int steps) -> int {
         if (launches++ == 1 && wait_before_second)
             FLB_HIP(hipStreamWaitEvent(s, wait_before_second, 0));
-        if (timing) {
-            std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
-            if (!h->spare_events.empty()) {
-                ev = h->spare_events.back();
-                h->spare_events.pop_back();
-            } else {
-                FLB_HIP(hipEventCreate(&ev.first));
-                if (hipEventCreate(&ev.second) != hipSuccess) {
-                    (void)hipEventDestroy(ev.first);
-                    return fail(FLB_EHIP, "timing event creation failed");
-                }
-            }
-            h->timed.push_back(ev);
-            h->timed_steps.push_back(steps);
-            FLB_HIP(hipEventRecord(ev.first, s));
-            stop = ev.second;
-        }
-        return FLB_OK;
+        return begin_timed(h, steps, s, stop);
     };
     auto after_launch = [&]() -> int {
-        if (timing) FLB_HIP(hipEventRecord(stop, s));
+        if (stop) FLB_HIP(hipEventRecord(stop, s));
         return FLB_OK;
     };
     const LaunchPlan plan = launch_plan(h, n);
@@ -1071,10 +1150,32 @@ int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_sec
     return FLB_OK;
 }
 
+// Steps per launch of the resident kernel (a launch of a few milliseconds).
+constexpr int64_t kResidentSteps = 4096;
+
+// n steps of lattices that are all small, resident, with a due sample before
+// them and samples at the multiples of `every` (0: none); the device counter
+// is advanced.
+int enqueue_resident(flb_t *h, int64_t n, int every, hipStream_t s)
+{
+    for (int64_t k = 0; k < n;) {
+        const int64_t m = std::min(n - k, kResidentSteps);
+        hipEvent_t stop = nullptr;
+        if (int rc = begin_timed(h, (int)m, s, stop)) return rc;
+        FLB_HIP(launch_resident(h, 0, (uint32_t)m, (uint32_t)every, h->due, s));
+        if (stop) FLB_HIP(hipEventRecord(stop, s));
+        h->due = false;
+        FLB_HIP(launch_advance_step(h->d_step, (uint32_t)m, s));
+        k += m;
+    }
+    return FLB_OK;
+}
+
 // n steps on stream s; a due sample of the state at their start runs on the
 // side stream beside them and s waits for its end.
 int enqueue_steps_overlapped(flb_t *h, int64_t n, hipStream_t s)
 {
+    if (n >= kResidentMin && h->tblock == 0 && h->all_small()) return enqueue_resident(h, n, 0, s);
     if (!h->due || n <= 0) return enqueue_steps(h, n, s);
     FLB_HIP(hipEventRecord(h->ev_fork, s));
     FLB_HIP(hipStreamWaitEvent(h->aux, h->ev_fork, 0));
@@ -1192,7 +1293,7 @@ flb_t *create_impl(int n, const flb_lattice_spec *specs, uint64_t seed, int stor
         fail(FLB_EHIP, "step counter reset failed");
         return bail(0);
     }
-    if (build_step_items(h) != FLB_OK) return bail(0);
+    if (build_step_items(h) != FLB_OK || build_small_items(h) != FLB_OK) return bail(0);
     for (int l = 0; l < n; ++l)
         if (launch_init(h->view(), l, h->params[l].plane, h->stream) != hipSuccess) {
             fail(FLB_EHIP, "init kernel launch failed");
@@ -1295,7 +1396,7 @@ void flb_destroy(flb_t *h)
                     h->d_accum, h->d_cols_l, h->d_fld, h->d_fields,
                     h->d_csum_part, h->d_csum, h->d_cols_lm, h->d_cols_m, h->d_rows_m,
                     h->d_rows_blue, h->d_stash, h->d_flush, h->d_items2, h->d_cols_blue,
-                    h->d_march[0], h->d_march[1]};
+                    h->d_march[0], h->d_march[1], h->d_small};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto &set : h->pipe)
@@ -1476,6 +1577,14 @@ int flb_run(flb_t *h, int64_t nsteps, int sample_every)
     if (sample_every == 0) return flb_step(h, nsteps);
     rc = setup_correlators(h);
     if (rc) return rc;
+    if (h->tblock == 0 && h->all_small()) {
+        // steps and samples resident, no graph (the last sample included)
+        const int64_t samples = (h->t + nsteps) / sample_every - h->t / sample_every;
+        if ((rc = enqueue_resident(h, nsteps, sample_every, h->stream))) return rc;
+        h->t += nsteps;
+        h->nsamples += samples;
+        return FLB_OK;
+    }
     while (nsteps > 0) {
         const int64_t phase = h->t % sample_every;
         if (phase == 0 && nsteps >= sample_every) {
@@ -1977,9 +2086,9 @@ static int time_shapes(flb_t *h, int nsteps, const std::vector<StepShape> &shape
                 const int tb = std::max(1, shapes[i].tb);  // whole launches
                 const int n = (nsteps + tb - 1) / tb * tb;
                 if ((rc = build_step_items(hh)) != FLB_OK) break;
-                if ((rc = enqueue_steps(hh, 2, hh->stream)) != FLB_OK) break;
+                if ((rc = enqueue_steps_overlapped(hh, 2, hh->stream)) != FLB_OK) break;
                 e = hipEventRecord(e0, hh->stream);
-                if (e == hipSuccess && (rc = enqueue_steps(hh, n, hh->stream)) != FLB_OK) break;
+                if (e == hipSuccess && (rc = enqueue_steps_overlapped(hh, n, hh->stream)) != FLB_OK) break;
                 if (e == hipSuccess) e = hipEventRecord(e1, hh->stream);
                 if (e == hipSuccess) e = hipEventSynchronize(e1);
                 float ms = 0;
