@@ -45,7 +45,9 @@
  *
  * Sample overlap (flb_set_sample_overlap): a sample registered by
  * flb_accumulate_correlators (or by flb_run at the end of a period) is
- * enqueued with the next steps, on an internal second stream beside them;
+ * enqueued with the next steps: on lattices large enough on an internal
+ * second stream beside them (on smaller ones before them, or inside the
+ * kernel that steps them);
  * the step that would overwrite the sampled state waits until the sample has
  * read it, and the work stream waits for the sample's end before the step
  * call's work is complete.  Results are identical to enqueueing the sample
@@ -164,12 +166,12 @@ int flb_set_sample_overlap(flb_t *h, int on);
 int flb_get_sample_overlap(flb_t *h);
 
 /* Launch timing: while on, every step-kernel launch that flb_step or
- * flb_run enqueues outside a captured graph is bracketed by a pair of HIP
+ * flb_run enqueues outside flb_run's whole periods is bracketed by a pair of HIP
  * events on the work stream, recorded after any wait on the sample, so the
  * pair measures that kernel's execution.  flb_get_launch_timing
  * synchronises the work stream and writes the number of timed launches and
  * the sum of their durations (ms) since the previous call, then starts a new
- * count.  Graph-replayed periods and flb_autotune's candidates are not
+ * count.  flb_run's whole periods and flb_autotune's candidates are not
  * timed; each timed launch keeps its event pair until it is read.
  * flb_get_launch_timing_kinds reads the same records split by the steps a
  * launch took: launches[q] and total_ms[q] (caller arrays of three) for the
@@ -185,10 +187,9 @@ int flb_step(flb_t *h, int64_t nsteps);
 
 /* Advances by nsteps and, after every step that reaches a time t with
  * t % sample_every == 0, adds a correlator sample (sample_every = 0: no
- * samples).  Whole periods of sample_every steps plus their sample are
- * replayed from a captured HIP graph (with sample overlap, each with the
- * previous period's sample beside its steps).  Enqueues only; with sample
- * overlap the last sample waits for the next steps or flb_synchronize. */
+ * samples): the calls of flb_step and flb_accumulate_correlators that this
+ * takes.  Enqueues only; with sample overlap the last sample may wait for
+ * the next steps or flb_synchronize. */
 int flb_run(flb_t *h, int64_t nsteps, int sample_every);
 
 /* Adds one sample of the current state of every lattice to its FP64

@@ -274,7 +274,7 @@ class Lattice:
         return bool(v)
 
     def set_launch_timing(self, on):
-        """Bracket every step-kernel launch enqueued outside a graph with a
+        """Bracket every step-kernel launch (but for run's whole periods) with a
         pair of HIP events (see ``launch_timing``)."""
         _check(lib().flb_set_launch_timing(self._h, int(bool(on))))
 

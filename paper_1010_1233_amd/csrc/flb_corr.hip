@@ -151,7 +151,7 @@ __device__ __forceinline__ void store_row_spectra(const float2 *lds, const Latti
 // rows use Bluestein's transform (other lengths than powers of two); the two
 // cases are separate instantiations so that the power-of-two one carries no
 // chirp state in registers.
-// item: lattice, first row, rows, index of the block's partial.
+// item: lattice, first row, rows (row_item), index of the block's partial.
 // At most 80 VGPRs (six waves per SIMD, three blocks per CU): the kernel is
 // bound by the latency of its transforms, and the third block hides more of
 // it.  Measured at 4096^2 (sample alone, whole path, row-kernel HBM bytes
@@ -159,6 +159,20 @@ __device__ __forceinline__ void store_row_spectra(const float2 *lds, const Latti
 // (6 values spilled) 0.77 ms, 83.4 GLUPS, 1.17; 64 VGPRs (28 spilled)
 // 0.80 ms, 84.1 GLUPS, 1.64, the spills' scratch traffic not worth the last
 // percent.
+// Small grids give each of a row group's three signals a block of its own
+// (it gathers the state again, from the L2): the kernel is then as long as
+// one signal's passes.  The block of the last signal writes the partial.
+struct RowItem {
+    int rows, lo, hi;  // signals lo .. hi - 1
+    __device__ __forceinline__ explicit RowItem(const CorrItem &it)
+    {
+        const int one = it.b >> 16;  // 0: all three
+        rows = it.b & 0xFFFF;
+        lo = one ? one - 1 : 0;
+        hi = one ? one : 3;
+    }
+};
+
 template <int S, bool BLUE>
 __global__ __launch_bounds__(kFftThreads, 6) void corr_rows_kernel(CorrArgs g)
 {
@@ -170,7 +184,8 @@ __global__ __launch_bounds__(kFftThreads, 6) void corr_rows_kernel(CorrArgs g)
     const LatticeParams &P = g.params[it.lattice];
     const LinePlan &L = g.plans[P.line_x];
     const int nx = P.nx;
-    const int y0 = it.a, nl = min(it.b, P.ny - y0);
+    const RowItem ri(it);
+    const int y0 = it.a, nl = min(ri.rows, P.ny - y0);
     const int m = L.m, lg = L.log2m, ne = nl * m;
     const T *p = (const T *)g.pops + P.base;
 
@@ -194,14 +209,14 @@ __global__ __launch_bounds__(kFftThreads, 6) void corr_rows_kernel(CorrArgs g)
             acc[4] += ((y0 + l) & 1) ? -Jy : Jy;
         }
     }
-    block_sum5<kFftThreads>(acc, g.csum_part + 5 * (int64_t)it.c);
+    if (ri.hi == 3) block_sum5<kFftThreads>(acc, g.csum_part + 5 * (int64_t)it.c);
 
     const float2 *chirp = g.tables + L.chirp_off;
     float2 *spec = g.spec + P.spec_base;
     const float rho0 = P.rho0, u0x = P.u0x, u0y = P.u0y;
     const float jx0 = rho0 * u0x, jy0 = rho0 * u0y;
 #pragma unroll 1
-    for (int sig = 0; sig < 3; ++sig) {
+    for (int sig = ri.lo; sig < ri.hi; ++sig) {
         // (the block sum and every earlier signal's reads of LDS are behind a
         // barrier before the lines are written)
         __syncthreads();
@@ -332,7 +347,8 @@ __device__ __forceinline__ void rows_p2_block(const CorrArgs &g, const CorrItem 
     static_assert(LG >= 9 && LG <= 12, "a line spans whole waves; a block holds 4096 elements");
     extern __shared__ float2 lds[];
     const LatticeParams &P = g.params[it.lattice];
-    const int y0 = it.a, nl = min(it.b, P.ny - y0);
+    const RowItem ri(it);
+    const int y0 = it.a, nl = min(ri.rows, P.ny - y0);
     const int t = (int)threadIdx.x, c = t & (H - 1);
     const int l = __builtin_amdgcn_readfirstlane(t >> (LG - 3));
     const T *p = (const T *)g.pops + P.base;
@@ -380,7 +396,7 @@ __device__ __forceinline__ void rows_p2_block(const CorrArgs &g, const CorrItem 
 #pragma unroll
         for (int j = 0; j < 8; ++j) r[j] = jx[j] = jy[j] = 0.f;
     }
-    block_sum5<kFftThreads>(acc, g.csum_part + 5 * (int64_t)it.c);
+    if (ri.hi == 3) block_sum5<kFftThreads>(acc, g.csum_part + 5 * (int64_t)it.c);
 
     const float2 *tw = g.tables;
     float2 *spec = g.spec + P.spec_base;
@@ -392,6 +408,7 @@ __device__ __forceinline__ void rows_p2_block(const CorrArgs &g, const CorrItem 
     // loop held every site value to its end and spilled)
 #pragma unroll
     for (int sig = 0; sig < 3; ++sig) {
+        if (sig < ri.lo || sig >= ri.hi) continue;
         // LDS addresses are recomputed for every signal rather than kept in
         // registers through the loop
         int tid = t;
@@ -488,7 +505,8 @@ __device__ __forceinline__ void rows_blue_block(const CorrArgs &g, const CorrIte
     const LatticeParams &P = g.params[it.lattice];
     const LinePlan &L = g.plans[P.line_x];
     const int nx = P.nx;
-    const int y0 = it.a, nl = min(it.b, P.ny - y0);
+    const RowItem ri(it);
+    const int y0 = it.a, nl = min(ri.rows, P.ny - y0);
     const int t = (int)threadIdx.x, c = t & (H - 1);
     // a line spans whole waves from 2^9 on
     const int l = LG >= 9 ? __builtin_amdgcn_readfirstlane(t >> (LG - 3)) : t >> (LG - 3);
@@ -522,7 +540,7 @@ __device__ __forceinline__ void rows_blue_block(const CorrArgs &g, const CorrIte
         acc[3] = (c & 1) ? -sx : sx;
         acc[4] = (y & 1) ? -sy : sy;
     }
-    block_sum5<kFftThreads>(acc, g.csum_part + 5 * (int64_t)it.c);
+    if (ri.hi == 3) block_sum5<kFftThreads>(acc, g.csum_part + 5 * (int64_t)it.c);
 
     const float2 *tw = g.tables;
     const float2 *kern = g.tables + L.kernel_off;
@@ -531,6 +549,7 @@ __device__ __forceinline__ void rows_blue_block(const CorrArgs &g, const CorrIte
     const float jx0 = rho0 * u0x, jy0 = rho0 * u0y;
 #pragma unroll
     for (int sig = 0; sig < 3; ++sig) {
+        if (sig < ri.lo || sig >= ri.hi) continue;
         int tid = t;
         asm volatile("" : "+v"(tid));
         const int cc = tid & (H - 1), base = (l * M) + cc;

@@ -4,8 +4,7 @@
 // per-lattice constant table, the step-kernel work list (one item per
 // (lattice, tile), ordered so that each XCD receives a contiguous run of
 // tiles), the correlator work lists, line plans and tables, the FP64
-// accumulators, a device step counter, and captured HIP graphs of one
-// sampling period.
+// accumulators and a device step counter.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -64,21 +63,6 @@ const double kW[9] = {4.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9,
 const int kVx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
 const int kVy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 
-// A captured sampling period: its length, the buffer holding the state at
-// its start, whether the sample of that state is due (it then runs beside
-// the period's steps) and how many stashed samples are pending (which
-// decides the accumulation modes of the period's samples).
-struct GraphKey {
-    int every, parity, pending, due;
-    bool operator<(const GraphKey &o) const
-    {
-        if (every != o.every) return every < o.every;
-        if (parity != o.parity) return parity < o.parity;
-        if (pending != o.pending) return pending < o.pending;
-        return due < o.due;
-    }
-};
-
 }  // namespace
 
 struct flb {
@@ -90,6 +74,7 @@ struct flb {
     std::vector<flb_lattice_spec> specs;
     std::vector<LatticeParams> params;
     int64_t total_elems = 0;  // per population buffer
+    int64_t total_sites = 0;
     bool noise = false;
 
     // device memory
@@ -188,17 +173,16 @@ struct flb {
     hipEvent_t ev_fork = nullptr, ev_read = nullptr, ev_done = nullptr;
 
     // launch timing (flb_set_launch_timing): an event pair around every step
-    // launch enqueued outside a graph capture, recorded after any wait so
+    // launch outside flb_run's whole periods, recorded after any wait so
     // that it brackets the kernel alone
-    bool timing = false, capturing = false;
+    bool timing = false;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> timed, spare_events;
     std::vector<int> timed_steps;  // steps of each timed launch
 
-    // streams and graphs
+    // streams
     hipStream_t own = nullptr;
     hipStream_t stream = nullptr;  // where work is enqueued
     hipEvent_t ev = nullptr;
-    std::map<GraphKey, hipGraphExec_t> graphs;
 
     DeviceView view() const
     {
@@ -529,7 +513,6 @@ int build_step_items(flb_t *h)
 // the longest first.
 struct LaunchPlan {
     int64_t of[6] = {0, 0, 0, 0, 0, 0};  // [steps of the launch]
-    int64_t launches() const { return of[1] + of[2] + of[3] + of[4] + of[5]; }
 };
 
 LaunchPlan launch_plan(const flb_t *h, int64_t n)
@@ -584,14 +567,6 @@ LaunchPlan launch_plan(const flb_t *h, int64_t n)
     return p;
 }
 
-// Kernel launches for n steps (the buffer parity flips once per launch).
-int64_t step_launches(const flb_t *h, int64_t n) { return launch_plan(h, n).launches(); }
-
-void clear_graphs(flb_t *h)
-{
-    for (auto &kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
-    h->graphs.clear();
-}
 
 // The list of small lattices and the block they need.
 int build_small_items(flb_t *h)
@@ -805,7 +780,30 @@ int setup_correlators(flb_t *h)
     auto plan_for = [&](int n) { return lt.plan_for(n); };
 
     int64_t spec = 0, acc = 0, fld = 0;
-    int nparts = 0;
+    int nparts = 0, ncu = 0;
+    FLB_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
+    // rows and columns of the lattices that the general transforms take
+    int64_t all_rows = 0, all_cols = 0;
+    for (auto &P : h->params)
+        if (!small_lattice(P.nx, P.ny)) {
+            all_rows += P.ny;
+            all_cols += (int64_t)kFields * P.nkx;
+        }
+    // Rows per block of the row kernels: up to 4096 line elements (32 KB of
+    // LDS), which they assume.  The kernels with run-time lengths take fewer
+    // where that leaves compute units without a block (the others work
+    // through 4096 elements whatever they hold): 256^2, one row a block
+    // instead of sixteen, 13 us instead of 22.
+    auto fixed_rows = [&](const LinePlan &L, int kxp) {
+        return L.bluestein ? corr_rows_blue_supported(L.log2m)
+                           : corr_rows_p2_supported(L.log2m) && kxp == L.m / 2 + 16;
+    };
+    auto rows_per_block = [&](const LatticeParams &P) {
+        const LinePlan &L = lt.plans[P.line_x];
+        const int rb = std::max(1, std::min(P.ny, 4096 / L.m));
+        if (fixed_rows(L, P.kxp)) return rb;
+        return (int)std::min<int64_t>(rb, (all_rows + ncu - 1) / ncu);
+    };
     h->rows_lds = h->cols_lds = h->cols_l_lds = 0;
     for (auto &P : h->params) {
         P.kxp = (P.nkx + 15) / 16 * 16;
@@ -838,11 +836,15 @@ int setup_correlators(flb_t *h)
         if (h->moments) fld += ((int64_t)kMomentFields * P.nx * P.ny + 63) / 64 * 64;
         P.fld_tiles_x = (P.nx + kThreads - 1) / kThreads;
         // one conservation partial per row group of the row kernel
-        const int mx = lt.plans[P.line_x].m;
-        const int rb = std::max(1, std::min(P.ny, 4096 / mx));
+        const int rb = rows_per_block(P);
         P.fld_part0 = nparts;
         P.fld_nparts = (P.ny + rb - 1) / rb;
         nparts += P.fld_nparts;
+// Sites from which a sample runs beside the steps.  Below, the waits between
+// the two streams cost more than they hide: 1024^2 119 us a period one after
+// the other, 127 side by side; 2048^2 398 and 380.
+constexpr int64_t kOverlapSites = 1 << 21;
+
     }
     h->spec_elems = spec;
     h->acc_elems = acc;
@@ -863,25 +865,29 @@ int setup_correlators(flb_t *h)
             for (int t = 0; t < ntiles; ++t) flds.push_back({(int32_t)l, t, 0, 0});
         }
         const int mx = lt.plans[P.line_x].m;
-        // rows per block: up to 4096 line elements (32 KB of LDS), which the
-        // row kernels assume
-        const int rb = std::max(1, std::min(P.ny, 4096 / mx));
+        const int rb = rows_per_block(P);
         if (rb * mx > 4096) return fail(FLB_ESIZE, "row transform longer than 4096 elements");
         // the row kernels pad their LDS lines (one slot per 16 and per 256);
         // the length-specialised one always transforms 4096 elements (lines
         // past the lattice's last row hold zeros)
         const LinePlan &Lx = lt.plans[P.line_x];
-        const bool p2 = !Lx.bluestein && corr_rows_p2_supported(Lx.log2m) && P.kxp == mx / 2 + 16;
-        const bool blue = Lx.bluestein && corr_rows_blue_supported(Lx.log2m);
+        const bool p2 = !Lx.bluestein && fixed_rows(Lx, P.kxp);
+        const bool blue = Lx.bluestein && fixed_rows(Lx, P.kxp);
         const int ne = (p2 || blue) ? 4096 : rb * mx;
         const int slots = ne + (ne >> 4) + (ne >> 8) + 1;
         h->rows_lds = std::max(h->rows_lds, slots * (int)sizeof(float2));
         for (int y = 0, part = P.fld_part0; y < P.ny; y += rb, ++part) {
-            const CorrItem ri{(int32_t)l, y, rb, part};
-            if (blue) rows_fixed_blue[11 - Lx.log2m].push_back(ri);
-            else if (Lx.bluestein) rows_blue.push_back(ri);
-            else if (p2) rows_fixed_p2[Lx.log2m].push_back(ri);
-            else rows.push_back(ri);
+            // one block, or one per signal (the kernels' RowItem)
+            for (int sig = 0; sig < (split ? 3 : 1); ++sig) {
+                const CorrItem ri{(int32_t)l, y, rb | (split ? (sig + 1) << 16 : 0), part};
+                if (blue) rows_fixed_blue[11 - Lx.log2m].push_back(ri);
+                else if (Lx.bluestein) rows_blue.push_back(ri);
+                else if (p2) rows_fixed_p2[Lx.log2m].push_back(ri);
+                else rows.push_back(ri);
+            }
+        // ... and down to 4 columns, a tile, where more would leave compute
+        // units without a block (256^2: 6.7 us instead of 9)
+        while (P.col_lgcb > 2 && (all_cols >> P.col_lgcb) < ncu) --P.col_lgcb;
             if (h->moments)
                 for (int sig = 0; sig < 3; ++sig) rows_m.push_back({(int32_t)l, y, rb, sig});
         }
@@ -908,6 +914,11 @@ int setup_correlators(flb_t *h)
                 for (int c0 = 0; c0 < P.nkx; c0 += 1 << P.col_lgcb) {
                     if (f < kFields && !cblue)
                         (P.col_large ? cols_l : cols).push_back({(int32_t)l, f, c0, P.col_lgcb});
+    // A block per signal where the row groups (nparts of them) leave the
+    // device partly idle and nothing runs beside the sample: 300 x 200 a
+    // sample in 20 us instead of 30, 512^2 16 and 20, 1000 x 700 (350 groups)
+    // 50 and 56; no gain from 900 x 2000 (1000 groups) on.
+    const bool split = nparts <= 2 * ncu && h->total_sites < kOverlapSites;
                     (P.col_large ? cols_lm : cols_m).push_back({(int32_t)l, f, c0, P.col_lgcb});
                 }
         }
@@ -937,8 +948,6 @@ int setup_correlators(flb_t *h)
     h->n_cols_lm = (int)cols_lm.size();
     h->n_rows_m = (int)rows_m.size();
     h->n_flush = (int)flush.size();
-    int ncu = 0;
-    FLB_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
     for (int set = 0; set < 2; ++set) {
         for (auto &pl : h->pipe[set])
             if (pl.d_sched) (void)hipFree(pl.d_sched);
@@ -1023,7 +1032,6 @@ int setup_correlators(flb_t *h)
     FLB_HIP(launch_fill(h->d_acc, (size_t)acc, h->stream));
     h->nsamples = 0;
     h->corr_ready = true;
-    clear_graphs(h);
     return FLB_OK;
 }
 
@@ -1083,12 +1091,12 @@ int flush_pending(flb_t *h)
     return FLB_OK;
 }
 
-// With launch timing on (and no graph being captured), records the first
+// With launch timing on, records the first
 // event of a launch of `steps` steps; stop is the one to record after it.
 int begin_timed(flb_t *h, int steps, hipStream_t s, hipEvent_t &stop)
 {
     stop = nullptr;
-    if (!h->timing || h->capturing) return FLB_OK;
+    if (!h->timing) return FLB_OK;
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
     if (!h->spare_events.empty()) {
         ev = h->spare_events.back();
@@ -1171,30 +1179,18 @@ int enqueue_resident(flb_t *h, int64_t n, int every, hipStream_t s)
     return FLB_OK;
 }
 
-// n steps on stream s; a due sample of the state at their start runs on the
-// side stream beside them and s waits for its end.
-int enqueue_steps_overlapped(flb_t *h, int64_t n, hipStream_t s)
+// Enqueues a due sample on the work stream.
+int settle_due(flb_t *h)
 {
     if (n >= kResidentMin && h->tblock == 0 && h->all_small()) return enqueue_resident(h, n, 0, s);
     if (!h->due || n <= 0) return enqueue_steps(h, n, s);
     FLB_HIP(hipEventRecord(h->ev_fork, s));
     FLB_HIP(hipStreamWaitEvent(h->aux, h->ev_fork, 0));
-    int rc = enqueue_sample(h, h->aux, h->ev_read);
-    if (rc) return rc;
+    if ((rc = enqueue_sample(h, h->aux, h->ev_read))) return rc;
     h->due = false;
     FLB_HIP(hipEventRecord(h->ev_done, h->aux));
     if ((rc = enqueue_steps(h, n, s, h->ev_read))) return rc;
     FLB_HIP(hipStreamWaitEvent(s, h->ev_done, 0));
-    return FLB_OK;
-}
-
-// Enqueues a due sample on the work stream.
-int settle_due(flb_t *h)
-{
-    if (!h->due) return FLB_OK;
-    int rc = enqueue_sample(h, h->stream);
-    if (rc) return rc;
-    h->due = false;
     return FLB_OK;
 }
 
@@ -1243,8 +1239,26 @@ flb_t *create_impl(int n, const flb_lattice_spec *specs, uint64_t seed, int stor
         off = (off + 63) / 64 * 64;  // 256-byte aligned planes per lattice
         for (int a = 0; a < 6; ++a) h->noise = h->noise || P.amp[a] != 0.0f;
         h->params.push_back(P);
+    if (!h->due) return FLB_OK;
+    int rc = enqueue_sample(h, h->stream);
+    if (rc) return rc;
+    h->due = false;
+    return FLB_OK;
+}
+
+// n steps; a due sample of the state at their start comes first, on the side
+// stream beside them on large lattices (the work stream then waits for its
+// end).
+int enqueue_steps_overlapped(flb_t *h, int64_t n)
+{
+    const hipStream_t s = h->stream;
     }
     h->total_elems = off;
+    int rc;
+    if (h->total_sites < kOverlapSites) {
+        if ((rc = settle_due(h))) return rc;
+        return enqueue_steps(h, n, s);
+    }
     // streaming accesses pay off once a buffer no longer fits the last-level
     // cache
     h->nontemporal = (double)off * h->elem_bytes > 256.0 * 1024 * 1024;
@@ -1308,6 +1322,7 @@ flb_t *create_impl(int n, const flb_lattice_spec *specs, uint64_t seed, int stor
 
 // Device address of `scratch` on device `dev`, looked up once per device
 // with that device current and kept.
+        h->total_sites += (int64_t)P.nx * P.ny;
 int scratch_on_device(int dev, double **out)
 {
     constexpr int kMaxDevices = 64;
@@ -1390,7 +1405,6 @@ void flb_destroy(flb_t *h)
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     if (h->own) (void)hipStreamSynchronize(h->own);
     if (h->aux) (void)hipStreamSynchronize(h->aux);
-    clear_graphs(h);
     void *ptrs[] = {h->pops[0], h->d_params, h->d_step, h->d_red, h->d_items,
                     h->d_plans, h->d_tables, h->d_spec, h->d_acc, h->d_rows, h->d_cols,
                     h->d_accum, h->d_cols_l, h->d_fld, h->d_fields,
@@ -1442,7 +1456,7 @@ int flb_step(flb_t *h, int64_t nsteps)
     if (check_handle(h)) return FLB_EINVAL;
     int rc = check_time(h, nsteps);
     if (rc) return rc;
-    rc = enqueue_steps_overlapped(h, nsteps, h->stream);
+    rc = enqueue_steps_overlapped(h, nsteps);
     if (rc) return rc;
     h->t += nsteps;
     return FLB_OK;
@@ -1468,10 +1482,7 @@ int flb_set_sample_overlap(flb_t *h, int on)
     if (check_handle(h)) return FLB_EINVAL;
     int rc = settle_due(h);
     if (rc) return rc;
-    if (h->overlap != (on != 0)) {
-        h->overlap = on != 0;
-        clear_graphs(h);
-    }
+    h->overlap = on != 0;
     return FLB_OK;
 }
 
@@ -1522,52 +1533,6 @@ int flb_get_launch_timing(flb_t *h, int64_t *launches, double *total_ms)
     return FLB_OK;
 }
 
-// One period of `every` steps followed by a sample, from a captured graph.
-static int run_period_graph(flb_t *h, int every)
-{
-    const bool due0 = h->due;
-    const GraphKey key{every, h->cur, h->pending, due0 ? 1 : 0};
-    auto it = h->graphs.find(key);
-    if (it == h->graphs.end()) {
-        // capture on the handle's own stream (capturing the legacy default
-        // stream is not allowed), then launch on the current stream; a due
-        // sample forks onto the side stream inside the capture and joins
-        // before its end
-        const int cur0 = h->cur;
-        const int pending0 = h->pending;
-        FLB_HIP(hipStreamBeginCapture(h->own, hipStreamCaptureModeRelaxed));
-        h->capturing = true;
-        int rc = enqueue_steps_overlapped(h, every, h->own);
-        if (!rc && !h->overlap) rc = enqueue_sample(h, h->own);  // the period's own sample
-        h->capturing = false;
-        hipGraph_t g = nullptr;
-        hipError_t e = hipStreamEndCapture(h->own, &g);
-        h->cur = cur0;
-        h->pending = pending0;
-        h->due = due0;
-        if (rc) {
-            if (g) (void)hipGraphDestroy(g);
-            return rc;
-        }
-        if (e != hipSuccess) return fail(FLB_EHIP, std::string("graph capture: ") + hipGetErrorString(e));
-        hipGraphExec_t ex = nullptr;
-        e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(g);
-        if (e != hipSuccess)
-            return fail(FLB_EHIP, std::string("graph instantiate: ") + hipGetErrorString(e));
-        it = h->graphs.emplace(key, ex).first;
-    }
-    FLB_HIP(hipGraphLaunch(it->second, h->stream));
-    if (step_launches(h, every) & 1) h->cur ^= 1;
-    // samples the graph enqueued: the due one, and without overlap its own
-    const int enqueued = (due0 ? 1 : 0) + (h->overlap ? 0 : 1);
-    if (h->defer) h->pending = (h->pending + enqueued) % kDeferK;
-    h->t += every;
-    h->nsamples += 1;
-    h->due = h->overlap;  // with overlap the period's sample runs beside the next steps
-    return FLB_OK;
-}
-
 int flb_run(flb_t *h, int64_t nsteps, int sample_every)
 {
     if (check_handle(h)) return FLB_EINVAL;
@@ -1578,30 +1543,26 @@ int flb_run(flb_t *h, int64_t nsteps, int sample_every)
     rc = setup_correlators(h);
     if (rc) return rc;
     if (h->tblock == 0 && h->all_small()) {
-        // steps and samples resident, no graph (the last sample included)
+        // steps and samples resident (the last sample included)
         const int64_t samples = (h->t + nsteps) / sample_every - h->t / sample_every;
-        if ((rc = enqueue_resident(h, nsteps, sample_every, h->stream))) return rc;
+        const bool timing = h->timing;
+        h->timing = false;
+        rc = enqueue_resident(h, nsteps, sample_every, h->stream);
+        h->timing = timing;
+        if (rc) return rc;
         h->t += nsteps;
         h->nsamples += samples;
         return FLB_OK;
     }
-    while (nsteps > 0) {
-        const int64_t phase = h->t % sample_every;
-        if (phase == 0 && nsteps >= sample_every) {
-            rc = run_period_graph(h, sample_every);
-            if (rc) return rc;
-            nsteps -= sample_every;
-            continue;
-        }
-        const int64_t to_sample = sample_every - phase;
+    // (plain launches: a captured graph per period was slower at every size,
+    // 256^2 73 against 60 us a period, 4096^2 1449 against 1406)
+    const bool timing = h->timing;
+    while (nsteps > 0 && !rc) {
+        const int64_t to_sample = sample_every - h->t % sample_every;
         const int64_t n = std::min(nsteps, to_sample);
         rc = flb_step(h, n);
-        if (rc) return rc;
         nsteps -= n;
-        if (n == to_sample) {
-            rc = flb_accumulate_correlators(h);
-            if (rc) return rc;
-        }
+        if (!rc && n == to_sample) rc = flb_accumulate_correlators(h);
     }
     return FLB_OK;
 }
@@ -1663,6 +1624,8 @@ int flb_read_normalized(flb_t *h, int lattice, double *out, size_t n_doubles, in
     if (nsamples) *nsamples = ns;
     return FLB_OK;
 }
+        // launch timing leaves out whole periods
+        h->timing = timing && n < sample_every;
 
 int flb_flush_correlators(flb_t *h)
 {
@@ -1682,7 +1645,8 @@ int flb_reset_correlators(flb_t *h)
     h->nsamples = 0;
     h->pending = 0;  // stashed and due samples are dropped with the sums
     h->due = false;
-    return FLB_OK;
+    h->timing = timing;
+    return rc;
 }
 
 int flb_get_populations(flb_t *h, int lattice, double *out, size_t n)
@@ -1877,7 +1841,6 @@ int flb_set_step_config(flb_t *h, int tile_w, int sites, int nontemporal)
     h->sites = sites;
     h->nontemporal = nontemporal != 0;
     if (h->tblock == 0) h->tblock = 1;  // the shape asked for, not the library's
-    clear_graphs(h);
     return build_step_items(h);
 }
 
@@ -1890,7 +1853,6 @@ int flb_set_time_blocking(flb_t *h, int steps_per_launch, int tile_w)
     FLB_HIP(hipStreamSynchronize(h->stream));
     h->tblock = steps_per_launch;
     h->tile2 = tile_w;
-    clear_graphs(h);
     return build_step_items(h);
 }
 
@@ -1916,7 +1878,6 @@ int flb_set_lattice_tiles(flb_t *h, const int *tile_w)
     h->tblock = 2;
     h->tile2 = 0;
     h->ltile = lt;
-    clear_graphs(h);
     return build_step_items(h);
 }
 
@@ -2060,7 +2021,6 @@ template <typename F> static int with_saved_state(flb_t *h, F body)
         e = hipMemcpyAsync(h->d_step, &step0, sizeof step0, hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     (void)hipFree(saved);
-    clear_graphs(h);
     if (rc != FLB_OK) return rc;
     if (e != hipSuccess) return fail(FLB_EHIP, std::string("autotune: ") + hipGetErrorString(e));
     return build_step_items(h);
@@ -2086,9 +2046,9 @@ static int time_shapes(flb_t *h, int nsteps, const std::vector<StepShape> &shape
                 const int tb = std::max(1, shapes[i].tb);  // whole launches
                 const int n = (nsteps + tb - 1) / tb * tb;
                 if ((rc = build_step_items(hh)) != FLB_OK) break;
-                if ((rc = enqueue_steps_overlapped(hh, 2, hh->stream)) != FLB_OK) break;
+                if ((rc = enqueue_steps_overlapped(hh, 2)) != FLB_OK) break;
                 e = hipEventRecord(e0, hh->stream);
-                if (e == hipSuccess && (rc = enqueue_steps_overlapped(hh, n, hh->stream)) != FLB_OK) break;
+                if (e == hipSuccess && (rc = enqueue_steps_overlapped(hh, n)) != FLB_OK) break;
                 if (e == hipSuccess) e = hipEventRecord(e1, hh->stream);
                 if (e == hipSuccess) e = hipEventSynchronize(e1);
                 float ms = 0;
@@ -2240,7 +2200,6 @@ int flb_autotune(flb_t *h, int nsteps, double *ms_out)
     if (cached_shape(cache, key, h->params.size(), c, ms)) {
         apply_shape(h, c);
         if (ms_out) *ms_out = ms;
-        clear_graphs(h);
         return build_step_items(h);
     }
     std::vector<std::pair<float, StepShape>> t;
@@ -2260,7 +2219,6 @@ int flb_autotune(flb_t *h, int nsteps, double *ms_out)
         }
     }
     apply_shape(h, pick);
-    clear_graphs(h);
     if (ms_out) *ms_out = pick_ms;
     cache_shape(cache, key, pick, pick_ms);
     return build_step_items(h);
@@ -2279,7 +2237,6 @@ int flb_autotune_path(flb_t *h, int nsteps, int sample_every, double *ms_out)
     if (cached_shape(cache, key, h->params.size(), c, ms)) {
         apply_shape(h, c);
         if (ms_out) *ms_out = ms;
-        clear_graphs(h);
         return build_step_items(h);
     }
     int rc = setup_correlators(h);
@@ -2315,7 +2272,6 @@ int flb_autotune_path(flb_t *h, int nsteps, int sample_every, double *ms_out)
             for (int round = 0; round < 2 && e == hipSuccess && r == FLB_OK; ++round)
                 for (size_t i = 0; i < cand.size() && e == hipSuccess && r == FLB_OK; ++i) {
                     apply_shape(hh, cand[i]);
-                    clear_graphs(hh);
                     if ((r = build_step_items(hh)) != FLB_OK) break;
                     if ((r = periods(4)) != FLB_OK) break;
                     e = hipEventRecord(e0, hh->stream);
@@ -2344,7 +2300,6 @@ int flb_autotune_path(flb_t *h, int nsteps, int sample_every, double *ms_out)
     for (size_t i = 1; i < cand.size(); ++i)
         if (best[i] < best[k]) k = i;
     apply_shape(h, cand[k]);
-    clear_graphs(h);
     if (ms_out) *ms_out = best[k];
     cache_shape(cache, key, cand[k], best[k]);
     return build_step_items(h);
