@@ -109,8 +109,6 @@ struct flb {
     // marching launches of 4 and 5 steps ([0], [1]), with tblock = 0 and
     // lattices large enough for them
     bool march = false;
-    StepItem *d_march[2] = {nullptr, nullptr};
-    int n_march[2] = {0, 0}, march_rows[2] = {0, 0};
     int64_t t = 0;
 
     // correlators
@@ -765,6 +763,11 @@ std::vector<PipeItem> pipe_items(const flb_t *h, const std::vector<CorrItem> &sc
     return out;
 }
 
+// Sites from which a sample runs beside the steps.  Below, the waits between
+// the two streams cost more than they hide: 1024^2 119 us a period one after
+// the other, 127 side by side; 2048^2 398 and 380.
+constexpr int64_t kOverlapSites = 1 << 21;
+
 int setup_correlators(flb_t *h)
 {
     if (h->corr_ready) return FLB_OK;
@@ -827,6 +830,9 @@ int setup_correlators(flb_t *h)
         P.col_large = !lt.plans[P.line_y].bluestein && my >= kColsLargeMin;
         P.col_lgcb =
             log2i(std::max(1, std::min(16, (P.col_large ? kColsLargeElems : kColsElems) / my)));
+        // ... and down to 4 columns, a tile, where more would leave compute
+        // units without a block (256^2: 6.7 us instead of 9)
+        while (P.col_lgcb > 2 && (all_cols >> P.col_lgcb) < ncu) --P.col_lgcb;
         const int e = my << P.col_lgcb;  // padded like the row kernels' lines
         int &lds = P.col_large ? h->cols_l_lds : h->cols_lds;
         lds = std::max(lds, (e + (e >> 4) + (e >> 8) + 1) * (int)sizeof(float2));
@@ -840,11 +846,6 @@ int setup_correlators(flb_t *h)
         P.fld_part0 = nparts;
         P.fld_nparts = (P.ny + rb - 1) / rb;
         nparts += P.fld_nparts;
-// Sites from which a sample runs beside the steps.  Below, the waits between
-// the two streams cost more than they hide: 1024^2 119 us a period one after
-// the other, 127 side by side; 2048^2 398 and 380.
-constexpr int64_t kOverlapSites = 1 << 21;
-
     }
     h->spec_elems = spec;
     h->acc_elems = acc;
@@ -857,6 +858,11 @@ constexpr int64_t kOverlapSites = 1 << 21;
     std::vector<CorrItem> rows_fixed_blue[4];
     std::map<int, std::vector<CorrItem>> rows_fixed_p2;
     std::map<int, std::vector<CorrItem>> pipe_full[2], pipe_part[2];  // per field set and lg
+    // A block per signal where the row groups (nparts of them) leave the
+    // device partly idle and nothing runs beside the sample: 300 x 200 a
+    // sample in 20 us instead of 30, 512^2 16 and 20, 1000 x 700 (350 groups)
+    // 50 and 56; no gain from 900 x 2000 (1000 groups) on.
+    const bool split = nparts <= 2 * ncu && h->total_sites < kOverlapSites;
     for (size_t l = 0; l < h->params.size(); ++l) {
         const LatticeParams &P = h->params[l];
         if (small_lattice(P.nx, P.ny)) continue;
@@ -885,9 +891,6 @@ constexpr int64_t kOverlapSites = 1 << 21;
                 else if (p2) rows_fixed_p2[Lx.log2m].push_back(ri);
                 else rows.push_back(ri);
             }
-        // ... and down to 4 columns, a tile, where more would leave compute
-        // units without a block (256^2: 6.7 us instead of 9)
-        while (P.col_lgcb > 2 && (all_cols >> P.col_lgcb) < ncu) --P.col_lgcb;
             if (h->moments)
                 for (int sig = 0; sig < 3; ++sig) rows_m.push_back({(int32_t)l, y, rb, sig});
         }
@@ -914,11 +917,6 @@ constexpr int64_t kOverlapSites = 1 << 21;
                 for (int c0 = 0; c0 < P.nkx; c0 += 1 << P.col_lgcb) {
                     if (f < kFields && !cblue)
                         (P.col_large ? cols_l : cols).push_back({(int32_t)l, f, c0, P.col_lgcb});
-    // A block per signal where the row groups (nparts of them) leave the
-    // device partly idle and nothing runs beside the sample: 300 x 200 a
-    // sample in 20 us instead of 30, 512^2 16 and 20, 1000 x 700 (350 groups)
-    // 50 and 56; no gain from 900 x 2000 (1000 groups) on.
-    const bool split = nparts <= 2 * ncu && h->total_sites < kOverlapSites;
                     (P.col_large ? cols_lm : cols_m).push_back({(int32_t)l, f, c0, P.col_lgcb});
                 }
         }
@@ -1182,8 +1180,26 @@ int enqueue_resident(flb_t *h, int64_t n, int every, hipStream_t s)
 // Enqueues a due sample on the work stream.
 int settle_due(flb_t *h)
 {
+    if (!h->due) return FLB_OK;
+    int rc = enqueue_sample(h, h->stream);
+    if (rc) return rc;
+    h->due = false;
+    return FLB_OK;
+}
+
+// n steps; a due sample of the state at their start comes first, on the side
+// stream beside them on large lattices (the work stream then waits for its
+// end).
+int enqueue_steps_overlapped(flb_t *h, int64_t n)
+{
+    const hipStream_t s = h->stream;
     if (n >= kResidentMin && h->tblock == 0 && h->all_small()) return enqueue_resident(h, n, 0, s);
     if (!h->due || n <= 0) return enqueue_steps(h, n, s);
+    int rc;
+    if (h->total_sites < kOverlapSites) {
+        if ((rc = settle_due(h))) return rc;
+        return enqueue_steps(h, n, s);
+    }
     FLB_HIP(hipEventRecord(h->ev_fork, s));
     FLB_HIP(hipStreamWaitEvent(h->aux, h->ev_fork, 0));
     if ((rc = enqueue_sample(h, h->aux, h->ev_read))) return rc;
@@ -1236,29 +1252,12 @@ flb_t *create_impl(int n, const flb_lattice_spec *specs, uint64_t seed, int stor
         LatticeParams P = make_params(specs[l], flags);
         P.base = off;
         off += 9 * P.plane;
+        h->total_sites += (int64_t)P.nx * P.ny;
         off = (off + 63) / 64 * 64;  // 256-byte aligned planes per lattice
         for (int a = 0; a < 6; ++a) h->noise = h->noise || P.amp[a] != 0.0f;
         h->params.push_back(P);
-    if (!h->due) return FLB_OK;
-    int rc = enqueue_sample(h, h->stream);
-    if (rc) return rc;
-    h->due = false;
-    return FLB_OK;
-}
-
-// n steps; a due sample of the state at their start comes first, on the side
-// stream beside them on large lattices (the work stream then waits for its
-// end).
-int enqueue_steps_overlapped(flb_t *h, int64_t n)
-{
-    const hipStream_t s = h->stream;
     }
     h->total_elems = off;
-    int rc;
-    if (h->total_sites < kOverlapSites) {
-        if ((rc = settle_due(h))) return rc;
-        return enqueue_steps(h, n, s);
-    }
     // streaming accesses pay off once a buffer no longer fits the last-level
     // cache
     h->nontemporal = (double)off * h->elem_bytes > 256.0 * 1024 * 1024;
@@ -1322,7 +1321,6 @@ int enqueue_steps_overlapped(flb_t *h, int64_t n)
 
 // Device address of `scratch` on device `dev`, looked up once per device
 // with that device current and kept.
-        h->total_sites += (int64_t)P.nx * P.ny;
 int scratch_on_device(int dev, double **out)
 {
     constexpr int kMaxDevices = 64;
@@ -1560,11 +1558,14 @@ int flb_run(flb_t *h, int64_t nsteps, int sample_every)
     while (nsteps > 0 && !rc) {
         const int64_t to_sample = sample_every - h->t % sample_every;
         const int64_t n = std::min(nsteps, to_sample);
+        // launch timing leaves out whole periods
+        h->timing = timing && n < sample_every;
         rc = flb_step(h, n);
         nsteps -= n;
         if (!rc && n == to_sample) rc = flb_accumulate_correlators(h);
     }
-    return FLB_OK;
+    h->timing = timing;
+    return rc;
 }
 
 // Lattice `lattice`'s sums (times scale, if given) to out[kind][ky][kx].
@@ -1624,8 +1625,6 @@ int flb_read_normalized(flb_t *h, int lattice, double *out, size_t n_doubles, in
     if (nsamples) *nsamples = ns;
     return FLB_OK;
 }
-        // launch timing leaves out whole periods
-        h->timing = timing && n < sample_every;
 
 int flb_flush_correlators(flb_t *h)
 {
@@ -1645,8 +1644,7 @@ int flb_reset_correlators(flb_t *h)
     h->nsamples = 0;
     h->pending = 0;  // stashed and due samples are dropped with the sums
     h->due = false;
-    h->timing = timing;
-    return rc;
+    return FLB_OK;
 }
 
 int flb_get_populations(flb_t *h, int lattice, double *out, size_t n)
