@@ -35,6 +35,7 @@
 namespace flbdev {
 
 constexpr int kThreads = 256;
+constexpr int kLdsPerCu = 160 * 1024;
 constexpr int kFields = 5;   // delta rho, delta jx, delta jy, delta ux, delta uy
 constexpr int kKinds = 15;
 constexpr int kMomentFields = 6;  // M^3 .. M^8, with the moment spectra
@@ -160,6 +161,12 @@ constexpr int kMarchWaves = 4;
 constexpr int march_cols(int steps) { return 64 - 2 * (steps - 1); }
 hipError_t launch_march(const DeviceView &v, const StepItem *items, int nitems, int steps,
                         int rows, uint32_t step_add, bool noise, hipStream_t s);
+// `steps` steps per launch on tiles of tw x th sites, item = lattice and
+// tile, for lattices too small to fill the device.
+constexpr int kPatchThreads = 1024;
+int patch_lds_bytes(int tw, int th, int steps);
+hipError_t launch_patch(const DeviceView &v, const StepItem *items, int nitems, int tw, int th,
+                        int steps, uint32_t step_add, bool noise, hipStream_t s);
 hipError_t launch_advance_step(uint32_t *step, uint32_t n, hipStream_t s);
 hipError_t launch_init(const DeviceView &v, int lattice, int64_t plane, hipStream_t s);
 // values first .. first + n - 1 of the lattice's FP64 populations, to or

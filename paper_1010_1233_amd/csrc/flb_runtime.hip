@@ -109,6 +109,11 @@ struct flb {
     // marching launches of 4 and 5 steps ([0], [1]), with tblock = 0 and
     // lattices large enough for them
     bool march = false;
+    // ... or launches of up to patch_steps steps on small tiles (0: not these)
+    int patch_steps = 0, patch_w = 0, patch_h = 0, n_patch = 0;
+    StepItem *d_patch = nullptr;
+    StepItem *d_march[2] = {nullptr, nullptr};
+    int n_march[2] = {0, 0}, march_rows[2] = {0, 0};
     int64_t t = 0;
 
     // correlators
@@ -480,6 +485,56 @@ int build_march_items(flb_t *h)
     return FLB_OK;
 }
 
+// Tile and steps per launch of the small-tile form, or none: the shape with
+// the least time per step by the kernel's bounds (us: a launch 4, a step's
+// barrier 0.12, four waves of a step 0.275 on a compute unit), among those
+// with at most one tile per compute unit.  Beyond that the tiles of three
+// and two steps are faster (us a step, ten steps a call, these against
+// those: 128^2 1.55 and 2.89, 256^2 1.88 and 3.00, 512^2 3.18 and 3.48, two
+// tiles per compute unit at 700 x 500 5.8 and 4.7).
+int build_patch_items(flb_t *h)
+{
+    h->patch_steps = 0;
+    if (h->tblock != 0 || h->march) return FLB_OK;
+    int ncu = 0;
+    FLB_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
+    auto tiles = [&](int tw, int th) {
+        int64_t n = 0;
+        for (const LatticeParams &P : h->params)
+            n += (int64_t)((P.nx + tw - 1) / tw) * ((P.ny + th - 1) / th);
+        return n;
+    };
+    double best = 2.95;
+    for (int tw : {8, 16, 32})
+        for (int th : {8, 16, 32}) {
+            if (th > tw) continue;
+            if (tiles(tw, th) > ncu) continue;
+            double work = 0;  // of all steps, from the last (no rings) back
+            for (int steps = 1; steps <= 12; ++steps) {
+                if (patch_lds_bytes(tw, th, steps) > kLdsPerCu) break;
+                const int n = (tw + 2 * steps - 2) * (th + 2 * steps - 2);
+                work += 0.12 + 0.275 * (((n + 63) / 64 + 3) / 4);
+                const double us = (4.0 + work) / steps;
+                if (us < best) {
+                    best = us;
+                    h->patch_steps = steps;
+                    h->patch_w = tw;
+                    h->patch_h = th;
+                }
+            }
+        }
+    if (!h->patch_steps) return FLB_OK;
+    std::vector<StepItem> items;
+    for (size_t l = 0; l < h->params.size(); ++l) {
+        const LatticeParams &P = h->params[l];
+        const int n = ((P.nx + h->patch_w - 1) / h->patch_w) * ((P.ny + h->patch_h - 1) / h->patch_h);
+        for (int t = 0; t < n; ++t) items.push_back({(int32_t)l, t});
+    }
+    items = xcd_order(items, StepItem{-1, 0});
+    h->n_patch = (int)items.size();
+    return upload(&h->d_patch, items);
+}
+
 int build_step_items(flb_t *h)
 {
     const int TH = kThreads / h->tile_w;
@@ -503,7 +558,7 @@ int build_step_items(flb_t *h)
         step2_items(h, h->tile2 == 0 ? &h->ltile : nullptr, h->tile2, nullptr);
     h->nitems2 = (int)items2.size();
     if ((rc = upload(&h->d_items2, items2))) return rc;
-    if ((rc = build_march_items(h))) return rc;
+    if ((rc = build_march_items(h)) || (rc = build_patch_items(h))) return rc;
     return upload(&h->d_params, h->params);
 }
 
@@ -1131,6 +1186,21 @@ int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_sec
         if (stop) FLB_HIP(hipEventRecord(stop, s));
         return FLB_OK;
     };
+    if (h->patch_steps && n > 1) {
+        // launches of (nearly) equal length
+        const int64_t launches = (n + h->patch_steps - 1) / h->patch_steps;
+        for (int64_t i = 0; i < launches; ++i) {
+            const int steps = (int)((n * (i + 1)) / launches - (n * i) / launches);
+            if (int rc = before_launch(steps)) return rc;
+            FLB_HIP(launch_patch(h->view(), h->d_patch, h->n_patch, h->patch_w, h->patch_h, steps,
+                                 (uint32_t)k, h->noise, s));
+            if (int rc = after_launch()) return rc;
+            h->cur ^= 1;
+            k += steps;
+        }
+        if (n > 0) FLB_HIP(launch_advance_step(h->d_step, (uint32_t)n, s));
+        return FLB_OK;
+    }
     const LaunchPlan plan = launch_plan(h, n);
     for (int steps = 5; steps >= 1; --steps)
         for (int64_t i = 0; i < plan.of[steps]; ++i, k += steps) {
@@ -1408,7 +1478,7 @@ void flb_destroy(flb_t *h)
                     h->d_accum, h->d_cols_l, h->d_fld, h->d_fields,
                     h->d_csum_part, h->d_csum, h->d_cols_lm, h->d_cols_m, h->d_rows_m,
                     h->d_rows_blue, h->d_stash, h->d_flush, h->d_items2, h->d_cols_blue,
-                    h->d_march[0], h->d_march[1], h->d_small};
+                    h->d_march[0], h->d_march[1], h->d_small, h->d_patch};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto &set : h->pipe)

@@ -23,7 +23,6 @@ constexpr int kResidentMin = 4;
 // LDS of a lattice's block, with or without samples, with or without the
 // sums beside them.
 int small_lds_bytes(int nx, int ny, bool sampled, bool moments, bool keep_sums);
-constexpr int kLdsPerCu = 160 * 1024;
 
 // nsteps steps of the nlat lattices listed (in place in v.pops[v.cur], one
 // block of `threads` >= sites each), with a sample of their state before

@@ -948,6 +948,122 @@ hipError_t launch_march(const DeviceView &v, const StepItem *items, int nitems, 
 }
 
 // ---------------------------------------------------------------------
+// Any number of steps per launch on small tiles, for lattices that leave
+// most of the device idle.  A block owns a tw x th tile; the region it
+// starts from adds steps - 1 rings.  Each step collides the box of sites
+// whose neighbours the step before left in LDS, one ring less every time,
+// from one LDS buffer into another (one barrier a step); the first step
+// reads HBM, the last writes it.  The threads share out each step's box
+// anew, so no wave is left with a ring's idle lanes.
+//
+// What bounds it: a launch (about 4 us with its first loads) and then the
+// VALU of the compute units that have a block, 0.28 us for every four waves
+// of a step.  So the tile is small enough to give every compute unit one,
+// and the rings, which grow with steps squared, are cheaper than another
+// launch: 256^2, ten steps in one launch of 16 x 16 tiles.
+// ---------------------------------------------------------------------
+template <int S, bool NOISE>
+__global__ __launch_bounds__(kPatchThreads) void patch_kernel(StepArgs g, int tw, int th, int steps)
+{
+    using E = typename Codec<S>::T;
+    extern __shared__ float buf[];  // two buffers of nine planes of the region
+    const StepItem it = g.items[blockIdx.x];
+    if (it.lattice < 0) return;
+    const LatticeParams &P = g.params[it.lattice];
+    const int nx = P.nx, ny = P.ny, px = P.px, plane = (int)P.plane;
+    const int tiles_x = (nx + tw - 1) / tw;
+    const int x0 = (it.tile % tiles_x) * tw, y0 = (it.tile / tiles_x) * th;
+    const int halo = steps - 1, w0 = tw + 2 * halo, h0 = th + 2 * halo, RN = w0 * h0;
+    const E *__restrict__ src = (const E *)g.src + P.base;
+    E *__restrict__ dst = (E *)g.dst + P.base;
+    const uint32_t t = *g.step + g.step_add;
+    for (int s = 0; s < steps; ++s) {
+        const int w = w0 - 2 * s, n = w * (h0 - 2 * s);
+        const float rw = 1.0f / (float)w;
+        const float *from = buf + ((s + 1) & 1) * 9 * RN;
+        float *to = buf + (s & 1) * 9 * RN;
+        for (int e = (int)threadIdx.x; e < n; e += kPatchThreads) {
+            // row of the box by a float reciprocal: (e + 1/2) / w is 1/(2 w)
+            // away from an integer (e < 2^13)
+            const int by = (int)(((float)e + 0.5f) * rw), bx = e - by * w;
+            int x = x0 - halo + s + bx, y = y0 - halo + s + by;
+            float d[9];
+            if (s == 0) {
+                while (x < 0) x += nx;
+                while (x >= nx) x -= nx;
+                while (y < 0) y += ny;
+                while (y >= ny) y -= ny;
+                const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
+                const int rc = y * px, rm = (y == 0 ? ny - 1 : y - 1) * px;
+                const int rp = (y == ny - 1 ? 0 : y + 1) * px;
+                d[0] = Work<S>::in(src[rc + x]);
+                d[1] = Work<S>::in(src[1 * plane + rc + xm]);
+                d[2] = Work<S>::in(src[2 * plane + rm + x]);
+                d[3] = Work<S>::in(src[3 * plane + rc + xp]);
+                d[4] = Work<S>::in(src[4 * plane + rp + x]);
+                d[5] = Work<S>::in(src[5 * plane + rm + xm]);
+                d[6] = Work<S>::in(src[6 * plane + rm + xp]);
+                d[7] = Work<S>::in(src[7 * plane + rp + xp]);
+                d[8] = Work<S>::in(src[8 * plane + rp + xm]);
+            } else {
+                const int c = (by + s) * w0 + bx + s;
+                d[0] = from[c];
+                d[1] = from[1 * RN + c - 1];
+                d[2] = from[2 * RN + c - w0];
+                d[3] = from[3 * RN + c + 1];
+                d[4] = from[4 * RN + c + w0];
+                d[5] = from[5 * RN + c - w0 - 1];
+                d[6] = from[6 * RN + c - w0 + 1];
+                d[7] = from[7 * RN + c + w0 + 1];
+                d[8] = from[8 * RN + c + w0 - 1];
+                while (x < 0) x += nx;
+                while (x >= nx) x -= nx;
+                while (y < 0) y += ny;
+                while (y >= ny) y -= ny;
+            }
+            update_site<NOISE, S>(d, P, (uint32_t)(y * nx + x), t + s, g.key0, g.key1);
+            if (s < halo) {
+                const int c = (by + s) * w0 + bx + s;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) to[i * RN + c] = stored<S>(d[i]);
+            } else if (x0 + bx < nx && y0 + by < ny) {
+                E *o = dst + y * px + x;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) o[i * plane] = Work<S>::out(d[i]);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+int patch_lds_bytes(int tw, int th, int steps)
+{
+    return steps < 2 ? 0 : 2 * 9 * (tw + 2 * steps - 2) * (th + 2 * steps - 2) * (int)sizeof(float);
+}
+
+hipError_t launch_patch(const DeviceView &v, const StepItem *items, int nitems, int tw, int th,
+                        int steps, uint32_t step_add, bool noise, hipStream_t s)
+{
+    const StepArgs a = step_args(v, items, step_add);
+    const dim3 grid(nitems), block(kPatchThreads);
+    const int lds = patch_lds_bytes(tw, th, steps);
+    if (steps < 1 || (tw + 2 * steps) * (th + 2 * steps) > 8192) return hipErrorInvalidValue;
+#define FLB_SEL(S_)                                                                              \
+    if (v.storage == S_) {                                                                       \
+        if (noise)                                                                               \
+            hipLaunchKernelGGL((patch_kernel<S_, true>), grid, block, lds, s, a, tw, th, steps); \
+        else                                                                                     \
+            hipLaunchKernelGGL((patch_kernel<S_, false>), grid, block, lds, s, a, tw, th, steps); \
+        return hipGetLastError();                                                                \
+    }
+    FLB_SEL(kF32)
+    FLB_SEL(kBF16)
+    FLB_SEL(kF16)
+#undef FLB_SEL
+    return hipErrorInvalidValue;
+}
+
+// ---------------------------------------------------------------------
 // Step counter
 // ---------------------------------------------------------------------
 __global__ void advance_step_kernel(uint32_t *step, uint32_t n)

@@ -577,12 +577,15 @@ def test_empty_calls_change_nothing(flb):
 
 @pytest.mark.parametrize("storage", ["f32", "bf16", "f16"])
 @pytest.mark.parametrize("sides", [[(2311, 1803)], [(2050, 2049)],
-                                   [(1000, 2200), (57, 9000), (4100, 901), (56, 58), (3, 2)]])
+                                   [(1000, 2200), (57, 9000), (4100, 901), (56, 58), (3, 2)],
+                                   [(66, 65)], [(256, 256)], [(300, 200), (70, 41), (2, 3)],
+                                   [(2, 900)], [(513, 500)]])
 @pytest.mark.parametrize("theta", [1e-4, 0.0])
 def test_library_grouping_equals_one_step_launches(flb, storage, sides, theta):
     """The library's own grouping of the steps (marching launches of four and
-    five steps on lattices this large, ragged strips and segments) gives the
-    bits of one step per launch, for every remainder."""
+    five steps on large lattices, ragged strips and segments; launches of many
+    steps on small tiles where the device would be idle) gives the bits of one
+    step per launch, for every remainder."""
     note("own grouping", storage, sides, theta)
     specs = [dict(nx=nx, ny=ny, tau=workloads.tau_vector(0.7, 1.1, 0.9), theta=theta,
                   u0=(0.04, -0.02), stream_id=7 + i) for i, (nx, ny) in enumerate(sides)]
@@ -593,7 +596,7 @@ def test_library_grouping_equals_one_step_launches(flb, storage, sides, theta):
     for g in (a, b):
         g.thermalize()
         g.set_populations(f)
-    for n in (1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 13):
+    for n in (1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 13, 25):
         a.step(n)
         b.step(n)
     for i in range(len(sides)):
