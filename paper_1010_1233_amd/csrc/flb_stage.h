@@ -3,10 +3,12 @@
 //
 // A transfer is cut into chunks.  Each chunk goes through a slot of pinned
 // host memory that a kernel writes (or reads) directly over PCIe, already
-// in the caller's layout and type; a worker thread per slot copies between
-// the slot and the caller's memory, so that the first touch of the caller's
-// pages, which a single thread does at about 10 GB/s, is spread over cores
-// and runs beside the next chunks' kernels.  No device memory is needed.
+// in the caller's layout and type; the calling thread and helper threads
+// copy between the slots and the caller's memory, each taking the next chunk
+// when it is free, so that the first touch of the caller's pages, which a
+// single thread does at about 10 GB/s, is spread over cores and runs beside
+// the next chunks' kernels, and a helper that finds no free core holds
+// nothing up.  No device memory is needed.
 #pragma once
 
 #include <stddef.h>
@@ -17,12 +19,12 @@
 
 namespace flbdev {
 
-constexpr int kStageSlots = 8;                      // worker threads at most
-constexpr size_t kStageSlotDoubles = (size_t)1 << 19;  // 4 MiB a slot
+constexpr int kStageWorkers = 8;  // threads of a transfer, the caller's among them
+constexpr size_t kStageSlotDoubles = (size_t)1 << 18;  // 2 MiB a slot, two per thread
 
 // Every open handle holds a reference; the slots (32 MiB, shared by all
-// handles, one transfer at a time) are allocated by the first transfer and
-// freed with the last reference.
+// handles, one transfer at a time) and the helper threads are made by the
+// first transfer that needs them and given back with the last reference.
 void stage_retain();
 void stage_release();
 

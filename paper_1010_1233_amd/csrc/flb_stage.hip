@@ -4,7 +4,7 @@
 #include <string.h>
 
 #include <algorithm>
-#include <atomic>
+#include <condition_variable>
 #include <mutex>
 #include <system_error>
 #include <thread>
@@ -14,118 +14,205 @@ namespace flbdev {
 
 namespace {
 
-std::mutex g_use;    // one transfer at a time; guards the slots
-std::mutex g_count;  // guards the reference count
-int g_refs = 0;
-double *g_slots = nullptr;
+// One transfer: the threads that have joined it take its chunks in turn.
+struct Job {
+    int device;
+    hipStream_t stream;
+    double *host;
+    size_t n, chunks;
+    bool to_host;
+    const StageKernel *kernel;
+    double *slots;
+    int seats = 0;   // threads that may still join (slots left)
+    int active = 0;  // threads at work (guarded by the pool's mutex)
+    int joined = 1;  // slot pairs handed out, the caller's first
+    std::mutex m;    // guards next and failed, and orders the launches
+    size_t next = 0;
+    hipError_t failed = hipSuccess;
+};
 
-// (caller holds g_use)
-hipError_t slots(double **p)
+// Takes the next chunk and enqueues its kernel into `slot` (from the
+// caller's memory: after copying the chunk there).  chunk: its index, or
+// job.chunks when none is left.
+hipError_t take(Job &j, double *slot, hipEvent_t ev, size_t &chunk)
 {
-    if (!g_slots) {
-        void *m = nullptr;
-        // portable: the transfers of every device go through the same slots
-        const hipError_t e = hipHostMalloc(&m, kStageSlots * kStageSlotDoubles * sizeof(double),
-                                           hipHostMallocPortable);
-        if (e != hipSuccess) return e;
-        g_slots = static_cast<double *>(m);
+    size_t first = 0, m = 0;
+    auto range = [&](size_t c) {
+        first = c * kStageSlotDoubles;
+        m = std::min(kStageSlotDoubles, j.n - first);
+    };
+    {
+        std::lock_guard<std::mutex> lock(j.m);
+        chunk = j.failed != hipSuccess ? j.chunks : std::min(j.next, j.chunks);
+        if (chunk == j.chunks) return hipSuccess;
+        ++j.next;
+        range(chunk);
+        if (j.to_host) {
+            hipError_t e = (*j.kernel)(slot, first, m, j.stream);
+            if (e == hipSuccess) e = hipEventRecord(ev, j.stream);
+            return e;
+        }
     }
-    *p = g_slots;
-    return hipSuccess;
+    memcpy(slot, j.host + first, m * sizeof(double));
+    std::lock_guard<std::mutex> lock(j.m);
+    hipError_t e = (*j.kernel)(slot, first, m, j.stream);
+    if (e == hipSuccess) e = hipEventRecord(ev, j.stream);
+    return e;
+}
+
+// A thread's share, through its two slots: one chunk's kernel runs while
+// the other's is copied.
+void work(Job &j, int seat)
+{
+    double *slot[2];
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    size_t chunk[2] = {j.chunks, j.chunks};  // in flight in each slot
+    hipError_t e = hipSuccess;
+    for (int q = 0; q < 2 && e == hipSuccess; ++q) {
+        slot[q] = j.slots + (size_t)(2 * seat + q) * kStageSlotDoubles;
+        e = hipEventCreateWithFlags(&ev[q], hipEventDisableTiming);
+        if (e == hipSuccess) e = take(j, slot[q], ev[q], chunk[q]);
+    }
+    for (int q = 0; e == hipSuccess && chunk[q] != j.chunks; q ^= 1) {
+        e = hipEventSynchronize(ev[q]);
+        if (e != hipSuccess) break;
+        if (j.to_host) {
+            const size_t first = chunk[q] * kStageSlotDoubles;
+            memcpy(j.host + first, slot[q],
+                   std::min(kStageSlotDoubles, j.n - first) * sizeof(double));
+        }
+        e = take(j, slot[q], ev[q], chunk[q]);
+    }
+    for (hipEvent_t x : ev)
+        if (x) (void)hipEventDestroy(x);
+    if (e != hipSuccess) {
+        std::lock_guard<std::mutex> lock(j.m);
+        j.failed = e;
+    }
+}
+
+// The helper threads and the slots.  (Never destroyed: helpers of handles
+// still open at the process's end sleep through it.)
+struct Pool {
+    std::mutex use;  // one transfer at a time; guards slots
+    double *slots = nullptr;
+    std::mutex m;  // guards the rest
+    std::condition_variable wake, done;
+    std::vector<std::thread> threads;
+    Job *job = nullptr;
+    bool stop = false;
+    int refs = 0;
+
+    void helper()
+    {
+        std::unique_lock<std::mutex> lock(m);
+        for (;;) {
+            wake.wait(lock, [&] { return stop || (job && job->seats > 0); });
+            if (stop) return;
+            Job &j = *job;
+            const int seat = j.joined++;
+            --j.seats;
+            ++j.active;
+            lock.unlock();
+            const hipError_t e = hipSetDevice(j.device);
+            if (e == hipSuccess) work(j, seat);  // (else: the others do it all)
+            lock.lock();
+            if (--j.active == 0) done.notify_all();
+        }
+    }
+};
+
+Pool &pool()
+{
+    static Pool *p = new Pool();
+    return *p;
 }
 
 hipError_t transfer(int device, hipStream_t s, double *host, size_t n, bool to_host,
                     const StageKernel &kernel)
 {
     if (!n) return hipStreamSynchronize(s);
-    std::lock_guard<std::mutex> use(g_use);
-    double *slot0 = nullptr;
-    hipError_t e = slots(&slot0);
-    if (e != hipSuccess) return e;
-    const size_t chunks = (n + kStageSlotDoubles - 1) / kStageSlotDoubles;
-    if (chunks == 1) {
-        if (!to_host) memcpy(slot0, host, n * sizeof(double));
-        if ((e = kernel(slot0, 0, n, s)) != hipSuccess) return e;
+    Pool &p = pool();
+    std::lock_guard<std::mutex> use(p.use);
+    if (!p.slots) {
+        void *mem = nullptr;
+        // portable: the transfers of every device go through the same slots
+        const hipError_t e = hipHostMalloc(
+            &mem, 2 * kStageWorkers * kStageSlotDoubles * sizeof(double), hipHostMallocPortable);
+        if (e != hipSuccess) return e;
+        p.slots = static_cast<double *>(mem);
+    }
+    Job j;
+    j.device = device;
+    j.stream = s;
+    j.host = host;
+    j.n = n;
+    j.chunks = (n + kStageSlotDoubles - 1) / kStageSlotDoubles;
+    j.to_host = to_host;
+    j.kernel = &kernel;
+    j.slots = p.slots;
+    if (j.chunks == 1) {
+        hipError_t e = hipSuccess;
+        if (!to_host) memcpy(p.slots, host, n * sizeof(double));
+        if ((e = kernel(p.slots, 0, n, s)) != hipSuccess) return e;
         if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        if (to_host) memcpy(host, slot0, n * sizeof(double));
+        if (to_host) memcpy(host, p.slots, n * sizeof(double));
         return hipSuccess;
     }
-
-    // worker w takes the chunks w, w + workers, ...
-    const int workers = (int)std::min<size_t>(chunks, kStageSlots);
-    std::mutex enqueue;
-    std::atomic<int> failed{0};
-    std::atomic<size_t> turn{0};
-    auto work = [&](bool own_thread) {
-        if (own_thread) {
-            const hipError_t d = hipSetDevice(device);
-            if (d != hipSuccess) {
-                failed = d;
-                return;
-            }
-        }
-        hipEvent_t ev = nullptr;
-        hipError_t q = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-        const int w = (int)(turn++ % kStageSlots);
-        double *slot = slot0 + (size_t)w * kStageSlotDoubles;
-        bool pending = false;  // a kernel may still read the slot
-        for (size_t c = (size_t)w; c < chunks && q == hipSuccess && !failed; c += workers) {
-            const size_t first = c * kStageSlotDoubles;
-            const size_t m = std::min(kStageSlotDoubles, n - first);
-            if (!to_host) {
-                if (pending) q = hipEventSynchronize(ev);
-                if (q != hipSuccess) break;
-                memcpy(slot, host + first, m * sizeof(double));
-            }
-            {
-                std::lock_guard<std::mutex> one(enqueue);
-                q = kernel(slot, first, m, s);
-                if (q == hipSuccess) q = hipEventRecord(ev, s);
-            }
-            pending = q == hipSuccess;
-            if (to_host && pending) {
-                q = hipEventSynchronize(ev);
-                if (q == hipSuccess) memcpy(host + first, slot, m * sizeof(double));
-            }
-        }
-        if (ev) (void)hipEventDestroy(ev);
-        if (q != hipSuccess) failed = q;
-    };
-    std::vector<std::thread> threads;
-    threads.reserve(workers);
-    for (int w = 1; w < workers; ++w) {
+    // a helper for every two chunks past the caller's own two
+    const int helpers = (int)std::min<size_t>((j.chunks - 1) / 2, kStageWorkers - 1);
+    if (helpers) {
+        std::lock_guard<std::mutex> lock(p.m);
         try {
-            threads.emplace_back(work, true);
+            while ((int)p.threads.size() < helpers)
+                p.threads.emplace_back([&p] { p.helper(); });
         } catch (const std::system_error &) {
-            break;  // fewer threads: the missing workers' chunks are done below
+            // fewer helpers, or none: the caller's thread does the rest
         }
+        j.seats = helpers;
+        p.job = &j;
     }
-    const int missing = workers - 1 - (int)threads.size();
-    work(false);
-    for (std::thread &t : threads) t.join();
-    for (int w = 0; w < missing; ++w) work(false);
-    if (failed) {
-        (void)hipStreamSynchronize(s);  // nothing uses the slots any more
-        return (hipError_t)failed.load();
+    for (int i = 0; i < helpers; ++i) p.wake.notify_one();
+    work(j, 0);
+    if (helpers) {
+        // no more joining; wait for those at work
+        std::unique_lock<std::mutex> lock(p.m);
+        p.job = nullptr;
+        p.done.wait(lock, [&] { return j.active == 0; });
     }
-    return hipStreamSynchronize(s);
+    // every kernel that uses a slot has ended (a failed transfer may have
+    // left some behind)
+    const hipError_t e = hipStreamSynchronize(s);
+    return j.failed != hipSuccess ? j.failed : e;
 }
 
 }  // namespace
 
 void stage_retain()
 {
-    std::lock_guard<std::mutex> lock(g_count);
-    ++g_refs;
+    std::lock_guard<std::mutex> lock(pool().m);
+    ++pool().refs;
 }
 
 void stage_release()
 {
-    std::lock_guard<std::mutex> lock(g_count);
-    if (--g_refs > 0) return;
-    std::lock_guard<std::mutex> use(g_use);
-    if (g_slots) (void)hipHostFree(g_slots);
-    g_slots = nullptr;
+    Pool &p = pool();
+    std::lock_guard<std::mutex> use(p.use);
+    std::vector<std::thread> threads;
+    {
+        std::lock_guard<std::mutex> lock(p.m);
+        if (--p.refs > 0) return;
+        p.stop = true;
+        threads.swap(p.threads);
+    }
+    p.wake.notify_all();
+    for (std::thread &t : threads) t.join();
+    {
+        std::lock_guard<std::mutex> lock(p.m);
+        p.stop = false;
+    }
+    if (p.slots) (void)hipHostFree(p.slots);
+    p.slots = nullptr;
 }
 
 hipError_t stage_out(int device, hipStream_t s, double *out, size_t n, const StageKernel &kernel)

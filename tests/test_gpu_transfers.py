@@ -1,5 +1,5 @@
 """Reads and writes of whole states and sums through the pinned staging slots
-(4 MiB each, up to eight at a time): sizes below, at and past a slot and past
+(2 MiB each, two per thread, up to sixteen at a time): sizes below, at and past a slot and past
 all eight, from one thread and from two."""
 import ctypes
 import threading
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 TAU = workloads.tau_vector(0.8, 1.0, 1.0)
 _dp = ctypes.POINTER(ctypes.c_double)
-SLOT = 1 << 19  # doubles per slot
+SLOT = 1 << 18  # doubles per slot
 
 
 def _noalloc(flb, g):
@@ -23,7 +23,7 @@ def _noalloc(flb, g):
     return out
 
 
-# 9 nx ny: one slot less nine, one slot and a bit, two, fourteen slots
+# 9 nx ny: two slots less a few values, two and a bit, four and a bit, 28
 @pytest.mark.parametrize("nx,ny", [(29126, 2), (233, 250), (257, 455), (901, 899)])
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
 def test_populations_through_the_slots(flb, nx, ny, storage):
