@@ -55,16 +55,136 @@ template <> struct DqSet<FLB_DQ_D3Q15> {
                                      {-1, 1, -1}, {1, -1, -1}, {-1, -1, -1}};
 };
 
+// Square root at compile time (Newton's iteration, x > 0).
+constexpr double dq_sqrt(double x)
+{
+    double r = x > 1 ? x : 1.0;
+    for (int k = 0; k < 64; ++k) r = 0.5 * (r + x / r);
+    return r;
+}
+
+// The velocity polynomials of flb_dq.h, in order.
+constexpr double dq_poly(int D, int a, const int (&v)[3])
+{
+    const double x = v[0], y = v[1], z = v[2], v2 = x * x + y * y + z * z;
+    if (a == 0) return 1.0;
+    if (a <= D) return (double)v[a - 1];
+    if (D == 1) return x * x - 1.0 / 3.0;
+    if (D == 2) {
+        const double p[9] = {0, 0, 0, x * x - y * y, x * y, v2 - 2.0 / 3.0, x * v2, y * v2, v2 * v2};
+        return p[a];
+    }
+    const double p[15] = {0, 0, 0, 0, 3 * x * x - v2, y * y - z * z, x * y, y * z, z * x, v2 - 1.0,
+                          x * v2, y * v2, z * v2, x * y * z, v2 * v2};
+    return p[a];
+}
+
+// A model's weights and moments at compile time: the polynomials
+// orthonormalised under the weights in their order (Eq. 4), the velocities'
+// opposite pairs, and which moments are even or odd in v.  In the kernels
+// every coefficient is an instruction's constant, zeros cost nothing, and a
+// pair enters the even moments by its sum and the odd ones by its
+// difference.
+template <int MODEL> struct DqTables {
+    using S = DqSet<MODEL>;
+    static constexpr int D = S::D, Q = S::Q, NP = (Q - 1) / 2;
+    double w[Q] = {}, m[Q][Q] = {};
+    float mf[Q][Q] = {};        // m[a][i]
+    float nw[Q][Q] = {};        // w_i m_i^a, as nw[a][i]
+    float wf[Q] = {};
+    float T[6][3][3] = {};      // stress tensors of the stress modes, in order
+    int pa[NP] = {}, pb[NP] = {};  // pairs v[pb] = -v[pa]
+    bool odd[Q] = {};           // m[a][pb] = -m[a][pa]
+    bool scalar[Q] = {};        // even, and the same on every velocity of a length
+    int shell[NP] = {};         // 0: the shortest velocities, 1: the others
+    float shell_m[Q][2] = {}, shell_nw[Q][2] = {};  // a scalar moment's mf and nw on each
+
+    constexpr DqTables()
+    {
+        for (int i = 0; i < Q; ++i) {
+            const int l = S::v[i][0] * S::v[i][0] + S::v[i][1] * S::v[i][1] + S::v[i][2] * S::v[i][2];
+            w[i] = D == 1 ? (l == 0 ? 2.0 / 3.0 : 1.0 / 6.0)
+                 : D == 2 ? (l == 0 ? 4.0 / 9.0 : l == 1 ? 1.0 / 9.0 : 1.0 / 36.0)
+                          : (l == 0 ? 2.0 / 9.0 : l == 1 ? 1.0 / 9.0 : 1.0 / 72.0);
+        }
+        for (int a = 0; a < Q; ++a) {
+            double h[Q] = {};
+            for (int i = 0; i < Q; ++i) h[i] = dq_poly(D, a, S::v[i]);
+            for (int b = 0; b < a; ++b) {
+                double p = 0.0;
+                for (int i = 0; i < Q; ++i) p += w[i] * h[i] * m[b][i];
+                for (int i = 0; i < Q; ++i) h[i] -= p * m[b][i];
+            }
+            double nrm = 0.0;
+            for (int i = 0; i < Q; ++i) nrm += w[i] * h[i] * h[i];
+            nrm = dq_sqrt(nrm);
+            for (int i = 0; i < Q; ++i) m[a][i] = h[i] / nrm;
+        }
+        int np = 0;
+        for (int i = 1; i < Q; ++i)
+            for (int j = i + 1; j < Q; ++j)
+                if (S::v[i][0] == -S::v[j][0] && S::v[i][1] == -S::v[j][1] &&
+                    S::v[i][2] == -S::v[j][2]) {
+                    const int l = S::v[i][0] * S::v[i][0] + S::v[i][1] * S::v[i][1] +
+                                  S::v[i][2] * S::v[i][2];
+                    shell[np] = l > 1;
+                    pa[np] = i;
+                    pb[np++] = j;
+                }
+        for (int a = 0; a < Q; ++a) {
+            for (int i = 0; i < Q; ++i) {
+                // what is 0 up to rounding is 0
+                const bool zero = m[a][i] < 1e-12 && m[a][i] > -1e-12;
+                mf[a][i] = zero ? 0.f : (float)m[a][i];
+                nw[a][i] = zero ? 0.f : (float)(w[i] * m[a][i]);
+            }
+            double sum = 0.0;  // of m[a][pa] m[a][pb]: negative if odd
+            for (int p = 0; p < NP; ++p) sum += m[a][pa[p]] * m[a][pb[p]];
+            odd[a] = sum < 0;
+            scalar[a] = !odd[a];
+            for (int p = 0; p < NP; ++p)
+                for (int q = 0; q < NP; ++q) {
+                    const double d = m[a][pa[p]] - m[a][pa[q]];
+                    if (shell[p] == shell[q] && (d > 1e-12 || d < -1e-12)) scalar[a] = false;
+                }
+        }
+        for (int a = 0; a < Q; ++a)
+            for (int p = 0; p < NP; ++p)
+                if (scalar[a]) {
+                    shell_m[a][shell[p]] = mf[a][pa[p]];
+                    shell_nw[a][shell[p]] = nw[a][pa[p]];
+                }
+        for (int i = 0; i < Q; ++i) wf[i] = (float)w[i];
+        for (int s = 0; s < D * (D + 1) / 2; ++s)
+            for (int al = 0; al < D; ++al)
+                for (int be = 0; be < D; ++be) {
+                    double t = 0;
+                    for (int i = 0; i < Q; ++i)
+                        t += w[i] * m[D + 1 + s][i] * S::v[i][al] * S::v[i][be];
+                    T[s][al][be] = (t < 1e-12 && t > -1e-12) ? 0.f : (float)t;
+                }
+    }
+};
+template <int MODEL> struct DqConst {
+    static constexpr DqTables<MODEL> C{};
+};
+
+// f(0), ..., f(N - 1) with the index a compile-time constant.
+template <int N, int I = 0, typename F> __device__ __forceinline__ void dq_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        dq_for<N, I + 1>(f);
+    }
+}
+
 struct DqParams {
     int32_t n[3];
-    int32_t tiles_x;            // blocks of kDqThreads sites along x
+    uint32_t V;
+    uint32_t mul[2], sh[2];     // division of a site by n[0], of a row by n[1] (dq_div)
     uint32_t stream_id;
     float rho0;
     float u0[3];
-    float m[kDqMaxQ][kDqMaxQ];  // m[a][i]
-    float nw[kDqMaxQ][kDqMaxQ]; // w_i m_i^a, as nw[a][i]
-    float w[kDqMaxQ];
-    float T[6][3][3];           // stress tensors of the stress modes, in order
     float omega[kDqMaxQ];       // 1/tau^a
     float amp[kDqMaxQ];         // sigma_a (Eq. 8)
     float therm[kDqMaxQ];       // sqrt(mu rho0 w_i)
@@ -75,16 +195,33 @@ struct DqParams {
 
 __device__ __forceinline__ int wrapi(int x, int n) { return x < 0 ? x + n : (x >= n ? x - n : x); }
 
-// Site of a thread: tiles of kDqThreads sites along x, one row (y, z) per
-// block row.  Returns false past the end of the row.
-__device__ __forceinline__ bool dq_site(const DqParams &P, int &x, int &y, int &z)
+// n / d for n < 2^31 by the multiplier and shift of dq_divisor(d), d >= 2.
+__device__ __forceinline__ uint32_t dq_div(uint32_t n, uint32_t mul, uint32_t sh)
 {
-    const int row = (int)(blockIdx.x / (uint32_t)P.tiles_x);
-    const int tile = (int)blockIdx.x - row * P.tiles_x;
-    x = tile * kDqThreads + (int)threadIdx.x;
-    y = row % P.n[1];
-    z = row / P.n[1];
-    return x < P.n[0];
+    return __umulhi(n, mul) >> sh;
+}
+inline void dq_divisor(uint32_t d, uint32_t &mul, uint32_t &sh)
+{
+    uint32_t l = 1;  // ceil(log2 d)
+    while (((uint64_t)1 << l) < d) ++l;
+    mul = (uint32_t)(((uint64_t)1 << (31 + l)) / d + 1);
+    sh = l - 1;
+}
+
+// Site of a thread: sites in their storage order, whatever the sides, so
+// that every lane of every block but the last has one.
+template <int D>
+__device__ __forceinline__ bool dq_site(const DqParams &P, uint32_t &site, int &x, int &y, int &z)
+{
+    site = blockIdx.x * (uint32_t)kDqThreads + threadIdx.x;
+    if (site >= P.V) return false;
+    uint32_t row = 0, plane = 0;
+    if (D > 1) row = dq_div(site, P.mul[0], P.sh[0]);
+    if (D > 2) plane = dq_div(row, P.mul[1], P.sh[1]);
+    x = (int)(site - row * (uint32_t)P.n[0]);
+    y = (int)(row - plane * (uint32_t)P.n[1]);
+    z = (int)plane;
+    return true;
 }
 
 // Element `off` of a buffer through a 32-bit byte offset from a wave-uniform
@@ -114,38 +251,53 @@ __device__ __forceinline__ void dq_pull(const float *__restrict__ src, const DqP
     }
 }
 
+// M^a = sum_i m_i^a d_i: from the sums and differences of the opposite
+// pairs, the scalar moments from the sums over a shell.
 template <int MODEL>
-__device__ __forceinline__ void dq_moments(const DqParams &P, const float (&d)[DqSet<MODEL>::Q],
+__device__ __forceinline__ void dq_moments(const float (&d)[DqSet<MODEL>::Q],
                                            float (&M)[DqSet<MODEL>::Q])
 {
-    constexpr int Q = DqSet<MODEL>::Q;
-#pragma unroll
-    for (int a = 0; a < Q; ++a) {
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) s = fmaf(P.m[a][i], d[i], s);
-        M[a] = s;
-    }
+    using K = DqConst<MODEL>;
+    constexpr int Q = DqSet<MODEL>::Q, NP = DqTables<MODEL>::NP;
+    float s[NP], q[NP], shell[2] = {0.f, 0.f};
+    dq_for<NP>([&](auto p) {
+        s[p] = d[K::C.pa[p]] + d[K::C.pb[p]];
+        q[p] = d[K::C.pa[p]] - d[K::C.pb[p]];
+        shell[K::C.shell[p]] += s[p];
+    });
+    dq_for<Q>([&](auto a) {
+        float v = 0.f;
+        constexpr float c0 = K::C.mf[a][0];
+        if constexpr (c0 != 0.f) v = c0 * d[0];
+        if constexpr (K::C.scalar[a]) {
+            dq_for<2>([&](auto k) {
+                constexpr float c = K::C.shell_m[a][k];
+                if constexpr (c != 0.f) v = fmaf(c, shell[k], v);
+            });
+        } else {
+            dq_for<NP>([&](auto p) {
+                constexpr float c = K::C.mf[a][K::C.pa[p]];
+                if constexpr (c != 0.f) v = fmaf(c, K::C.odd[a] ? q[p] : s[p], v);
+            });
+        }
+        M[a] = v;
+    });
 }
 
-// NT: streaming (non-temporal) loads and stores, for buffers well beyond the
-// last-level cache.
-template <int MODEL, bool NOISE, bool NT>
-__global__ __launch_bounds__(kDqThreads) void dq_step_kernel(const float *__restrict__ src,
-                                                             float *__restrict__ dst,
-                                                             const DqParams *__restrict__ Pp,
-                                                             uint32_t t, uint32_t key0, uint32_t key1)
+// The collision of one site (Eq. 5) on its deviations, in place: bound by
+// VALU issue where the state sits in the caches (about 400 instructions on
+// D3Q15, of which the noise is 160; with run-time tables it was 700, and
+// their 450 scalars were read by every wave).
+template <int MODEL, bool NOISE>
+__device__ __forceinline__ void dq_collide(float (&d)[DqSet<MODEL>::Q], const DqParams &P,
+                                           uint32_t site, uint32_t t, uint32_t key0, uint32_t key1)
 {
     using S = DqSet<MODEL>;
+    using K = DqConst<MODEL>;
     constexpr int D = S::D, Q = S::Q, NM = Q - D - 1, NS = D * (D + 1) / 2;
-    const DqParams &P = *Pp;
-    int x, y, z;
-    if (!dq_site(P, x, y, z)) return;
-    const uint32_t V = (uint32_t)P.n[0] * (uint32_t)P.n[1] * (uint32_t)P.n[2];
-    const uint32_t site = (uint32_t)x + (uint32_t)P.n[0] * ((uint32_t)y + (uint32_t)P.n[1] * (uint32_t)z);
-    float d[Q], M[Q];
-    dq_pull<MODEL, NT>(src, P, x, y, z, V, d);
-    dq_moments<MODEL>(P, d, M);
+    constexpr int NP = DqTables<MODEL>::NP;
+    float M[Q];
+    dq_moments<MODEL>(d, M);
     const float rho = P.rho0 + M[0];
     const float ir = 1.0f / rho;
     float u[3] = {0.f, 0.f, 0.f};
@@ -161,46 +313,92 @@ __global__ __launch_bounds__(kDqThreads) void dq_step_kernel(const float *__rest
                      zn + 6 * dd);
     }
     float dM[Q];
-#pragma unroll
-    for (int a = D + 1; a < Q; ++a) {
+    dq_for<NM>([&](auto n) {
+        constexpr int a = D + 1 + n;
         float eq = 0.f;
-        if (a < D + 1 + NS) {
-            const int s = a - D - 1;
+        if constexpr (n < NS) {
             float q = 0.f;
-#pragma unroll
-            for (int al = 0; al < D; ++al)
-#pragma unroll
-                for (int be = 0; be < D; ++be) q = fmaf(P.T[s][al][be], u[al] * u[be], q);
+            // T is symmetric: the off-diagonal terms twice
+            dq_for<D>([&](auto al) {
+                dq_for<D>([&](auto be) {
+                    constexpr float c = (al == be ? 1.f : 2.f) * K::C.T[n][al][be];
+                    if constexpr (be >= al && c != 0.f) q = fmaf(c, u[al] * u[be], q);
+                });
+            });
             eq = 4.5f * rho * q;
         }
-        dM[a] = fmaf(P.omega[a], eq - M[a], P.amp[a] * zn[a - D - 1]);
-    }
-    float inc[Q];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        float s = 0.f;
-#pragma unroll
-        for (int a = D + 1; a < Q; ++a) s = fmaf(P.nw[a][i], dM[a], s);
-        inc[i] = s;
-    }
+        dM[a] = fmaf(P.omega[a], eq - M[a], P.amp[a] * zn[n]);
+    });
+    // the change of the rest population and of each pair, even and odd part
+    // (the scalar moments' once per shell)
+    float rest = 0.f, ev[NP], od[NP], sh[2] = {0.f, 0.f};
+    dq_for<NM>([&](auto n) {
+        constexpr int a = D + 1 + n;
+        constexpr float c0 = K::C.nw[a][0];
+        if constexpr (c0 != 0.f) rest = fmaf(c0, dM[a], rest);
+        if constexpr (K::C.scalar[a])
+            dq_for<2>([&](auto k) {
+                constexpr float c = K::C.shell_nw[a][k];
+                if constexpr (c != 0.f) sh[k] = fmaf(c, dM[a], sh[k]);
+            });
+    });
+    dq_for<NP>([&](auto p) {
+        ev[p] = sh[K::C.shell[p]];
+        od[p] = 0.f;
+        dq_for<NM>([&](auto n) {
+            constexpr int a = D + 1 + n;
+            constexpr float c = K::C.nw[a][K::C.pa[p]];
+            if constexpr (!K::C.scalar[a] && c != 0.f) {
+                if constexpr (K::C.odd[a]) od[p] = fmaf(c, dM[a], od[p]);
+                else ev[p] = fmaf(c, dM[a], ev[p]);
+            }
+        });
+    });
     // leakage into mass and momentum through the rounded tables
     float lr = 0.f, lj[3] = {0.f, 0.f, 0.f};
+    dq_for<NP>([&](auto p) {
+        lr += ev[p];
+        dq_for<D>([&](auto al) {
+            constexpr int v = S::v[K::C.pa[p]][al];
+            if constexpr (v != 0) lj[al] += v > 0 ? od[p] : -od[p];
+        });
+    });
+    lr = fmaf(2.f, lr, rest);
+    dq_for<D>([&](auto al) { lj[al] *= 6.f; });  // 3 sum_i v_i inc_i
+    constexpr float w0 = K::C.wf[0];
+    d[0] += fmaf(-w0, lr, rest);
+    dq_for<NP>([&](auto p) {
+        constexpr int i = K::C.pa[p], j = K::C.pb[p];
+        constexpr float w = K::C.wf[i];
+        float c = 0.f;
+        dq_for<D>([&](auto al) {
+            constexpr int v = S::v[i][al];
+            if constexpr (v != 0) c += v > 0 ? lj[al] : -lj[al];
+        });
+        const float e = fmaf(-w, lr, ev[p]), o = fmaf(-w, c, od[p]);
+        d[i] += e + o;
+        d[j] += e - o;
+    });
+}
+
+// NT: streaming (non-temporal) loads and stores, for buffers well beyond the
+// last-level cache.
+template <int MODEL, bool NOISE, bool NT>
+__global__ __launch_bounds__(kDqThreads) void dq_step_kernel(const float *__restrict__ src,
+                                                             float *__restrict__ dst,
+                                                             const DqParams *__restrict__ Pp,
+                                                             uint32_t t, uint32_t key0, uint32_t key1)
+{
+    constexpr int Q = DqSet<MODEL>::Q;
+    const DqParams &P = *Pp;
+    int x, y, z;
+    uint32_t site;
+    if (!dq_site<DqSet<MODEL>::D>(P, site, x, y, z)) return;
+    float d[Q];
+    dq_pull<MODEL, NT>(src, P, x, y, z, P.V, d);
+    dq_collide<MODEL, NOISE>(d, P, site, t, key0, key1);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        lr += inc[i];
-#pragma unroll
-        for (int al = 0; al < D; ++al)
-            if (S::v[i][al]) lj[al] += S::v[i][al] > 0 ? inc[i] : -inc[i];
-    }
-    const uint32_t out = site;
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        float c = lr;
-#pragma unroll
-        for (int al = 0; al < D; ++al)
-            if (S::v[i][al]) c += S::v[i][al] > 0 ? 3.f * lj[al] : -3.f * lj[al];
-        gstore<NT>(dq_at(dst, (uint32_t)i * V + out), d[i] + fmaf(-P.w[i], c, inc[i]));
-    }
+    for (int i = 0; i < Q; ++i) gstore<NT>(dq_at(dst, (uint32_t)i * P.V + site), d[i]);
 }
 
 // Thermal start, first half: adds sqrt(mu rho0 w_i) z_i(x) to the value
@@ -217,14 +415,13 @@ __global__ __launch_bounds__(kDqThreads) void dq_thermal_add_kernel(float *__res
     const DqParams &P = *Pp;
     __shared__ double red[Q][kDqThreads / 64];
     int x, y, z;
-    const bool on = dq_site(P, x, y, z);
+    uint32_t site;
+    const bool on = dq_site<S::D>(P, site, x, y, z);
     double a[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) a[i] = 0.0;
     if (on) {
-        const uint32_t V = (uint32_t)P.n[0] * (uint32_t)P.n[1] * (uint32_t)P.n[2];
-        const uint32_t site =
-            (uint32_t)x + (uint32_t)P.n[0] * ((uint32_t)y + (uint32_t)P.n[1] * (uint32_t)z);
+        const uint32_t V = P.V;
         float zn[18];
 #pragma unroll
         for (int dd = 0; dd < (Q + 5) / 6; ++dd)
@@ -298,11 +495,9 @@ __global__ __launch_bounds__(kDqThreads) void dq_conservation_kernel(const float
     using S = DqSet<MODEL>;
     const DqParams &P = *Pp;
     __shared__ double red[4][kDqThreads / 64];
-    int x, y, z;
     double a[4] = {0.0, 0.0, 0.0, 0.0};
-    if (dq_site(P, x, y, z)) {
-        const uint32_t V = (uint32_t)P.n[0] * (uint32_t)P.n[1] * (uint32_t)P.n[2];
-        const uint32_t s = (uint32_t)x + (uint32_t)P.n[0] * ((uint32_t)y + (uint32_t)P.n[1] * (uint32_t)z);
+    const uint32_t s = blockIdx.x * (uint32_t)kDqThreads + threadIdx.x, V = P.V;
+    if (s < V) {
 #pragma unroll
         for (int i = 0; i < S::Q; ++i) {
             const double f = buf[(uint32_t)i * V + s];
@@ -400,12 +595,12 @@ __global__ __launch_bounds__(kDqThreads) void dq_fields_kernel(const float *__re
     constexpr int D = S::D, Q = S::Q;
     const DqParams &P = *Pp;
     int x, y, z;
-    if (!dq_site(P, x, y, z)) return;
-    const uint32_t V = (uint32_t)P.n[0] * (uint32_t)P.n[1] * (uint32_t)P.n[2];
-    const uint32_t s = (uint32_t)x + (uint32_t)P.n[0] * ((uint32_t)y + (uint32_t)P.n[1] * (uint32_t)z);
+    uint32_t s;
+    if (!dq_site<D>(P, s, x, y, z)) return;
+    const uint32_t V = P.V;
     float d[Q], M[Q];
     dq_pull<MODEL>(src, P, x, y, z, V, d);
-    dq_moments<MODEL>(P, d, M);
+    dq_moments<MODEL>(d, M);
     const float ir = 1.0f / (P.rho0 + M[0]);
     fld[s] = M[0];
 #pragma unroll
@@ -699,66 +894,29 @@ int dq_fail(int code, const std::string &msg) { return set_error(code, msg); }
             return dq_fail(FLB_EHIP, std::string(#call) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-// The velocity polynomials of flb_dq.h, in order.
-double dq_poly(int D, int a, const int v[3])
+template <int MODEL>
+void dq_copy_tables(int &D, int &Q, int v[kDqMaxQ][3], double w[kDqMaxQ],
+                    double m[kDqMaxQ][kDqMaxQ])
 {
-    const double x = v[0], y = v[1], z = v[2], v2 = x * x + y * y + z * z;
-    if (a == 0) return 1.0;
-    if (a <= D) return (double)v[a - 1];
-    if (D == 1) return x * x - 1.0 / 3.0;
-    if (D == 2) {
-        const double p[9] = {0, 0, 0, x * x - y * y, x * y, v2 - 2.0 / 3.0, x * v2, y * v2, v2 * v2};
-        return p[a];
+    using S = DqSet<MODEL>;
+    const DqTables<MODEL> C{};
+    D = S::D;
+    Q = S::Q;
+    for (int i = 0; i < Q; ++i) {
+        for (int a = 0; a < 3; ++a) v[i][a] = S::v[i][a];
+        w[i] = C.w[i];
+        for (int a = 0; a < Q; ++a) m[a][i] = C.m[a][i];
     }
-    const double p[15] = {0, 0, 0, 0, 3 * x * x - v2, y * y - z * z, x * y, y * z, z * x, v2 - 1.0,
-                          x * v2, y * v2, z * v2, x * y * z, v2 * v2};
-    return p[a];
 }
 
 int dq_build(int model, int &D, int &Q, int v[kDqMaxQ][3], double w[kDqMaxQ],
              double m[kDqMaxQ][kDqMaxQ])
 {
     std::memset(v, 0, sizeof(int) * kDqMaxQ * 3);
-    if (model == FLB_DQ_D1Q3) {
-        D = 1;
-        Q = 3;
-        const int vx[3] = {0, 1, -1};
-        const double ww[3] = {2.0 / 3.0, 1.0 / 6.0, 1.0 / 6.0};
-        for (int i = 0; i < 3; ++i) {
-            v[i][0] = vx[i];
-            w[i] = ww[i];
-        }
-    } else if (model == FLB_DQ_D2Q9) {
-        D = 2;
-        Q = 9;
-        for (int i = 0; i < 9; ++i) {
-            v[i][0] = DqSet<FLB_DQ_D2Q9>::v[i][0];
-            v[i][1] = DqSet<FLB_DQ_D2Q9>::v[i][1];
-            w[i] = i == 0 ? 4.0 / 9.0 : i < 5 ? 1.0 / 9.0 : 1.0 / 36.0;
-        }
-    } else if (model == FLB_DQ_D3Q15) {
-        D = 3;
-        Q = 15;
-        for (int i = 0; i < 15; ++i) {
-            for (int a = 0; a < 3; ++a) v[i][a] = DqSet<FLB_DQ_D3Q15>::v[i][a];
-            w[i] = i == 0 ? 2.0 / 9.0 : i < 7 ? 1.0 / 9.0 : 1.0 / 72.0;
-        }
-    } else {
-        return dq_fail(FLB_EINVAL, "unknown model");
-    }
-    for (int a = 0; a < Q; ++a) {
-        double h[kDqMaxQ];
-        for (int i = 0; i < Q; ++i) h[i] = dq_poly(D, a, v[i]);
-        for (int b = 0; b < a; ++b) {
-            double p = 0.0;
-            for (int i = 0; i < Q; ++i) p += w[i] * h[i] * m[b][i];
-            for (int i = 0; i < Q; ++i) h[i] -= p * m[b][i];
-        }
-        double nrm = 0.0;
-        for (int i = 0; i < Q; ++i) nrm += w[i] * h[i] * h[i];
-        nrm = std::sqrt(nrm);
-        for (int i = 0; i < Q; ++i) m[a][i] = h[i] / nrm;
-    }
+    if (model == FLB_DQ_D1Q3) dq_copy_tables<FLB_DQ_D1Q3>(D, Q, v, w, m);
+    else if (model == FLB_DQ_D2Q9) dq_copy_tables<FLB_DQ_D2Q9>(D, Q, v, w, m);
+    else if (model == FLB_DQ_D3Q15) dq_copy_tables<FLB_DQ_D3Q15>(D, Q, v, w, m);
+    else return dq_fail(FLB_EINVAL, "unknown model");
     return FLB_OK;
 }
 
@@ -769,7 +927,7 @@ template <typename F> hipError_t dispatch(int model, F f)
     return f(std::integral_constant<int, FLB_DQ_D3Q15>());
 }
 
-uint32_t grid_sites(const flb_dq *h) { return (uint32_t)h->P.tiles_x * h->n[1] * h->n[2]; }
+uint32_t grid_sites(const flb_dq *h) { return (h->V + kDqThreads - 1) / kDqThreads; }
 
 int enqueue_steps(flb_dq *h, int64_t n)
 {
@@ -1005,14 +1163,14 @@ flb_dq_t *flb_dq_create(int model, const int32_t n[3], const double *tau, double
     DqParams &P = h->P;
     std::memset(&P, 0, sizeof P);
     for (int a = 0; a < 3; ++a) P.n[a] = n[a];
-    P.tiles_x = (n[0] + kDqThreads - 1) / kDqThreads;
+    P.V = h->V;
+    for (int a = 0; a < 2; ++a) dq_divisor(n[a] > 1 ? (uint32_t)n[a] : 2, P.mul[a], P.sh[a]);
     P.stream_id = stream_id;
     P.rho0 = (float)rho0;
     for (int a = 0; a < 3; ++a) P.u0[a] = (float)u0[a];
     const double mu = 3.0 * theta;
     const int first_ghost = 1 + D + D * (D + 1) / 2;
     for (int i = 0; i < Q; ++i) {
-        P.w[i] = (float)h->w[i];
         P.f0[i] = h->w[i] * rho0;
         double vu = 0;
         for (int a = 0; a < 3; ++a) vu += h->v[i][a] * u0[a];
@@ -1021,26 +1179,12 @@ flb_dq_t *flb_dq_create(int model, const int32_t n[3], const double *tau, double
         P.feq[i] = (float)(feq - h->w[i] * rho0);
         P.therm[i] = (float)std::sqrt(mu * rho0 * h->w[i]);
     }
-    for (int a = 0; a < Q; ++a)
-        for (int i = 0; i < Q; ++i) {
-            P.m[a][i] = (float)h->m[a][i];
-            P.nw[a][i] = (float)(h->w[i] * h->m[a][i]);
-        }
     for (int a = D + 1; a < Q; ++a) {
         P.omega[a] = (float)(1.0 / tau[a]);
         double sigma = std::sqrt(mu * rho0 * (2.0 * tau[a] - 1.0)) / tau[a];
         if ((flags & FLB_FLAG_NO_GHOST_NOISE) && a >= first_ghost) sigma = 0.0;
         P.amp[a] = (float)sigma;
         h->noise = h->noise || sigma != 0.0;
-    }
-    for (int s = 0; s < D * (D + 1) / 2; ++s) {
-        const int a = D + 1 + s;
-        for (int al = 0; al < 3; ++al)
-            for (int be = 0; be < 3; ++be) {
-                double t = 0;
-                for (int i = 0; i < Q; ++i) t += h->w[i] * h->m[a][i] * h->v[i][al] * h->v[i][be];
-                P.T[s][al][be] = (float)t;
-            }
     }
     h->nblocks = (int)grid_sites(h);
     if (hipGetDevice(&h->device) != hipSuccess) return bail(FLB_EHIP, "no HIP device");
