@@ -623,8 +623,229 @@ struct DqCorrArgs {
     int nkx, kxp;
     int nf;
     int line_x, line_y, line_z;
+    int roots[3];  // exp(-2 pi i j / n) of each axis with direct transforms
     int D;
 };
+
+// Kind index of field f's auto-correlation: the two u_x u_y* kinds come
+// just before the first non-conserved moment (D >= 2).
+__device__ __forceinline__ int dq_auto_kind(int f, int D)
+{
+    return (D >= 2 && f >= 1 + 2 * D) ? f + 2 : f;
+}
+
+// ---------------------------------------------------------------------
+// Direct line transforms (lengths up to kDqDirect, see there).  A task adds
+// up cosine and sine sums over j < n / 2 of the folded values z_j + z_{n-j}
+// and z_j - z_{n-j}; for even n the even and the odd j apart, as
+// exp(-2 pi i j (n/2 - k) / n) is (-1)^j times the conjugate of that of k.
+// So one pass over a line gives the outputs k, n - k, n/2 - k and n/2 + k,
+// about n operations an output, in two barriers whatever the length, where
+// Bluestein's convolution takes two transforms of two to four times the
+// length.  LDS bounds it: one root and two values per pass and step.
+// ---------------------------------------------------------------------
+constexpr int kDirectThreads = 256;
+
+__device__ __forceinline__ float2 operator+(float2 a, float2 b)
+{
+    return make_float2(a.x + b.x, a.y + b.y);
+}
+__device__ __forceinline__ float2 operator-(float2 a, float2 b)
+{
+    return make_float2(a.x - b.x, a.y - b.y);
+}
+__device__ __forceinline__ float dq_fma(float w, float z, float a) { return fmaf(w, z, a); }
+__device__ __forceinline__ float2 dq_fma(float w, float2 z, float2 a)
+{
+    return make_float2(fmaf(w, z.x, a.x), fmaf(w, z.y, a.y));
+}
+
+// The sums of NF lines of real (float) or complex (float2) values at output
+// k: line f's value j is z(f, j); c[f][p], s[f][p]: over the j of parity p
+// (all in c[f][0], s[f][0] for odd n).
+template <int NF, typename Z, typename F>
+__device__ __forceinline__ void direct_sums(int n, int k, const float2 *roots, F &&z,
+                                            Z (&c)[NF][2], Z (&s)[NF][2])
+{
+    const bool even = (n & 1) == 0;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        c[f][0] = z(f, 0);
+        c[f][1] = s[f][0] = s[f][1] = Z{};
+    }
+    auto term = [&](int j, int m, int p) {
+        const float2 w = roots[m];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const Z a = z(f, j), b = z(f, n - j);
+            c[f][p] = dq_fma(w.x, a + b, c[f][p]);
+            s[f][p] = dq_fma(w.y, a - b, s[f][p]);
+        }
+    };
+    const int last = (n - 1) / 2;  // the j below n / 2
+    int m = 0;
+    auto next = [&]() {
+        m += k;
+        m = m >= n ? m - n : m;
+        return m;
+    };
+    if (even) {
+        int j = 1;
+        for (; j + 1 <= last; j += 2) {
+            const int m1 = next(), m2 = next();
+            term(j, m1, 1);
+            term(j + 1, m2, 0);
+        }
+        if (j <= last) term(j, next(), 1);
+        // j = n / 2: (-1)^k
+        const float w = (k & 1) ? -1.f : 1.f;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const Z v = z(f, n / 2);
+            if ((n / 2) & 1) c[f][1] = dq_fma(w, v, c[f][1]);
+            else c[f][0] = dq_fma(w, v, c[f][0]);
+        }
+    } else {
+        for (int j = 1; j <= last; ++j) term(j, next(), 0);
+    }
+}
+// Tasks per line: k = 0 .. n/4 for even n, 0 .. n/2 for odd.
+__host__ __device__ inline int direct_tasks(int n) { return ((n & 1) ? n / 2 : n / 4) + 1; }
+
+// Along x: blocks of three fields and `rb` rows; item order fields, rows.
+__global__ __launch_bounds__(kDirectThreads) void dq_rows_direct_kernel(DqCorrArgs g, int rb)
+{
+    extern __shared__ float2 lds[];
+    constexpr int G = 3;
+    const int nx = g.n[0], nrows = g.n[1] * g.n[2];
+    const int ngroups = (nrows + rb - 1) / rb;
+    const int f0 = (int)blockIdx.x / ngroups * G, r0 = (int)(blockIdx.x % ngroups) * rb;
+    const int nl = min(rb, nrows - r0), nf = min(G, g.nf - f0);
+    float2 *roots = lds;
+    float *val = reinterpret_cast<float *>(lds + nx);  // [G][rb][nx]
+    const size_t V = (size_t)nx * nrows;
+    for (int j = (int)threadIdx.x; j < nx; j += kDirectThreads) roots[j] = g.tables[g.roots[0] + j];
+    const float *in = g.fld + (size_t)f0 * V + (size_t)r0 * nx;
+    for (int e = (int)threadIdx.x; e < nl * nx; e += kDirectThreads)
+#pragma unroll
+        for (int f = 0; f < G; ++f)
+            // (a field past the last is that one again, and not stored)
+            val[f * rb * nx + e] = in[(size_t)min(f, nf - 1) * V + e];
+    __syncthreads();
+    const int nt = direct_tasks(nx);
+    const size_t fstride = (size_t)nrows * g.kxp;
+    for (int task = (int)threadIdx.x; task < nl * nt; task += kDirectThreads) {
+        const int l = task / nt, k = task - l * nt;
+        const float *row = val + l * nx;
+        float c[G][2], s[G][2];
+        direct_sums<G>(nx, k, roots, [&](int f, int j) { return row[f * rb * nx + j]; }, c, s);
+        float2 *o = g.spec + (size_t)f0 * fstride + (size_t)(r0 + l) * g.kxp;
+#pragma unroll
+        for (int f = 0; f < G; ++f) {
+            if (f >= nf) break;
+            o[f * fstride + k] = make_float2(c[f][0] + c[f][1], s[f][0] + s[f][1]);
+            if ((nx & 1) == 0 && 4 * k != nx)
+                o[f * fstride + nx / 2 - k] = make_float2(c[f][0] - c[f][1], s[f][1] - s[f][0]);
+        }
+    }
+}
+
+// The outputs of a complex line from its sums: emit(ky, values of the NF
+// lines), each ky once.
+template <int NF, typename F>
+__device__ __forceinline__ void direct_outputs(int n, int k, const float2 (&c)[NF][2],
+                                               const float2 (&s)[NF][2], F &&emit)
+{
+    // cosine sums C and sine sums S (of -sin): output C + i S at k, C - i S
+    // at n - k
+    auto both = [&](int ky, float sg) {
+        float2 C[NF], S[NF], X[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            C[f] = dq_fma(sg, c[f][1], c[f][0]);
+            S[f] = dq_fma(sg, s[f][0], s[f][1]);  // sg = 1: the sum; -1: odd less even
+            X[f] = make_float2(C[f].x - S[f].y, C[f].y + S[f].x);
+        }
+        emit(ky, X);
+        if (ky == 0 || 2 * ky == n) return;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) X[f] = make_float2(C[f].x + S[f].y, C[f].y - S[f].x);
+        emit(n - ky, X);
+    };
+    both(k, 1.f);
+    if ((n & 1) == 0 && 4 * k != n) both(n / 2 - k, -1.f);
+}
+
+template <int NF, bool ADD>
+__device__ __forceinline__ void dq_lines_direct(const DqCorrArgs &g, int axis, int cb, int f0, int o,
+                                                int cgi, float2 *lds)
+{
+    const int D = g.D, ny = g.n[1], nz = g.n[2];
+    const int n = axis == 1 ? ny : nz;
+    const size_t stride = axis == 1 ? (size_t)g.kxp : (size_t)ny * g.kxp;
+    const size_t ostride = axis == 1 ? (size_t)ny * g.kxp : (size_t)g.kxp;
+    const size_t fstride = (size_t)ny * nz * g.kxp;
+    const int c0 = cgi * cb, ncol = min(cb, g.nkx - c0);
+    float2 *roots = lds, *val = lds + n;  // [NF][n][cb]
+    const size_t base = (size_t)o * ostride + c0;
+    for (int j = (int)threadIdx.x; j < n; j += kDirectThreads) roots[j] = g.tables[g.roots[axis] + j];
+    for (int e = (int)threadIdx.x; e < n * cb; e += kDirectThreads) {
+        const int j = e / cb, c = e - j * cb;
+        if (c >= ncol) continue;
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            val[f * n * cb + e] = g.spec[(size_t)(f0 + f) * fstride + base + (size_t)j * stride + c];
+    }
+    __syncthreads();
+    const int nt = direct_tasks(n);
+    for (int task = (int)threadIdx.x; task < nt * cb; task += kDirectThreads) {
+        const int k = task / cb, c = task - k * cb;
+        if (c >= ncol) continue;
+        const float2 *col = val + c;
+        float2 cs[NF][2], sn[NF][2];
+        direct_sums<NF>(n, k, roots, [&](int f, int j) { return col[(f * n + j) * cb]; }, cs, sn);
+        direct_outputs<NF>(n, k, cs, sn, [&](int ky, const float2(&X)[NF]) {
+            const size_t off = base + (size_t)ky * stride + c;
+            if constexpr (!ADD) {
+                g.spec[(size_t)f0 * fstride + off] = X[0];
+            } else {
+                if (ky == 0 && o == 0 && c0 + c == 0) return;  // k = 0
+                const double xr = X[0].x, xi = X[0].y;
+                g.acc[(size_t)dq_auto_kind(f0, D) * fstride + off] += xr * xr + xi * xi;
+                if constexpr (NF == 2) {
+                    const double yr = X[1].x, yi = X[1].y;
+                    g.acc[(size_t)dq_auto_kind(f0 + 1, D) * fstride + off] += yr * yr + yi * yi;
+                    g.acc[(size_t)(1 + 2 * D) * fstride + off] += xr * yr + xi * yi;
+                    g.acc[(size_t)(2 + 2 * D) * fstride + off] += xi * yr - xr * yi;
+                }
+            }
+        });
+    }
+}
+
+// Along y (axis 1) or z (axis 2).  ADD false: in place, one block per (field,
+// position along the other axis, group of cb adjacent kx).  ADD true: the
+// last axis, the products added to the sums instead: the first blocks take
+// u_x and u_y together, for their cross kinds (cb / 2 columns each, so that
+// every block has the same LDS), the others a field each.
+template <bool ADD>
+__global__ __launch_bounds__(kDirectThreads) void dq_lines_direct_kernel(DqCorrArgs g, int axis,
+                                                                         int cb)
+{
+    extern __shared__ float2 lds[];
+    const int nouter = axis == 1 ? g.n[2] : g.n[1], ncg = (g.nkx + cb - 1) / cb;
+    int b = (int)blockIdx.x;
+    if constexpr (ADD) {
+        const int half = cb / 2, ncp = (g.nkx + half - 1) / half;
+        if (b < nouter * ncp) {
+            dq_lines_direct<2, true>(g, axis, half, 1 + g.D, b / ncp, b % ncp, lds);
+            return;
+        }
+        b -= nouter * ncp;
+    }
+    const int cgi = b % ncg, o = b / ncg % nouter, grp = b / ncg / nouter;
+    dq_lines_direct<1, ADD>(g, axis, cb, ADD && grp >= 1 + g.D ? grp + 2 : grp, o, cgi, lds);
+}
 
 // The transform kernels below are instantiated for power-of-two lines
 // (BLUE false) and for Bluestein lines (BLUE true); the host picks the one
@@ -738,13 +959,6 @@ __global__ __launch_bounds__(kFftThreads) void dq_lines_kernel(DqCorrArgs g, int
         const int j = idx / cb, c = idx - j * cb;
         if (c < ncol) col[(size_t)j * stride + c] = lds[idx];
     }
-}
-
-// Kind index of field f's auto-correlation: the two u_x u_y* kinds come
-// just before the first non-conserved moment (D >= 2).
-__device__ __forceinline__ int dq_auto_kind(int f, int D)
-{
-    return (D >= 2 && f >= 1 + 2 * D) ? f + 2 : f;
 }
 
 // Last transform axis with the accumulation fused in: one block per (field,
@@ -876,6 +1090,8 @@ struct flb_dq {
     double *d_acc = nullptr;
     int line[3] = {0, 0, 0};
     bool blue[3] = {false, false, false};  // the axis's line plan is a Bluestein one
+    bool direct[3] = {false, false, false};  // the axis is transformed by direct sums
+    int roots[3] = {0, 0, 0};
     int rows_lds = 0, lines_lds = 0, rb = 1, cb = 1;
     // fused last pass: columns per block for single fields and for the u
     // pair (0: a separate accumulation)
@@ -959,6 +1175,22 @@ int enqueue_steps(flb_dq *h, int64_t n)
     return FLB_OK;
 }
 
+// Lengths up to which direct sums beat the LDS transforms.  A sample, direct
+// against Bluestein: 60^3 63 and 118 us, 96^3 254 and 403, 160 x 96 x 60 243
+// and 425, 192^3 2317 and 2809, 300^2 x 20 644 and 1081; power-of-two sides:
+// 32^3 33 and 39, 64^3 97 and 83.
+constexpr int kDqDirect = 320, kDqDirectP2 = 32;
+bool dq_direct(int n, bool bluestein) { return n <= (bluestein ? kDqDirect : kDqDirectP2); }
+
+// Columns per block of the direct line kernels: whole 128-byte lines of the
+// spectra, as many as give the block's threads a task each.
+int direct_cols(int n)
+{
+    int cb = 16;
+    while (cb < 64 && 2 * cb * direct_tasks(n) <= kDirectThreads) cb *= 2;
+    return cb;
+}
+
 int setup_corr(flb_dq *h)
 {
     if (h->corr_ready) return FLB_OK;
@@ -971,6 +1203,8 @@ int setup_corr(flb_dq *h)
     for (int a = 0; a < 3; ++a) {
         h->line[a] = lt.plan_for(h->n[a] > 1 ? h->n[a] : 2);
         h->blue[a] = lt.plans[h->line[a]].bluestein != 0;
+        h->direct[a] = a < h->D && dq_direct(h->n[a], h->blue[a]);
+        if (h->direct[a]) h->roots[a] = lt.roots_for(h->n[a]);
     }
     const int mx = lt.plans[h->line[0]].m;
     h->rb = std::max(1, std::min(h->n[1] * h->n[2], 4096 / mx));
@@ -1028,6 +1262,7 @@ DqCorrArgs corr_args(const flb_dq *h)
     g.line_x = h->line[0];
     g.line_y = h->line[1];
     g.line_z = h->line[2];
+    for (int a = 0; a < 3; ++a) g.roots[a] = h->roots[a];
     g.D = h->D;
     return g;
 }
@@ -1045,7 +1280,12 @@ int enqueue_sample(flb_dq *h)
     const int nrows = h->n[1] * h->n[2];
     const int ngroups = (nrows + h->rb - 1) / h->rb;
     const int npairs = (h->nf + 1) / 2;
-    if (h->blue[0])
+    if (h->direct[0]) {
+        const int nx = h->n[0], rb = std::max(1, std::min(nrows, kDirectThreads / direct_tasks(nx)));
+        const int lds = nx * (int)sizeof(float2) + 3 * rb * nx * (int)sizeof(float);
+        hipLaunchKernelGGL(dq_rows_direct_kernel, dim3((h->nf + 2) / 3 * ((nrows + rb - 1) / rb)),
+                           dim3(kDirectThreads), lds, h->stream, g, rb);
+    } else if (h->blue[0])
         hipLaunchKernelGGL(dq_rows_kernel<true>, dim3(npairs * ngroups), dim3(kFftThreads),
                            h->rows_lds, h->stream, g, h->rb);
     else
@@ -1057,7 +1297,14 @@ int enqueue_sample(flb_dq *h)
     for (int axis = 1; axis < 3; ++axis) {
         if (h->n[axis] < 2) continue;
         const int nouter = axis == 1 ? h->n[2] : h->n[1];
-        if (axis == last && h->last_cb) {
+        if (h->direct[axis]) {
+            const int n = h->n[axis], cb = direct_cols(n), ncgd = (h->P.nkx + cb - 1) / cb;
+            auto kernel = axis == last ? dq_lines_direct_kernel<true> : dq_lines_direct_kernel<false>;
+            const int lds = n * (1 + cb) * (int)sizeof(float2);
+            const int ncp = (h->P.nkx + cb / 2 - 1) / (cb / 2);  // of the u pair
+            const int nb = axis == last ? nouter * ((h->nf - 2) * ncgd + ncp) : h->nf * nouter * ncgd;
+            hipLaunchKernelGGL(kernel, dim3(nb), dim3(kDirectThreads), lds, h->stream, g, axis, cb);
+        } else if (axis == last && h->last_cb) {
             const int ncgl = (h->P.nkx + h->last_cb - 1) / h->last_cb;
             const int ncgp = (h->P.nkx + h->last_cb_pair - 1) / h->last_cb_pair;
             auto lastk = h->blue[axis] ? dq_last_kernel<true> : dq_last_kernel<false>;
@@ -1073,7 +1320,7 @@ int enqueue_sample(flb_dq *h)
         }
         DQ_HIP(hipGetLastError());
     }
-    if (!h->last_cb) {
+    if (!h->last_cb && !(h->D >= 2 && h->direct[last])) {
         const int64_t nk = (int64_t)nrows * h->P.nkx;
         hipLaunchKernelGGL(dq_accum_kernel, dim3((unsigned)((nk + kDqThreads - 1) / kDqThreads)),
                            dim3(kDqThreads), 0, h->stream, g);

@@ -216,3 +216,31 @@ def test_large_lattice_with_streaming_accesses(flb, oracle_lib):
     g.step(2)
     o.step(2)
     assert np.abs(g.get_populations() - o.f).max() < 2e-6
+
+
+@pytest.mark.parametrize("model,sides", [
+    ("D3Q15", (2, 2, 2)), ("D3Q15", (3, 4, 5)), ("D3Q15", (6, 9, 12)), ("D3Q15", (33, 2, 20)),
+    ("D3Q15", (20, 64, 3)), ("D3Q15", (320, 3, 2)), ("D3Q15", (321, 2, 6)), ("D3Q15", (5, 319, 2)),
+    ("D3Q15", (4, 2, 322)), ("D3Q15", (64, 32, 30)), ("D2Q9", (100, 31)), ("D2Q9", (32, 64)),
+    ("D2Q9", (64, 18)), ("D1Q3", (7,)), ("D1Q3", (320,)), ("D1Q3", (322,))])
+def test_sums_at_the_limits_of_the_line_transforms(flb, oracle_lib, model, sides):
+    """Direct sums (all residues of n mod 4, the longest) and the LDS
+    transforms along every axis, two samples against the oracle."""
+    note("line transforms", model, sides)
+    D, _, w, _ = oracle_lib.dq_tables(model)
+    Q = len(w)
+    kw = dict(u0=[0.03, -0.02, 0.01][:D], seed=5, stream_id=1)
+    g = flb.DqLattice(model, sides, _tau(D, Q), 1e-3, **kw)
+    o = oracle_lib.DqLattice(model, sides, _tau(D, Q), 1e-3, **kw)
+    g.thermalize()
+    o.thermalize()
+    for _ in range(2):
+        g.step(2)
+        o.step(2)
+        g.accumulate()
+        o.sample()
+    acc, n = g.read_correlators()
+    assert n == 2 and acc.shape == o.acc.shape
+    scale = np.abs(o.acc).reshape(len(acc), -1).max(axis=1)
+    for q in range(len(acc)):
+        assert np.abs(acc[q] - o.acc[q]).max() <= 2e-4 * max(scale[q], scale.max() * 1e-3), q
