@@ -11,14 +11,12 @@
 //
 // Why direct sums: the lines are a few dozen points of any length, where
 // Bluestein's convolution works on lines of up to four times the length
-// (20 points: 64) and every pass is a barrier.  The sums fold the j-th and
-// (n - j)-th value of a line first: the cosine terms need their sum, the
-// sine terms their difference, so a real row costs n / 2 complex multiply-
-// adds per output, and a column n / 2 for outputs k and n - k together.
+// (20 points: 64) and every pass is a barrier (flb_direct.h).
 //
 // What bounds it: VALU issue and LDS of the compute units that hold a
 // lattice; a step waits for nothing but its two barriers.
 #include "flb_collide.h"
+#include "flb_direct.h"
 #include "flb_small.h"
 #include "flb_sums.h"
 
@@ -41,82 +39,44 @@ struct SmallArgs {
 
 // Half spectra of NF real fields [f][ny][nx] along their rows:
 // out[(f ny + y) nkx + k], k = 0 .. nx/2; roots[m] = exp(-2 pi i m / nx).
-// A task is one output of up to three fields, which share the roots.
+// A task is a pass over one row of two fields, which share the roots.
 template <int NF>
 __device__ __forceinline__ void small_rows(const float *fld, int V, float2 *out,
                                            const float2 *roots, int nx, int ny, int nkx)
 {
-    constexpr int G = 3, NG = (NF + G - 1) / G;
-    const int nt = (int)blockDim.x, np = ny * nkx;
-    for (int task = (int)threadIdx.x; task < NG * np; task += nt) {
-        const int y = task / nkx, k = task - y * nkx;  // y runs through the groups' rows
-        const int grp = (y >= ny) + (NG > 2 && y >= 2 * ny);
-        const int yy = y - grp * ny, f0 = grp * G;
-        // (a group past the last field reads it again and does not store)
-        const float *row[G];
-        float re[G], im[G];
+    constexpr int G = 2, NG = (NF + G - 1) / G;
+    const int per = direct_tasks(nx), nt = per * ny;
+    for (int task = (int)threadIdx.x; task < NG * nt; task += (int)blockDim.x) {
+        const int grp = task / nt, r = task - grp * nt, y = r / per, k = r - y * per;
+        const int f0 = grp * G, f1 = min(f0 + 1, NF - 1);  // (the last field again, not stored)
+        const float *row[G] = {fld + f0 * V + y * nx, fld + f1 * V + y * nx};
+        float c[G][2], s[G][2];
+        direct_sums<G>(nx, k, roots, [&](int f, int j) { return row[f][j]; }, c, s);
 #pragma unroll
         for (int f = 0; f < G; ++f) {
-            row[f] = fld + min(f0 + f, NF - 1) * V + yy * nx;
-            re[f] = row[f][0];
-            im[f] = 0.f;
+            if (f0 + f >= NF) break;
+            float2 *o = out + ((f0 + f) * ny + y) * nkx;
+            o[k] = make_float2(c[f][0] + c[f][1], s[f][0] + s[f][1]);
+            if ((nx & 1) == 0 && 4 * k != nx)
+                o[nx / 2 - k] = make_float2(c[f][0] - c[f][1], s[f][1] - s[f][0]);
         }
-        int m = 0;
-#pragma unroll 2
-        for (int j = 1; 2 * j < nx; ++j) {
-            m += k;
-            m = m >= nx ? m - nx : m;
-            const float2 w = roots[m];
-#pragma unroll
-            for (int f = 0; f < G; ++f) {
-                const float a = row[f][j], b = row[f][nx - j];
-                re[f] = fmaf(w.x, a + b, re[f]);
-                im[f] = fmaf(w.y, a - b, im[f]);
-            }
-        }
-        if ((nx & 1) == 0) {
-            const float sign = (k & 1) ? -1.f : 1.f;
-#pragma unroll
-            for (int f = 0; f < G; ++f) re[f] = fmaf(sign, row[f][nx / 2], re[f]);
-        }
-#pragma unroll
-        for (int f = 0; f < G; ++f)
-            if (f0 + f < NF) out[((f0 + f) * ny + yy) * nkx + k] = make_float2(re[f], im[f]);
     }
 }
 
 // Column transforms of NF row spectra, [f][ny][nkx] to the same order: a
-// task is one field's column kx and the outputs ky and ny - ky.
+// task is a pass over one column of one field.
 template <int NF>
 __device__ __forceinline__ void small_cols(const float2 *in, float2 *out, const float2 *roots,
                                            int ny, int nkx)
 {
-    const int nt = (int)blockDim.x, half = ny / 2, np = (half + 1) * nkx;
-    for (int task = (int)threadIdx.x; task < NF * np; task += nt) {
+    const int np = direct_tasks(ny) * nkx;
+    for (int task = (int)threadIdx.x; task < NF * np; task += (int)blockDim.x) {
         const int f = task / np, r = task - f * np, ky = r / nkx, kx = r - ky * nkx;
         const float2 *col = in + f * ny * nkx + kx;
         float2 *o = out + f * ny * nkx + kx;
-        // sums over cosines (a) and sines (b)
-        float ar = col[0].x, ai = col[0].y, br = 0.f, bi = 0.f;
-        int m = 0;
-#pragma unroll 2
-        for (int j = 1; 2 * j < ny; ++j) {
-            m += ky;
-            m = m >= ny ? m - ny : m;
-            const float2 w = roots[m], p = col[j * nkx], q = col[(ny - j) * nkx];
-            ar = fmaf(w.x, p.x + q.x, ar);
-            ai = fmaf(w.x, p.y + q.y, ai);
-            br = fmaf(w.y, p.x - q.x, br);
-            bi = fmaf(w.y, p.y - q.y, bi);
-        }
-        if ((ny & 1) == 0) {
-            const float sign = (ky & 1) ? -1.f : 1.f;
-            const float2 z = col[half * nkx];
-            ar = fmaf(sign, z.x, ar);
-            ai = fmaf(sign, z.y, ai);
-        }
-        o[ky * nkx] = make_float2(ar - bi, ai + br);
-        if (ky) o[(ny - ky) * nkx] = make_float2(ar + bi, ai - br);
+        float2 c[1][2], s[1][2];
+        direct_sums<1>(ny, ky, roots, [&](int, int j) { return col[j * nkx]; }, c, s);
+        direct_outputs<1>(ny, ky, c, s, [&](int k, const float2(&X)[1]) { o[k * nkx] = X[0]; });
     }
 }
 
