@@ -1458,29 +1458,32 @@ __global__ __launch_bounds__(kThreads) void corr_export_kernel(const double *__r
                                                                const LatticeParams *params,
                                                                int lattice, uint32_t first,
                                                                uint32_t n, SumScale sc,
-                                                               double *__restrict__ out)
+                                                               double *__restrict__ out,
+                                                               StageDone done)
 {
     const LatticeParams &P = params[lattice];
     const uint32_t j = blockIdx.x * (uint32_t)kThreads + threadIdx.x;
-    if (j >= n) return;
-    const uint32_t nkx = (uint32_t)P.nkx, ny = (uint32_t)P.ny;
-    const uint32_t row = (first + j) / nkx, kx = first + j - row * nkx;
-    const uint32_t q = row / ny, y = row - q * ny;
-    double v = acc[P.acc_base + (int64_t)q * ny * P.kxp + spec_offset((int)y, (int)kx, (int)ny)];
-    if (SCALED) v = v / sc.nsamples * sc.norm[q];
-    out[j] = v;
+    if (j < n) {
+        const uint32_t nkx = (uint32_t)P.nkx, ny = (uint32_t)P.ny;
+        const uint32_t row = (first + j) / nkx, kx = first + j - row * nkx;
+        const uint32_t q = row / ny, y = row - q * ny;
+        double v = acc[P.acc_base + (int64_t)q * ny * P.kxp + spec_offset((int)y, (int)kx, (int)ny)];
+        if (SCALED) v = v / sc.nsamples * sc.norm[q];
+        out[j] = v;
+    }
+    stage_signal(done);
 }
 
 hipError_t launch_corr_export(const DeviceView &v, int lattice, size_t first, size_t n,
-                              const SumScale *scale, double *out, hipStream_t s)
+                              const SumScale *scale, double *out, StageDone done, hipStream_t s)
 {
     const dim3 grid((unsigned)((n + kThreads - 1) / kThreads)), block(kThreads);
     if (scale)
         hipLaunchKernelGGL(corr_export_kernel<true>, grid, block, 0, s, v.acc, v.params, lattice,
-                           (uint32_t)first, (uint32_t)n, *scale, out);
+                           (uint32_t)first, (uint32_t)n, *scale, out, done);
     else
         hipLaunchKernelGGL(corr_export_kernel<false>, grid, block, 0, s, v.acc, v.params, lattice,
-                           (uint32_t)first, (uint32_t)n, SumScale(), out);
+                           (uint32_t)first, (uint32_t)n, SumScale(), out, done);
     return hipGetLastError();
 }
 

@@ -131,5 +131,5 @@ struct SumScale {
     double nsamples;
 };
 hipError_t launch_corr_export(const DeviceView &v, int lattice, size_t first, size_t n,
-                              const SumScale *scale, double *out, hipStream_t s);
+                              const SumScale *scale, double *out, StageDone done, hipStream_t s);
 }  // namespace flbdev

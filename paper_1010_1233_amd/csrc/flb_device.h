@@ -105,6 +105,17 @@ template <> struct Codec<kF16> {
     }
 };
 
+// Called by every thread of a block after its last store.
+__device__ __forceinline__ void stage_signal(const StageDone &done)
+{
+    if (!done.flag) return;
+    __threadfence_system();  // this thread's values are in host memory
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&done.flag[blockIdx.x], done.seq, __ATOMIC_RELEASE,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Plain or streaming (non-temporal) global stores and loads.
 template <bool NT, typename T> __device__ __forceinline__ void gstore(T *p, T v)
 {

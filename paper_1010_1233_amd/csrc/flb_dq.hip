@@ -541,21 +541,24 @@ template <int MODEL, bool GET>
 __global__ __launch_bounds__(kDqThreads) void dq_copy_kernel(float *__restrict__ buf,
                                                              const DqParams *__restrict__ Pp,
                                                              uint32_t first, uint32_t n,
-                                                             double *__restrict__ host)
+                                                             double *__restrict__ host,
+                                                             StageDone done)
 {
     using S = DqSet<MODEL>;
     const DqParams &P = *Pp;
     const uint32_t j = blockIdx.x * (uint32_t)kDqThreads + threadIdx.x;
-    if (j >= n) return;
-    const uint32_t nx = (uint32_t)P.n[0], ny = (uint32_t)P.n[1], nz = (uint32_t)P.n[2];
-    const uint32_t row = (first + j) / nx, x = first + j - row * nx;
-    const uint32_t plane = row / ny, y = row - plane * ny;
-    const uint32_t i = plane / nz, z = plane - i * nz;
-    const int xs = wrapi((int)x - S::v[i][0], (int)nx), ys = wrapi((int)y - S::v[i][1], (int)ny);
-    const int zs = wrapi((int)z - S::v[i][2], (int)nz);
-    float *p = dq_at(buf, (uint32_t)xs + nx * ((uint32_t)ys + ny * ((uint32_t)zs + nz * i)));
-    if (GET) host[j] = (double)*p + P.f0[i];
-    else *p = (float)(host[j] - P.f0[i]);
+    if (j < n) {
+        const uint32_t nx = (uint32_t)P.n[0], ny = (uint32_t)P.n[1], nz = (uint32_t)P.n[2];
+        const uint32_t row = (first + j) / nx, x = first + j - row * nx;
+        const uint32_t plane = row / ny, y = row - plane * ny;
+        const uint32_t i = plane / nz, z = plane - i * nz;
+        const int xs = wrapi((int)x - S::v[i][0], (int)nx), ys = wrapi((int)y - S::v[i][1], (int)ny);
+        const int zs = wrapi((int)z - S::v[i][2], (int)nz);
+        float *p = dq_at(buf, (uint32_t)xs + nx * ((uint32_t)ys + ny * ((uint32_t)zs + nz * i)));
+        if (GET) host[j] = (double)*p + P.f0[i];
+        else *p = (float)(host[j] - P.f0[i]);
+    }
+    if (GET) stage_signal(done);
 }
 
 // Sums first .. first + n - 1 in the order [kind][nz][ny][nx/2+1], without
@@ -569,15 +572,18 @@ __global__ __launch_bounds__(kDqThreads) void dq_export_kernel(const double *__r
                                                                uint32_t nrows, uint32_t nkx,
                                                                uint32_t kxp, uint64_t first,
                                                                uint32_t n, DqScale sc,
-                                                               double *__restrict__ out)
+                                                               double *__restrict__ out,
+                                                               StageDone done)
 {
     const uint32_t j = blockIdx.x * (uint32_t)kDqThreads + threadIdx.x;
-    if (j >= n) return;
-    const uint64_t row = (first + j) / nkx;
-    const uint32_t kx = (uint32_t)(first + j - row * nkx);
-    double v = acc[row * kxp + kx];
-    if (SCALED) v = v / sc.nsamples * sc.norm[row / nrows];
-    out[j] = v;
+    if (j < n) {
+        const uint64_t row = (first + j) / nkx;
+        const uint32_t kx = (uint32_t)(first + j - row * nkx);
+        double v = acc[row * kxp + kx];
+        if (SCALED) v = v / sc.nsamples * sc.norm[row / nrows];
+        out[j] = v;
+    }
+    stage_signal(done);
 }
 
 // ---------------------------------------------------------------------
@@ -1443,18 +1449,18 @@ static int dq_read_sums(flb_dq *h, double *out, size_t n_doubles, const DqScale 
     const size_t need = (size_t)h->nkinds * nrows * h->P.nkx;
     if (n_doubles < need) return dq_fail(FLB_ESIZE, "output buffer too small for the correlators");
     DQ_HIP(stage_out(h->device, h->stream, out, need,
-                     [&](double *slot, size_t first, size_t n, hipStream_t s) {
+                     [&](double *slot, size_t first, size_t n, StageDone done, hipStream_t s) {
                          const dim3 grid((unsigned)((n + kDqThreads - 1) / kDqThreads));
                          if (scale)
                              hipLaunchKernelGGL(dq_export_kernel<true>, grid, dim3(kDqThreads), 0,
                                                 s, h->d_acc, nrows, (uint32_t)h->P.nkx,
                                                 (uint32_t)h->P.kxp, (uint64_t)first, (uint32_t)n,
-                                                *scale, slot);
+                                                *scale, slot, done);
                          else
                              hipLaunchKernelGGL(dq_export_kernel<false>, grid, dim3(kDqThreads),
                                                 0, s, h->d_acc, nrows, (uint32_t)h->P.nkx,
                                                 (uint32_t)h->P.kxp, (uint64_t)first, (uint32_t)n,
-                                                DqScale(), slot);
+                                                DqScale(), slot, done);
                          return hipGetLastError();
                      }));
     return FLB_OK;
@@ -1517,16 +1523,16 @@ int flb_dq_reset(flb_dq_t *h)
 static int dq_copy(flb_dq *h, double *host, size_t total, bool get)
 {
     float *buf = h->pops[h->cur];
-    auto kernel = [&](double *slot, size_t first, size_t n, hipStream_t s) {
+    auto kernel = [&](double *slot, size_t first, size_t n, StageDone done, hipStream_t s) {
         const dim3 grid((unsigned)((n + kDqThreads - 1) / kDqThreads)), block(kDqThreads);
         return dispatch(h->model, [&](auto mc) {
             constexpr int MODEL = decltype(mc)::value;
             if (get)
                 hipLaunchKernelGGL((dq_copy_kernel<MODEL, true>), grid, block, 0, s, buf, h->d_P,
-                                   (uint32_t)first, (uint32_t)n, slot);
+                                   (uint32_t)first, (uint32_t)n, slot, done);
             else
                 hipLaunchKernelGGL((dq_copy_kernel<MODEL, false>), grid, block, 0, s, buf, h->d_P,
-                                   (uint32_t)first, (uint32_t)n, slot);
+                                   (uint32_t)first, (uint32_t)n, slot, done);
             return hipGetLastError();
         });
     };

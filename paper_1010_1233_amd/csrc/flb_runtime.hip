@@ -1648,8 +1648,8 @@ static int read_sums(flb_t *h, int lattice, double *out, size_t n_doubles, const
     if ((rc = settle_due(h)) || (rc = flush_pending(h))) return rc;
     const DeviceView v = h->view();
     FLB_HIP(stage_out(h->device, h->stream, out, need,
-                      [&](double *slot, size_t first, size_t n, hipStream_t s) {
-                          return launch_corr_export(v, lattice, first, n, scale, slot, s);
+                      [&](double *slot, size_t first, size_t n, StageDone done, hipStream_t s) {
+                          return launch_corr_export(v, lattice, first, n, scale, slot, done, s);
                       }));
     return FLB_OK;
 }
@@ -1726,8 +1726,8 @@ int flb_get_populations(flb_t *h, int lattice, double *out, size_t n)
     if (n < need) return fail(FLB_ESIZE, "output buffer smaller than 9*nx*ny");
     const DeviceView v = h->view();
     FLB_HIP(stage_out(h->device, h->stream, out, need,
-                      [&](double *slot, size_t first, size_t m, hipStream_t s) {
-                          return launch_get(v, lattice, (int64_t)first, (int64_t)m, slot, s);
+                      [&](double *slot, size_t first, size_t m, StageDone done, hipStream_t s) {
+                          return launch_get(v, lattice, (int64_t)first, (int64_t)m, slot, done, s);
                       }));
     return FLB_OK;
 }
@@ -1747,7 +1747,7 @@ int flb_get_populations_noalloc(flb_t *h, int lattice, double *out, size_t n)
     if (rc) return rc;
     // every value the copy reads is written by the kernel first: nothing
     // needs clearing
-    FLB_HIP(launch_get(h->view(), lattice, 0, (int64_t)need, d, h->stream));
+    FLB_HIP(launch_get(h->view(), lattice, 0, (int64_t)need, d, StageDone{nullptr, 0}, h->stream));
     FLB_HIP(hipMemcpyAsync(out, d, need * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     FLB_HIP(hipStreamSynchronize(h->stream));
     return FLB_OK;
@@ -1764,7 +1764,7 @@ int flb_set_populations(flb_t *h, int lattice, const double *in, size_t n)
     if (rc) return rc;
     const DeviceView v = h->view();
     FLB_HIP(stage_in(h->device, h->stream, in, need,
-                     [&](double *slot, size_t first, size_t m, hipStream_t s) {
+                     [&](double *slot, size_t first, size_t m, StageDone, hipStream_t s) {
                          return launch_set(v, lattice, (int64_t)first, (int64_t)m, slot, s);
                      }));
     return FLB_OK;

@@ -28,9 +28,16 @@ constexpr size_t kStageSlotDoubles = (size_t)1 << 18;  // 2 MiB a slot, two per 
 void stage_retain();
 void stage_release();
 
+// (StageDone: flb_internal.h)
+constexpr int kStageFlags = 64;  // blocks at most
+// Blocks of 256 values each that a kernel gets for n values.
+constexpr size_t kStageBlock = 256;
+
 // Enqueues the kernel for `n` doubles of the transfer, from its double
-// `first` on, on stream s; `slot` is their place in the pinned memory.
-using StageKernel = std::function<hipError_t(double *slot, size_t first, size_t n, hipStream_t s)>;
+// `first` on, on stream s, in ceil(n / kStageBlock) blocks; `slot` is their
+// place in the pinned memory.
+using StageKernel =
+    std::function<hipError_t(double *slot, size_t first, size_t n, StageDone done, hipStream_t s)>;
 
 // Fills out[0 .. n-1] through kernels on stream s (behind the work already
 // there); returns when out is complete.

@@ -4,6 +4,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <condition_variable>
 #include <mutex>
 #include <system_error>
@@ -48,14 +49,14 @@ hipError_t take(Job &j, double *slot, hipEvent_t ev, size_t &chunk)
         ++j.next;
         range(chunk);
         if (j.to_host) {
-            hipError_t e = (*j.kernel)(slot, first, m, j.stream);
+            hipError_t e = (*j.kernel)(slot, first, m, StageDone{nullptr, 0}, j.stream);
             if (e == hipSuccess) e = hipEventRecord(ev, j.stream);
             return e;
         }
     }
     memcpy(slot, j.host + first, m * sizeof(double));
     std::lock_guard<std::mutex> lock(j.m);
-    hipError_t e = (*j.kernel)(slot, first, m, j.stream);
+    hipError_t e = (*j.kernel)(slot, first, m, StageDone{nullptr, 0}, j.stream);
     if (e == hipSuccess) e = hipEventRecord(ev, j.stream);
     return e;
 }
@@ -96,6 +97,8 @@ void work(Job &j, int seat)
 struct Pool {
     std::mutex use;  // one transfer at a time; guards slots
     double *slots = nullptr;
+    uint32_t *flags = nullptr;  // (behind the slots)
+    uint32_t seq = 0;           // of the last transfer with flags; 0 is never one's
     std::mutex m;  // guards the rest
     std::condition_variable wake, done;
     std::vector<std::thread> threads;
@@ -128,6 +131,21 @@ Pool &pool()
     return *p;
 }
 
+// Waits for the flags of all blocks, at most 100 us (the stream may have
+// more work before the kernel): false if some are missing.
+bool all_done(const StageDone &done, size_t blocks)
+{
+    const auto t0 = std::chrono::steady_clock::now();
+    for (size_t b = 0; b < blocks;) {
+        for (int spin = 0; spin < 64 && b < blocks; ++spin)
+            while (b < blocks && __atomic_load_n(&done.flag[b], __ATOMIC_ACQUIRE) == done.seq) ++b;
+        if (b < blocks &&
+            std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(100))
+            return false;
+    }
+    return true;
+}
+
 hipError_t transfer(int device, hipStream_t s, double *host, size_t n, bool to_host,
                     const StageKernel &kernel)
 {
@@ -137,10 +155,14 @@ hipError_t transfer(int device, hipStream_t s, double *host, size_t n, bool to_h
     if (!p.slots) {
         void *mem = nullptr;
         // portable: the transfers of every device go through the same slots
-        const hipError_t e = hipHostMalloc(
-            &mem, 2 * kStageWorkers * kStageSlotDoubles * sizeof(double), hipHostMallocPortable);
+        const size_t bytes = 2 * kStageWorkers * kStageSlotDoubles * sizeof(double);
+        const hipError_t e =
+            hipHostMalloc(&mem, bytes + kStageFlags * sizeof(uint32_t), hipHostMallocPortable);
         if (e != hipSuccess) return e;
         p.slots = static_cast<double *>(mem);
+        p.flags = reinterpret_cast<uint32_t *>(static_cast<char *>(mem) + bytes);
+        memset(p.flags, 0, kStageFlags * sizeof(uint32_t));
+        p.seq = 0;
     }
     Job j;
     j.device = device;
@@ -152,10 +174,19 @@ hipError_t transfer(int device, hipStream_t s, double *host, size_t n, bool to_h
     j.kernel = &kernel;
     j.slots = p.slots;
     if (j.chunks == 1) {
-        hipError_t e = hipSuccess;
+        const size_t blocks = (n + kStageBlock - 1) / kStageBlock;
+        const bool flags = to_host && blocks <= (size_t)kStageFlags;
         if (!to_host) memcpy(p.slots, host, n * sizeof(double));
-        if ((e = kernel(p.slots, 0, n, s)) != hipSuccess) return e;
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+        StageDone done{nullptr, 0};
+        if (flags) {
+            done.flag = p.flags;
+            if (++p.seq == 0) p.seq = 1;
+            done.seq = p.seq;
+        }
+        hipError_t e = kernel(p.slots, 0, n, done, s);
+        if (e != hipSuccess) return e;
+        if (!flags || !all_done(done, blocks))
+            if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
         if (to_host) memcpy(host, p.slots, n * sizeof(double));
         return hipSuccess;
     }

@@ -1125,7 +1125,8 @@ __device__ constexpr double kWd[9] = {4.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 9, 1.0 / 
 template <int S>
 __global__ __launch_bounds__(kThreads) void get_kernel(const void *pops,
                                                        const LatticeParams *params, int lattice,
-                                                       int64_t first, int64_t n, double *out)
+                                                       int64_t first, int64_t n, double *out,
+                                                       StageDone done)
 {
     using T = typename Codec<S>::T;
     const LatticeParams &P = params[lattice];
@@ -1142,6 +1143,7 @@ __global__ __launch_bounds__(kThreads) void get_kernel(const void *pops,
         const float d = Codec<S>::decode(p[(int64_t)i * plane + ys * px + xs], P, i);
         out[j] = kWd[i] * (double)P.rho0 + (double)d;
     }
+    stage_signal(done);
 }
 
 template <int S>
@@ -1168,16 +1170,19 @@ __global__ __launch_bounds__(kThreads) void set_kernel(void *pops, const Lattice
 }
 
 hipError_t launch_get(const DeviceView &v, int lattice, int64_t first, int64_t n, double *out,
-                      hipStream_t s)
+                      StageDone done, hipStream_t s)
 {
     const dim3 grid(grid_for(n)), block(kThreads);
     const void *p = v.pops[v.cur];
     if (v.storage == kF32)
-        hipLaunchKernelGGL(get_kernel<kF32>, grid, block, 0, s, p, v.params, lattice, first, n, out);
+        hipLaunchKernelGGL(get_kernel<kF32>, grid, block, 0, s, p, v.params, lattice, first, n, out,
+                           done);
     else if (v.storage == kBF16)
-        hipLaunchKernelGGL(get_kernel<kBF16>, grid, block, 0, s, p, v.params, lattice, first, n, out);
+        hipLaunchKernelGGL(get_kernel<kBF16>, grid, block, 0, s, p, v.params, lattice, first, n, out,
+                           done);
     else
-        hipLaunchKernelGGL(get_kernel<kF16>, grid, block, 0, s, p, v.params, lattice, first, n, out);
+        hipLaunchKernelGGL(get_kernel<kF16>, grid, block, 0, s, p, v.params, lattice, first, n, out,
+                           done);
     return hipGetLastError();
 }
 
