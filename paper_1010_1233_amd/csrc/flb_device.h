@@ -149,6 +149,17 @@ __device__ __forceinline__ float2 stream_load(const float2 *p)
     return make_float2(t.x, t.y);
 }
 
+// The value of the lane to the left or right (wave shift right or left); the
+// wave's end lanes get 0.
+__device__ __forceinline__ float wave_from_left(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float wave_from_right(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+
 // D2Q9 velocities in the order of Sec. 3.
 __device__ constexpr int kVX[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
 __device__ constexpr int kVY[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};

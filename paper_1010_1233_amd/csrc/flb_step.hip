@@ -788,17 +788,6 @@ hipError_t launch_step3(const DeviceView &v, const StepItem *items, int nitems, 
 // loop (25 KB more code, fetched cold by every launch) cost a quarter.
 // ---------------------------------------------------------------------
 
-// the value of the lane at x - 1 (wave shift right) or x + 1 (left); the
-// wave's end lanes get 0
-__device__ __forceinline__ float from_left(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float from_right(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
-}
-
 // `base` plus a byte offset
 template <typename U> __device__ __forceinline__ const U *bytes_at(const U *base, uint32_t off)
 {
@@ -889,14 +878,14 @@ __attribute__((amdgpu_waves_per_eu(4))) void march_kernel(StepArgs g, int rows)
             e[5] = B[k][p][1];
             e[6] = B[k][p][2];
             e[4] = stored<S>(d[4]);
-            e[7] = from_right(stored<S>(d[7]));
-            e[8] = from_left(stored<S>(d[8]));
+            e[7] = wave_from_right(stored<S>(d[7]));
+            e[8] = wave_from_left(stored<S>(d[8]));
             A[k][0] = stored<S>(d[0]);
-            A[k][1] = from_left(stored<S>(d[1]));
-            A[k][2] = from_right(stored<S>(d[3]));
+            A[k][1] = wave_from_left(stored<S>(d[1]));
+            A[k][2] = wave_from_right(stored<S>(d[3]));
             B[k][p][0] = stored<S>(d[2]);
-            B[k][p][1] = from_left(stored<S>(d[5]));
-            B[k][p][2] = from_right(stored<S>(d[6]));
+            B[k][p][1] = wave_from_left(stored<S>(d[5]));
+            B[k][p][2] = wave_from_right(stored<S>(d[6]));
             if (i < 2 * k) break;
             update_site<NOISE, S>(e, P, (uint32_t)(yk[k] * nx) + sx, t + k, g.key0, g.key1);
 #pragma unroll

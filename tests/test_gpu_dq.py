@@ -244,3 +244,21 @@ def test_sums_at_the_limits_of_the_line_transforms(flb, oracle_lib, model, sides
     scale = np.abs(o.acc).reshape(len(acc), -1).max(axis=1)
     for q in range(len(acc)):
         assert np.abs(acc[q] - o.acc[q]).max() <= 2e-4 * max(scale[q], scale.max() * 1e-3), q
+
+
+@pytest.mark.parametrize("n", [2, 3, 7, 9, 255, 497, 498, 499, 505, 1993, 2005])
+@pytest.mark.parametrize("steps", [2, 7, 8, 9, 23])
+def test_line_launches_equal_one_step_launches(flb, n, steps):
+    """D1Q3 launches of several steps, at the edges of a wave's 498 sites and
+    a block's 1992: the same bits as one step at a time."""
+    got = []
+    for many in (True, False):
+        g = flb.DqLattice("D1Q3", (n,), [1.0, 1.0, 0.8], 1e-3, u0=[0.03], seed=8, stream_id=2)
+        g.thermalize()
+        if many:
+            g.step(steps)
+        else:
+            for _ in range(steps):
+                g.step(1)
+        got.append(g.get_populations())
+    assert np.array_equal(got[0], got[1])
