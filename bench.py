@@ -18,8 +18,8 @@ second (GLUPS) over the timed region, inputs resident in HBM.
 The JSON line also carries
   roofline      the step kernel (dominant): algorithmic bytes per launch
                 (9 reads + 9 writes per site update, times the updates of
-                one launch: two per site for the time-blocked kernel, which
-                moves the state once for both) over its average duration,
+                one launch: up to five per site in the time-blocked kernels,
+                which move the state once for all) over its average duration,
                 measured with a HIP event pair around each launch of every
                 fourth benchmark step on the stream it runs on, within the
                 timed region (so while the sample shares the device;
@@ -36,7 +36,7 @@ The JSON line also carries
   forms         step-kernel rates of the other storage formats and of the
                 noise-free step (the paper's ghost-noise overhead), and the
                 batched forms (96 x 512^2 Galilean-invariance sweep, 64
-                uneven lattices) through graph-replayed sampling periods,
+                uneven lattices) through whole sampling periods,
                 and the other velocity sets (D3Q15 at 256^3 with its
                 correlators, D1Q3 at 2^26 sites).
 Every handle's step-kernel launch shape is chosen by the library's autotuner
@@ -69,43 +69,64 @@ STEP_KERNEL = "step_kernel"
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("flb_step.hip", "flb_device.h", "flb_internal.h"):
+    for f in ("flb_step.hip", "flb_collide.h", "flb_device.h", "flb_internal.h"):
         with open(os.path.join(ROOT, "paper_1010_1233_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
 
-def shape_key(workload, storage, shape, blocking=(1, 64)):
-    """Key of a launch shape: one-step kernels by threads x sites, the
-    two-step kernel by its tile width."""
+def shape_key(workload, storage, shape, blocking=(1, 64), steps=None):
+    """Key of a launch shape: one-step kernels by threads x sites, the tiled
+    kernels of several steps by their tile width, the library's own grouping
+    (`steps` above what `blocking` says) by its steps per launch."""
     tw, sites, nt = shape
+    if steps is not None and steps > blocking[0]:
+        return f"{workload}/{storage}/own{round(steps)}"
     if blocking[0] >= 2:
         return f"{workload}/{storage}/step{blocking[0]}_{blocking[1]}/nt{int(bool(nt))}"
     return f"{workload}/{storage}/{tw}x{sites}/nt{int(bool(nt))}"
 
 
-KERNEL_OF_STEPS = {1: STEP_KERNEL, 2: "step2_kernel", 3: "step3_kernel"}
+# the dominant kernel of one large lattice by its steps per launch
+KERNEL_OF_STEPS = {1: STEP_KERNEL, 2: "step2_kernel", 3: "step3_kernel", 4: "march_kernel",
+                   5: "march_kernel"}
 
 
-def launch_figures(g, sites, step_ms, steps=None):
+def kind_steps(kinds, steps):
+    """Steps per launch of each of launch_timing_kinds' three kinds, `steps`
+    in all: one, two, and the mean of the rest (three, or more when the
+    library groups the steps itself)."""
+    rest = steps - kinds[0][0] - 2 * kinds[1][0]
+    assert rest >= 0 and (rest > 0) == (kinds[2][0] > 0), (kinds, steps)
+    return [1, 2, rest / kinds[2][0] if kinds[2][0] else 3]
+
+
+def steps_per_launch(g, n=60):
+    """Steps per launch of n steps taken by one call."""
+    g.launch_timing_kinds()
+    g.set_launch_timing(True)
+    g.step(n)
+    g.set_launch_timing(False)
+    return n / sum(c for c, _ in g.launch_timing_kinds())
+
+
+def launch_figures(g, sites, step_ms, steps):
     """The dominant kernel's launch: which kernel, steps per launch, its
     duration and its algorithmic bytes = 18 values per site update (9 loads
-    + 9 stores) x the site updates of one launch.  The two- and three-step
-    kernels do two or three updates per site and launch on one read and one
+    + 9 stores) x the site updates of one launch.  The kernels of several
+    steps do that many updates per site and launch on one read and one
     write of the state, so their algorithmic rate can exceed what HBM moves
     (see the measured traffic)."""
-    if steps is None:
-        steps = g.time_blocking()[0]
     bpv = g.storage_info()[1]
     launch_ms = steps * step_ms
     algo = 18 * bpv * sites * steps
-    return {"kernel": KERNEL_OF_STEPS[steps],
+    return {"kernel": KERNEL_OF_STEPS.get(round(steps), "patch_kernel"),
             "steps_per_launch": steps, "avg_launch_ms": launch_ms,
             "algorithmic_bytes_per_launch": algo,
             "achieved_GBs": algo / (launch_ms * 1e-3) / 1e9}
 
 
-def counter_entry(workload, storage, shape, blocking=(1, 64)):
+def counter_entry(workload, storage, shape, blocking=(1, 64), steps=None):
     """This launch shape's entry of the committed counter summary (HBM bytes
     per step-kernel launch, VALU instructions per site update), or {}
     when it is missing or was taken on a different kernel source."""
@@ -115,23 +136,19 @@ def counter_entry(workload, storage, shape, blocking=(1, 64)):
             d = json.load(fh)
     except (OSError, ValueError):
         return {}
-    e = d.get(shape_key(workload, storage, shape, blocking))
+    e = d.get(shape_key(workload, storage, shape, blocking, steps))
     if not e or e.get("kernel_source_hash") != kernel_source_hash():
         return {}
     return e
 
 
-def measured_traffic(workload, storage, shape, blocking=(1, 64)):
-    """HBM bytes per step-kernel launch of this launch shape from the
-    committed counter summary, or None (see counter_entry)."""
-    return counter_entry(workload, storage, shape, blocking).get("bytes_per_launch")
-
-
 def sweep_shapes(flb, workloads, name, storage, steps=5):
     """Runs every step-kernel launch shape for a few steps (no timing): the
-    workload for per-shape hardware-counter runs."""
+    workload for per-shape hardware-counter runs.  First the library's own
+    grouping: launches of five steps (16-bit storage: four)."""
     g, c = make_lattice(flb, workloads, name, storage)
     g.thermalize()
+    g.step((5 if storage == "f32" else 4) * steps)
     for tw in (64, 128, 256):
         for sites in (1, 2, 4):
             for nt in (0, 1):
@@ -145,7 +162,8 @@ def sweep_shapes(flb, workloads, name, storage, steps=5):
                 g.step(blocking * steps)
     g.set_time_blocking(1, 64)
     g.synchronize()
-    print(f"sweep-shapes: {name} {storage}: 18 one-step shapes x {steps} steps, "
+    print(f"sweep-shapes: {name} {storage}: {steps} launches of the library's grouping, "
+          f"18 one-step shapes x {steps} steps, "
           f"6 two-step and 6 three-step shapes x {steps} launches", flush=True)
 
 
@@ -232,19 +250,17 @@ def plain_path_ms(torch, g, stream, n=ACCUMULATE_EVERY, warm=16):
 
 
 def batched_form(torch, flb, stream, specs, storage, periods=ACCUMULATE_EVERY):
-    """Whole path (graph-replayed periods of SAMPLE_EVERY steps + a sample)
-    and step-only rates of one batched handle."""
-    # the captured periods depend on the buffer parity and on how many of the
-    # samples of an accumulation cycle are stashed: a whole number of cycles
-    # starts the timed run where the warm-up started, so that it replays
-    # graphs the warm-up captured
+    """Whole path (periods of SAMPLE_EVERY steps + a sample) and step-only
+    rates of one batched handle."""
+    # whole accumulation cycles: the timed run does the whole work of exactly
+    # its own samples
     assert periods % ACCUMULATE_EVERY == 0
     b = flb.Lattice.batch(specs, seed=3, storage=storage)
     b.set_stream(stream)
     b.thermalize()
     shape, _ = b.autotune_path(50, SAMPLE_EVERY)
     sites = sum(s["nx"] * s["ny"] for s in specs)
-    b.run(periods * SAMPLE_EVERY, SAMPLE_EVERY)  # capture the graphs
+    b.run(periods * SAMPLE_EVERY, SAMPLE_EVERY)
     b.synchronize()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     e0.record(stream)
@@ -254,7 +270,7 @@ def batched_form(torch, flb, stream, specs, storage, periods=ACCUMULATE_EVERY):
     e1.synchronize()
     ms_period = e0.elapsed_time(e1) / periods
     step_ms = steady_step_ms(torch, b, stream)
-    lf = launch_figures(b, sites, step_ms)
+    lf = launch_figures(b, sites, step_ms, steps_per_launch(b))
     shape = list(shape) + [list(b.time_blocking())]
     tiles = b.lattice_tiles()
     b.close()
@@ -539,20 +555,21 @@ def main():
         elapsed = time.perf_counter() - t0
         kinds = g.launch_timing_kinds()
 
-    # launches of 1, 2 and 3 steps (with three steps per launch a period of
-    # ten steps is 3 + 3 + 2 + 2); the roofline takes the kind that took the
-    # most time
+    # launches of 1, 2 and more steps (with three steps per launch a period of
+    # ten steps is 3 + 3 + 2 + 2, with the library's own grouping 5 + 5); the
+    # roofline takes the kind that took the most time
     steps_timed = -(-args.steps // LAUNCH_TIMING_EVERY)
-    assert sum((q + 1) * n for q, (n, _) in enumerate(kinds)) == steps_timed * SAMPLE_EVERY, kinds
+    ksteps = kind_steps(kinds, steps_timed * SAMPLE_EVERY)
     n_launches = sum(n for n, _ in kinds)
     step_ms = sum(ms for _, ms in kinds) / (steps_timed * SAMPLE_EVERY)
     qd = max(range(3), key=lambda q: kinds[q][1])
     ms_per_step = elapsed * 1e3 / args.steps
     value = args.steps * SAMPLE_EVERY * V / elapsed / 1e9
-    launch = launch_figures(g, V, kinds[qd][1] / kinds[qd][0] / (qd + 1), steps=qd + 1)
+    launch = launch_figures(g, V, kinds[qd][1] / kinds[qd][0] / ksteps[qd], ksteps[qd])
     achieved = launch["achieved_GBs"]
-    traffic = measured_traffic(args.workload, args.storage, tuned, blocking)
-    valu = counter_entry(args.workload, args.storage, tuned, blocking).get("valu_insts_per_update")
+    counters = counter_entry(args.workload, args.storage, tuned, blocking, ksteps[qd])
+    traffic = counters.get("bytes_per_launch")
+    valu = counters.get("valu_insts_per_update")
     drift = float(abs(g.sample_conservation()[0] - cons0[0]))
 
     # correlator sanity (matched S(k)): k-averaged S(rho) over the run
@@ -565,7 +582,8 @@ def main():
     with torch.cuda.stream(stream):
         # 120 steps: whole launches of the dominant kind
         iso_ms = steady_step_ms(torch, g, stream, n=120, warm=240)
-    iso = launch_figures(g, V, iso_ms)
+        iso_steps = steps_per_launch(g, 120)
+    iso = launch_figures(g, V, iso_ms, iso_steps)
     # the device copy of one population buffer (the bytes one step moves at
     # the algorithmic count): the practical ceiling next to 8 TB/s
     copy_rate = copy_GBs(torch, stream, 9 * V * g.storage_info()[1])
@@ -645,7 +663,7 @@ def main():
                 h.thermalize()
                 shape, _ = h.autotune(50)
                 ms = steady_step_ms(torch, h, stream)
-                lf = launch_figures(h, V, ms)
+                lf = launch_figures(h, V, ms, steps_per_launch(h))
                 pms = plain_path_ms(torch, h, stream)
                 forms[st] = {"step_glups": V / (ms * 1e-3) / 1e9,
                              "path_glups": SAMPLE_EVERY * V / (pms * 1e-3) / 1e9,

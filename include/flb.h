@@ -348,8 +348,9 @@ int flb_get_step_config(flb_t *h, int *tile_w, int *sites, int *nontemporal);
  * Until this call, flb_set_lattice_tiles, flb_set_step_config or a tuning
  * call chooses a shape, the library groups the steps itself, by the
  * lattices' sizes and the storage format, up to five per launch;
- * flb_get_time_blocking then reports steps_per_launch = 1 (as it does when
- * a tuning call finds that grouping the fastest).
+ * flb_get_time_blocking then reports steps_per_launch = 1.  When a tuning
+ * call finds that grouping the fastest, the handle keeps it and this call and
+ * flb_get_step_config report the fastest of the shapes that can be set.
  * flb_get_time_blocking reports tile_w = 0 while each lattice has its own
  * tile (flb_set_lattice_tiles). */
 int flb_set_time_blocking(flb_t *h, int steps_per_launch, int tile_w);

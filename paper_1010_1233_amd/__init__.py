@@ -324,7 +324,9 @@ class Lattice:
 
     def time_blocking(self):
         """(steps per launch, two-step tile width); the width is 0 while
-        each lattice has its own (lattice_tiles())."""
+        each lattice has its own (lattice_tiles()).  While the library groups
+        the steps itself: (1, 64), or after tuning the fastest shape that can
+        be set."""
         a, b = ctypes.c_int(), ctypes.c_int()
         _check(lib().flb_get_time_blocking(self._h, ctypes.byref(a), ctypes.byref(b)))
         return a.value, b.value
@@ -355,7 +357,8 @@ class Lattice:
         """Time every step-kernel launch shape on this handle, the
         time-blocked ones included, and keep the fastest (state unchanged);
         returns the chosen (tile_w, sites, nontemporal) and its ms per step
-        (``time_blocking()`` tells whether pairs of steps won)."""
+        (``time_blocking()`` holds the steps per launch of the fastest
+        shape that can be set)."""
         ms = ctypes.c_double()
         _check(lib().flb_autotune(self._h, int(nsteps), ctypes.byref(ms)))
         return self.step_config(), ms.value

@@ -90,24 +90,26 @@ struct flb {
     bool nontemporal = false;
     StepItem *d_items = nullptr;
     int nitems = 0;
-    // time blocking: steps per launch (1, 2 or 3; 0 while no shape was set
-    // or tuned: the library's own choice, see launch_plan) and the two- and
-    // three-step kernels' tile width; tile2 = 0: each lattice has its own,
-    // log2 of it in ltile (5 or 6)
+    // time blocking: steps per launch (1, 2 or 3; 0 while no shape was set or
+    // tuned: the library's own grouping, see launch_plan; negative: that
+    // grouping by a tuning call, -tblock what the handle reports) and the
+    // two- and three-step kernels' tile width; tile2 = 0: each lattice has its
+    // own, log2 of it in ltile (5 or 6)
     int tblock = 0, tile2 = 64;
+    bool own_grouping() const { return tblock <= 0; }
     std::vector<int8_t> ltile;
     StepItem *d_items2 = nullptr;
     int nitems2 = 0;
     // lattices small enough for one block each (flb_small.h): all of them
-    // are (then they step and sample resident in LDS while tblock = 0), and
-    // the threads and LDS of a block, stepping alone and with samples
+    // are (then the library's own grouping steps and samples them resident in
+    // LDS), and the threads and LDS of a block, stepping alone and with samples
     int32_t *d_small = nullptr;
     int n_small = 0, small_threads = 0;
     int small_lds[3] = {0, 0, 0};  // steps only, samples, samples and their sums
     bool small_keep = false;       // launches of several samples keep the sums in LDS
     bool all_small() const { return n_small == (int)params.size(); }
-    // marching launches of 4 and 5 steps ([0], [1]), with tblock = 0 and
-    // lattices large enough for them
+    // marching launches of 4 and 5 steps ([0], [1]), in the library's own
+    // grouping of lattices large enough for them
     bool march = false;
     // ... or launches of up to patch_steps steps on small tiles (0: not these)
     int patch_steps = 0, patch_w = 0, patch_h = 0, n_patch = 0;
@@ -468,7 +470,7 @@ constexpr int kMarchMinRows = 12;
 int build_march_items(flb_t *h)
 {
     h->march = false;
-    if (h->tblock != 0) return FLB_OK;
+    if (!h->own_grouping()) return FLB_OK;
     int ncu = 0;
     FLB_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
     for (int q = 0; q < 2; ++q) {
@@ -495,7 +497,7 @@ int build_march_items(flb_t *h)
 int build_patch_items(flb_t *h)
 {
     h->patch_steps = 0;
-    if (h->tblock != 0 || h->march) return FLB_OK;
+    if (!h->own_grouping() || h->march) return FLB_OK;
     int ncu = 0;
     FLB_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
     auto tiles = [&](int tw, int th) {
@@ -1144,8 +1146,8 @@ int flush_pending(flb_t *h)
     return FLB_OK;
 }
 
-// With launch timing on, records the first
-// event of a launch of `steps` steps; stop is the one to record after it.
+// With launch timing on, records the first event of a launch of `steps`
+// steps; stop is the one to record after it.
 int begin_timed(flb_t *h, int steps, hipStream_t s, hipEvent_t &stop)
 {
     stop = nullptr;
@@ -1263,7 +1265,7 @@ int settle_due(flb_t *h)
 int enqueue_steps_overlapped(flb_t *h, int64_t n)
 {
     const hipStream_t s = h->stream;
-    if (n >= kResidentMin && h->tblock == 0 && h->all_small()) return enqueue_resident(h, n, 0, s);
+    if (n >= kResidentMin && h->own_grouping() && h->all_small()) return enqueue_resident(h, n, 0, s);
     if (!h->due || n <= 0) return enqueue_steps(h, n, s);
     int rc;
     if (h->total_sites < kOverlapSites) {
@@ -1610,7 +1612,7 @@ int flb_run(flb_t *h, int64_t nsteps, int sample_every)
     if (sample_every == 0) return flb_step(h, nsteps);
     rc = setup_correlators(h);
     if (rc) return rc;
-    if (h->tblock == 0 && h->all_small()) {
+    if (h->own_grouping() && h->all_small()) {
         // steps and samples resident (the last sample included)
         const int64_t samples = (h->t + nsteps) / sample_every - h->t / sample_every;
         const bool timing = h->timing;
@@ -1908,7 +1910,7 @@ int flb_set_step_config(flb_t *h, int tile_w, int sites, int nontemporal)
     h->tile_w = tile_w;
     h->sites = sites;
     h->nontemporal = nontemporal != 0;
-    if (h->tblock == 0) h->tblock = 1;  // the shape asked for, not the library's
+    if (h->own_grouping()) h->tblock = std::max(1, -h->tblock);  // the shape asked for
     return build_step_items(h);
 }
 
@@ -1927,7 +1929,7 @@ int flb_set_time_blocking(flb_t *h, int steps_per_launch, int tile_w)
 int flb_get_time_blocking(flb_t *h, int *steps_per_launch, int *tile_w)
 {
     if (check_handle(h)) return FLB_EINVAL;
-    if (steps_per_launch) *steps_per_launch = std::max(1, h->tblock);
+    if (steps_per_launch) *steps_per_launch = std::max(1, std::abs(h->tblock));
     if (tile_w) *tile_w = h->tile2;
     return FLB_OK;
 }
@@ -1970,9 +1972,9 @@ int flb_get_step_config(flb_t *h, int *tile_w, int *sites, int *nontemporal)
 }  // extern "C"
 
 // A step launch shape: one-step tile width, sites per thread, streaming
-// accesses, steps per launch (1, 2 or 3; 0 the library's own grouping, see
-// launch_plan), two- and three-step tile width
-// (0: per lattice, log2 of each lattice's in lt).
+// accesses, steps per launch (1, 2 or 3; 0 or less the library's own grouping,
+// see flb_t::tblock), two- and three-step tile width (0: per lattice, log2 of
+// each lattice's in lt).
 struct StepShape {
     int tw, sv, nt, tb, t2;
     std::vector<int8_t> lt;
@@ -2033,7 +2035,7 @@ static bool cached_shape(const char *cache, const std::string &key, size_t nlat,
             x.t2 = atoi(t2s.c_str());
             if (!step2_tile_supported(x.t2)) continue;
         }
-        if (step_tile_supported(x.tw, x.sv) && x.tb >= 0 && x.tb <= 3) {
+        if (step_tile_supported(x.tw, x.sv) && x.tb >= -3 && x.tb <= 3) {
             found = true;
             c = x;
             ms = t;
@@ -2131,7 +2133,9 @@ static int time_shapes(flb_t *h, int nsteps, const std::vector<StepShape> &shape
     });
 }
 
-// Every supported launch shape timed alone, fastest first.
+// Every supported launch shape timed alone, fastest first.  The library's own
+// grouping carries the fastest of the others, as what the handle reports: a
+// program that copies a tuned shape to another handle sets that one.
 static int time_every_shape(flb_t *h, int nsteps, std::vector<std::pair<float, StepShape>> &out)
 {
     std::vector<StepShape> shapes;
@@ -2141,7 +2145,7 @@ static int time_every_shape(flb_t *h, int nsteps, std::vector<std::pair<float, S
     for (int tb : {2, 3})
         for (int t2 : {32, 64, 128})
             for (int nt = 0; nt < 2; ++nt) shapes.push_back({h->tile_w, h->sites, nt, tb, t2, {}});
-    for (int nt = 0; nt < 2; ++nt) shapes.push_back({h->tile_w, h->sites, nt, 0, 64, {}});
+    shapes.push_back({h->tile_w, h->sites, h->nontemporal ? 1 : 0, 0, 64, {}});
     std::vector<float> best;
     if (int rc = time_shapes(h, nsteps, shapes, best)) return rc;
     out.clear();
@@ -2150,6 +2154,12 @@ static int time_every_shape(flb_t *h, int nsteps, std::vector<std::pair<float, S
                      [](const std::pair<float, StepShape> &a, const std::pair<float, StepShape> &b) {
                          return a.first < b.first;
                      });
+    const StepShape named = out[out[0].second.tb < 1 ? 1 : 0].second;
+    for (auto &o : out)
+        if (o.second.tb < 1) {
+            o.second = named;
+            o.second.tb = -named.tb;
+        }
     return FLB_OK;
 }
 
