@@ -132,8 +132,7 @@ struct DeviceView {
     void *pops[2];
     int cur;                          // index of the buffer holding the state
     const LatticeParams *params;      // device
-    const uint32_t *step;             // device step counter
-    uint32_t *step_rw;
+    uint32_t *step;                   // device step counters, one per population buffer
     float2 *spec;
     float2 *stash;                    // spectra awaiting accumulation (stash_offset)
     double *acc;
@@ -148,8 +147,7 @@ struct DeviceView {
 };
 
 hipError_t launch_step(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
-                       int sites, uint32_t step_add, bool nontemporal, bool noise,
-                       hipStream_t s);
+                       int sites, bool nontemporal, bool noise, hipStream_t s);
 bool step_tile_supported(int tw, int r);
 // Two steps per launch: tiles of tile_w x (1024 / tile_w) sites, tile_w 32,
 // 64 or 128; items enumerate each lattice's tiles of that shape.  tile_w 0:
@@ -157,25 +155,25 @@ bool step_tile_supported(int tw, int r);
 // an item of a 32 x 32 lattice carries kStep2Square.
 constexpr int32_t kStep2Square = 1 << 30;
 hipError_t launch_step2(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
-                        uint32_t step_add, bool nontemporal, bool noise, hipStream_t s);
+                        bool nontemporal, bool noise, hipStream_t s);
 bool step2_tile_supported(int tw);
 // Three steps per launch on the two-step kernel's tiles (tile_w 32, 64 or
 // 128, the same items).
 hipError_t launch_step3(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
-                        uint32_t step_add, bool nontemporal, bool noise, hipStream_t s);
+                        bool nontemporal, bool noise, hipStream_t s);
 // Four or five steps per launch by waves marching along y: strips of
 // march_cols(steps) columns, segments of `rows` rows; item tile = strip +
 // segment * strips, items in groups of kMarchWaves (one block each).
 constexpr int kMarchWaves = 4;
 constexpr int march_cols(int steps) { return 64 - 2 * (steps - 1); }
 hipError_t launch_march(const DeviceView &v, const StepItem *items, int nitems, int steps,
-                        int rows, uint32_t step_add, bool noise, hipStream_t s);
+                        int rows, bool noise, hipStream_t s);
 // `steps` steps per launch on tiles of tw x th sites, item = lattice and
 // tile, for lattices too small to fill the device.
 constexpr int kPatchThreads = 1024;
 int patch_lds_bytes(int tw, int th, int steps);
 hipError_t launch_patch(const DeviceView &v, const StepItem *items, int nitems, int tw, int th,
-                        int steps, uint32_t step_add, bool noise, hipStream_t s);
+                        int steps, bool noise, hipStream_t s);
 hipError_t launch_advance_step(uint32_t *step, uint32_t n, hipStream_t s);
 hipError_t launch_init(const DeviceView &v, int lattice, int64_t plane, hipStream_t s);
 // values first .. first + n - 1 of the lattice's FP64 populations, to or

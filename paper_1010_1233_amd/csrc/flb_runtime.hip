@@ -81,7 +81,7 @@ struct flb {
     void *pops[2] = {nullptr, nullptr};
     int cur = 0;
     LatticeParams *d_params = nullptr;
-    uint32_t *d_step = nullptr;
+    uint32_t *d_step = nullptr;  // step counters of the states in pops[0], pops[1]
     double *d_red = nullptr;  // reduction scratch
     int red_blocks = 1024;
 
@@ -197,7 +197,6 @@ struct flb {
         v.cur = cur;
         v.params = d_params;
         v.step = d_step;
-        v.step_rw = d_step;
         v.spec = d_spec;
         v.stash = d_stash;
         v.acc = d_acc;
@@ -650,13 +649,13 @@ int build_small_items(flb_t *h)
 
 // The resident kernel: nsteps steps of lattices that are all small, the
 // samples inside (see launch_small).
-hipError_t launch_resident(flb_t *h, uint32_t step_add, uint32_t nsteps, uint32_t every,
+hipError_t launch_resident(flb_t *h, uint32_t nsteps, uint32_t every,
                            bool sample_first, hipStream_t s)
 {
     const bool sampled = every || sample_first;
     const bool keep = h->small_keep && every && nsteps >= 2 * every;
     return launch_small(h->view(), h->d_small, h->n_small, h->small_threads,
-                        h->small_lds[sampled ? (keep ? 2 : 1) : 0], step_add, nsteps, every,
+                        h->small_lds[sampled ? (keep ? 2 : 1) : 0], nsteps, every,
                         sample_first, keep, h->noise, h->moments, s);
 }
 
@@ -1096,7 +1095,7 @@ int setup_correlators(flb_t *h)
 int enqueue_sample(flb_t *h, hipStream_t s, hipEvent_t ev_read = nullptr)
 {
     const DeviceView v = h->view();
-    if (h->n_small) FLB_HIP(launch_resident(h, 0, 0, 0, true, s));
+    if (h->n_small) FLB_HIP(launch_resident(h, 0, 0, true, s));
     if (h->all_small()) {
         if (ev_read) FLB_HIP(hipEventRecord(ev_read, s));
         return FLB_OK;
@@ -1170,13 +1169,22 @@ int begin_timed(flb_t *h, int steps, hipStream_t s, hipEvent_t &stop)
     return FLB_OK;
 }
 
-// n steps from the device counter value; the counter is advanced afterwards.
-// launch_plan says how the steps are grouped. When wait_before_second is
-// given, the second launch (the first to write the buffer that held the
-// state at the start) waits for it.
+// Whether the stream is being captured into the caller's graph.
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// n steps from the device counter's value.  launch_plan says how the steps
+// are grouped. When wait_before_second is given, the second launch (the first
+// to write the buffer that held the state at the start) waits for it.
 int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_second = nullptr)
 {
-    int64_t k = 0;
     int launches = 0;
     hipEvent_t stop = nullptr;
     auto before_launch = [&](int steps) -> int {
@@ -1186,46 +1194,50 @@ int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_sec
     };
     auto after_launch = [&]() -> int {
         if (stop) FLB_HIP(hipEventRecord(stop, s));
+        h->cur ^= 1;
         return FLB_OK;
     };
-    if (h->patch_steps && n > 1) {
-        // launches of (nearly) equal length
-        const int64_t launches = (n + h->patch_steps - 1) / h->patch_steps;
-        for (int64_t i = 0; i < launches; ++i) {
-            const int steps = (int)((n * (i + 1)) / launches - (n * i) / launches);
-            if (int rc = before_launch(steps)) return rc;
-            FLB_HIP(launch_patch(h->view(), h->d_patch, h->n_patch, h->patch_w, h->patch_h, steps,
-                                 (uint32_t)k, h->noise, s));
-            if (int rc = after_launch()) return rc;
-            h->cur ^= 1;
-            k += steps;
+    auto enqueue = [&](int64_t n) -> int {
+        if (h->patch_steps && n > 1) {
+            // launches of (nearly) equal length
+            const int64_t m = (n + h->patch_steps - 1) / h->patch_steps;
+            for (int64_t i = 0; i < m; ++i) {
+                const int steps = (int)((n * (i + 1)) / m - (n * i) / m);
+                if (int rc = before_launch(steps)) return rc;
+                FLB_HIP(launch_patch(h->view(), h->d_patch, h->n_patch, h->patch_w, h->patch_h,
+                                     steps, h->noise, s));
+                if (int rc = after_launch()) return rc;
+            }
+            return FLB_OK;
         }
-        if (n > 0) FLB_HIP(launch_advance_step(h->d_step, (uint32_t)n, s));
+        const LaunchPlan plan = launch_plan(h, n);
+        for (int steps = 5; steps >= 1; --steps)
+            for (int64_t i = 0; i < plan.of[steps]; ++i) {
+                if (int rc = before_launch(steps)) return rc;
+                const DeviceView v = h->view();
+                if (steps >= 4)
+                    FLB_HIP(launch_march(v, h->d_march[steps - 4], h->n_march[steps - 4], steps,
+                                         h->march_rows[steps - 4], h->noise, s));
+                else if (steps == 3)
+                    FLB_HIP(launch_step3(v, h->d_items2, h->nitems2, h->tile2, h->nontemporal,
+                                         h->noise, s));
+                else if (steps == 2)
+                    FLB_HIP(launch_step2(v, h->d_items2, h->nitems2, h->tile2, h->nontemporal,
+                                         h->noise, s));
+                else
+                    FLB_HIP(launch_step(v, h->d_items, h->nitems, h->tile_w, h->sites,
+                                        h->nontemporal, h->noise, s));
+                if (int rc = after_launch()) return rc;
+            }
         return FLB_OK;
+    };
+    // A caller's graph of an even number of steps can be replayed: it leaves
+    // the state in the buffer it found it in, whatever the grouping.
+    if (n > 0 && n % 2 == 0 && h->own_grouping() && capturing(s)) {
+        if (int rc = enqueue(n / 2)) return rc;
+        return enqueue(n / 2);
     }
-    const LaunchPlan plan = launch_plan(h, n);
-    for (int steps = 5; steps >= 1; --steps)
-        for (int64_t i = 0; i < plan.of[steps]; ++i, k += steps) {
-            if (int rc = before_launch(steps)) return rc;
-            const DeviceView v = h->view();
-            const uint32_t add = (uint32_t)k;
-            if (steps >= 4)
-                FLB_HIP(launch_march(v, h->d_march[steps - 4], h->n_march[steps - 4], steps,
-                                     h->march_rows[steps - 4], add, h->noise, s));
-            else if (steps == 3)
-                FLB_HIP(launch_step3(v, h->d_items2, h->nitems2, h->tile2, add, h->nontemporal,
-                                     h->noise, s));
-            else if (steps == 2)
-                FLB_HIP(launch_step2(v, h->d_items2, h->nitems2, h->tile2, add, h->nontemporal,
-                                     h->noise, s));
-            else
-                FLB_HIP(launch_step(v, h->d_items, h->nitems, h->tile_w, h->sites, add,
-                                    h->nontemporal, h->noise, s));
-            if (int rc = after_launch()) return rc;
-            h->cur ^= 1;
-        }
-    if (n > 0) FLB_HIP(launch_advance_step(h->d_step, (uint32_t)n, s));
-    return FLB_OK;
+    return enqueue(n);
 }
 
 // Steps per launch of the resident kernel (a launch of a few milliseconds).
@@ -1240,10 +1252,10 @@ int enqueue_resident(flb_t *h, int64_t n, int every, hipStream_t s)
         const int64_t m = std::min(n - k, kResidentSteps);
         hipEvent_t stop = nullptr;
         if (int rc = begin_timed(h, (int)m, s, stop)) return rc;
-        FLB_HIP(launch_resident(h, 0, (uint32_t)m, (uint32_t)every, h->due, s));
+        FLB_HIP(launch_resident(h, (uint32_t)m, (uint32_t)every, h->due, s));
         if (stop) FLB_HIP(hipEventRecord(stop, s));
         h->due = false;
-        FLB_HIP(launch_advance_step(h->d_step, (uint32_t)m, s));
+        FLB_HIP(launch_advance_step(h->d_step + h->cur, (uint32_t)m, s));
         k += m;
     }
     return FLB_OK;
@@ -1368,13 +1380,13 @@ flb_t *create_impl(int n, const flb_lattice_spec *specs, uint64_t seed, int stor
         return bail(0);
     }
     h->pops[1] = (char *)h->pops[0] + bytes;
-    if (hipMalloc((void **)&h->d_step, sizeof(uint32_t)) != hipSuccess ||
+    if (hipMalloc((void **)&h->d_step, 2 * sizeof(uint32_t)) != hipSuccess ||
         hipMalloc((void **)&h->d_red, (size_t)(h->red_blocks * 9 + 16) * sizeof(double)) !=
             hipSuccess) {
         fail(FLB_ENOMEM, "scratch allocation failed");
         return bail(0);
     }
-    if (hipMemsetAsync(h->d_step, 0, sizeof(uint32_t), h->stream) != hipSuccess) {
+    if (hipMemsetAsync(h->d_step, 0, 2 * sizeof(uint32_t), h->stream) != hipSuccess) {
         fail(FLB_EHIP, "step counter reset failed");
         return bail(0);
     }
@@ -1867,7 +1879,7 @@ int flb_set_step(flb_t *h, int64_t t)
     if (t < 0 || t >= (int64_t)0xFFFFFFFF) return fail(FLB_EINVAL, "t outside [0, 2^32 - 1)");
     const uint32_t v = (uint32_t)t;
     FLB_HIP(hipStreamSynchronize(h->stream));
-    FLB_HIP(hipMemcpy(h->d_step, &v, sizeof v, hipMemcpyHostToDevice));
+    FLB_HIP(hipMemcpy(h->d_step + h->cur, &v, sizeof v, hipMemcpyHostToDevice));
     h->t = t;
     return FLB_OK;
 }
@@ -2077,7 +2089,7 @@ template <typename F> static int with_saved_state(flb_t *h, F body)
                            h->ltile};
     h->timing = false;
     hipError_t e = hipMemcpyAsync(saved, h->pops[cur0], bytes, hipMemcpyDeviceToDevice, h->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&step0, h->d_step, sizeof step0, hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(&step0, h->d_step + cur0, sizeof step0, hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     int rc = e == hipSuccess ? body(h) : FLB_OK;
     h->timing = timing0;
@@ -2088,7 +2100,7 @@ template <typename F> static int with_saved_state(flb_t *h, F body)
     if (e == hipSuccess)
         e = hipMemcpyAsync(h->pops[cur0], saved, bytes, hipMemcpyDeviceToDevice, h->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(h->d_step, &step0, sizeof step0, hipMemcpyHostToDevice, h->stream);
+        e = hipMemcpyAsync(h->d_step + cur0, &step0, sizeof step0, hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     (void)hipFree(saved);
     if (rc != FLB_OK) return rc;
@@ -2209,10 +2221,10 @@ static int tune_lattice_tiles(flb_t *h, int nsteps, int nt, std::vector<int8_t> 
                 for (int o = 0; o < 2 && e == hipSuccess; ++o) {
                     // the same launch repeated on the same buffers: the
                     // state is put back afterwards
-                    e = launch_step2(hh->view(), d_it[o], n[o], 0, 0, nt != 0, hh->noise, hh->stream);
+                    e = launch_step2(hh->view(), d_it[o], n[o], 0, nt != 0, hh->noise, hh->stream);
                     if (e == hipSuccess) e = hipEventRecord(e0, hh->stream);
                     for (int k = 0; k < launches && e == hipSuccess; ++k)
-                        e = launch_step2(hh->view(), d_it[o], n[o], 0, 0, nt != 0, hh->noise,
+                        e = launch_step2(hh->view(), d_it[o], n[o], 0, nt != 0, hh->noise,
                                          hh->stream);
                     if (e == hipSuccess) e = hipEventRecord(e1, hh->stream);
                     if (e == hipSuccess) e = hipEventSynchronize(e1);

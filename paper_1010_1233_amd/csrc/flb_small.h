@@ -30,7 +30,7 @@ int small_lds_bytes(int nx, int ny, bool sampled, bool moments, bool keep_sums);
 // by `every` (0: none).  keep_sums: the sums stay in LDS from the first
 // sample of the launch to its end.
 hipError_t launch_small(const DeviceView &v, const int32_t *lattices, int nlat, int threads,
-                        int lds_bytes, uint32_t step_add, uint32_t nsteps, uint32_t every,
+                        int lds_bytes, uint32_t nsteps, uint32_t every,
                         bool sample_first, bool keep_sums, bool noise, bool moments,
                         hipStream_t s);
 

@@ -32,7 +32,7 @@ struct SmallArgs {
     const uint32_t *step;
     double *acc;
     double *csum_part;
-    uint32_t step_add, nsteps, every;
+    uint32_t nsteps, every;
     int sample_first, keep_sums;
     uint32_t key0, key1;
 };
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kSmallSites) void small_kernel(SmallArgs g)
         }
     }
     __syncthreads();
-    uint32_t t = *g.step + g.step_add, left = g.nsteps;
+    uint32_t t = *g.step, left = g.nsteps;
     bool due = g.sample_first != 0;
     for (;;) {
         // steps to the next sample after this one
@@ -359,7 +359,7 @@ int small_lds_bytes(int nx, int ny, bool sampled, bool moments, bool keep_sums)
 }
 
 hipError_t launch_small(const DeviceView &v, const int32_t *lattices, int nlat, int threads,
-                        int lds_bytes, uint32_t step_add, uint32_t nsteps, uint32_t every,
+                        int lds_bytes, uint32_t nsteps, uint32_t every,
                         bool sample_first, bool keep_sums, bool noise, bool moments,
                         hipStream_t s)
 {
@@ -368,10 +368,9 @@ hipError_t launch_small(const DeviceView &v, const int32_t *lattices, int nlat, 
     a.params = v.params;
     a.tables = v.tables;
     a.lattices = lattices;
-    a.step = v.step;
+    a.step = v.step + v.cur;
     a.acc = v.acc;
     a.csum_part = v.csum_part;
-    a.step_add = step_add;
     a.nsteps = nsteps;
     a.every = every;
     a.sample_first = sample_first;

@@ -20,20 +20,30 @@ struct StepArgs {
     void *dst;
     const LatticeParams *params;
     const StepItem *items;
-    const uint32_t *step;
-    uint32_t step_add;
+    const uint32_t *step;  // step counter of the state in src
+    uint32_t *step_next;   // ... and of the one in dst
     uint32_t key0, key1;
 };
 
-static StepArgs step_args(const DeviceView &v, const StepItem *items, uint32_t step_add)
+// Every step kernel calls this first: the launch's one writer of the new
+// state's counter.  (The counter belongs to the population buffer, so a launch
+// never writes the one its other blocks read, and none is needed to advance
+// it: 256^2, 100 periods of ten steps and a sample, 3.95 ms with such a launch
+// after each period's steps, 3.70 without.)
+__device__ __forceinline__ void advance_counter(const StepArgs &g, int steps)
+{
+    if (blockIdx.x == 0 && threadIdx.x == 0) *g.step_next = *g.step + (uint32_t)steps;
+}
+
+static StepArgs step_args(const DeviceView &v, const StepItem *items)
 {
     StepArgs a;
     a.src = v.pops[v.cur];
     a.dst = v.pops[v.cur ^ 1];
     a.params = v.params;
     a.items = items;
-    a.step = v.step;
-    a.step_add = step_add;
+    a.step = v.step + v.cur;
+    a.step_next = v.step + (v.cur ^ 1);
     a.key0 = (uint32_t)(v.seed & 0xFFFFFFFFu);
     a.key1 = (uint32_t)(v.seed >> 32);
     return a;
@@ -78,6 +88,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs g)
     using T = typename Codec<S>::T;
     using VT = typename Vec<T, V>::type;
     constexpr int TH = kThreads / TX;
+    advance_counter(g, 1);
     const StepItem it = g.items[blockIdx.x];
     if (it.lattice < 0) return;
     const LatticeParams &P = g.params[it.lattice];
@@ -92,7 +103,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs g)
     const T *__restrict__ src = (const T *)g.src + P.base;
     T *__restrict__ dst = (T *)g.dst + P.base;
     const uint32_t plane = (uint32_t)P.plane;
-    const uint32_t t = *g.step + g.step_add;
+    const uint32_t t = *g.step;
     const uint32_t ym = (y == 0) ? ny - 1 : y - 1;
     const uint32_t yp = (y == ny - 1) ? 0 : y + 1;
     const uint32_t rc = (uint32_t)y * px, rm = ym * px, rp = yp * px;
@@ -196,9 +207,9 @@ bool step_tile_supported(int tx, int v)
 }
 
 hipError_t launch_step(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
-                       int sites, uint32_t step_add, bool nontemporal, bool noise, hipStream_t s)
+                       int sites, bool nontemporal, bool noise, hipStream_t s)
 {
-    const StepArgs a = step_args(v, items, step_add);
+    const StepArgs a = step_args(v, items);
 #define FLB_SEL(S_)                                                                              \
     if (v.storage == S_) {                                                                       \
         if (nontemporal)                                                                         \
@@ -288,7 +299,7 @@ __device__ __forceinline__ void step2_tile(const StepArgs &g, StepItem it, const
     const T *__restrict__ src = (const T *)g.src + P.base;
     T *__restrict__ dst = (T *)g.dst + P.base;
     const uint32_t plane = (uint32_t)P.plane, px = (uint32_t)P.px;
-    const uint32_t t = *g.step + g.step_add;
+    const uint32_t t = *g.step;
     const int tid = threadIdx.x;
 
     // An interior tile: the region and every site it pulls from lie inside
@@ -432,6 +443,7 @@ __global__ __launch_bounds__(kStep2Threads) void step2_kernel(StepArgs g)
     using T = typename Codec<S>::T;
     using SH = Fixed<TW, TH>;
     __shared__ T mid[8 * SH::rn];
+    advance_counter(g, 2);
     const StepItem it = g.items[blockIdx.x];
     if (it.lattice < 0) return;
     step2_tile<S, NT, NOISE>(g, it, SH{}, mid);
@@ -448,6 +460,7 @@ __global__ __launch_bounds__(kStep2Threads) void step2_mixed_kernel(StepArgs g)
     using T = typename Codec<S>::T;
     constexpr int RN = Fixed<32, 32>::rn > Fixed<64, 16>::rn ? Fixed<32, 32>::rn : Fixed<64, 16>::rn;
     __shared__ T mid[8 * RN];
+    advance_counter(g, 2);
     StepItem it = g.items[blockIdx.x];
     if (it.lattice < 0) return;
     const bool square = (it.tile & kStep2Square) != 0;
@@ -475,9 +488,9 @@ static hipError_t launch_step2_tiles(const StepArgs &a, int nitems, int tw, hipS
 bool step2_tile_supported(int tw) { return tw == 32 || tw == 64 || tw == 128; }
 
 hipError_t launch_step2(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
-                        uint32_t step_add, bool nontemporal, bool noise, hipStream_t s)
+                        bool nontemporal, bool noise, hipStream_t s)
 {
-    const StepArgs a = step_args(v, items, step_add);
+    const StepArgs a = step_args(v, items);
 #define FLB_SEL(S_)                                                                              \
     if (v.storage == S_) {                                                                       \
         if (nontemporal)                                                                         \
@@ -544,6 +557,7 @@ __attribute__((amdgpu_waves_per_eu(S == kF32 ? 6 : 4))) void step3_kernel(StepAr
     static_assert(N1 <= kStep2Threads && N2 <= kStep2Threads, "tile shape");
     constexpr int LG = TW == 32 ? 5 : TW == 64 ? 6 : 7;
     __shared__ T mid[8 * RN];  // planes 1..8 of the region
+    advance_counter(g, 3);
     const StepItem it = g.items[blockIdx.x];
     if (it.lattice < 0) return;
     const LatticeParams &P = g.params[it.lattice];
@@ -553,7 +567,7 @@ __attribute__((amdgpu_waves_per_eu(S == kF32 ? 6 : 4))) void step3_kernel(StepAr
     const T *__restrict__ src = (const T *)g.src + P.base;
     T *__restrict__ dst = (T *)g.dst + P.base;
     const uint32_t plane = (uint32_t)P.plane, px = (uint32_t)P.px;
-    const uint32_t t = *g.step + g.step_add;
+    const uint32_t t = *g.step;
     const int tid = threadIdx.x;
     const bool has1 = tid < N1, has2 = tid >= kStep2Threads - N2;
     const bool interior = x0 >= 3 && y0 >= 3 && x0 + TW + 3 <= nx && y0 + TH + 3 <= ny;
@@ -737,9 +751,9 @@ static hipError_t launch_step3_tiles(const StepArgs &a, int nitems, int tw, hipS
 }
 
 hipError_t launch_step3(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
-                        uint32_t step_add, bool nontemporal, bool noise, hipStream_t s)
+                        bool nontemporal, bool noise, hipStream_t s)
 {
-    const StepArgs a = step_args(v, items, step_add);
+    const StepArgs a = step_args(v, items);
 #define FLB_SEL(S_)                                                                              \
     if (v.storage == S_) {                                                                       \
         if (nontemporal)                                                                         \
@@ -807,6 +821,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void march_kernel(StepArgs g, int rows)
     using E = typename Codec<S>::T;
     constexpr int W = march_cols(T);
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    advance_counter(g, T);
     const StepItem it = g.items[blockIdx.x * kMarchWaves + wv];
     if (it.lattice < 0) return;
     const LatticeParams &P = g.params[it.lattice];
@@ -816,7 +831,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void march_kernel(StepArgs g, int rows)
     const int seg = it.tile / nstrips, strip = it.tile - seg * nstrips;
     const int y0 = seg * rows, h = min(rows, ny - y0);
     const int lane = (int)threadIdx.x & 63;
-    const uint32_t t = *g.step + g.step_add;
+    const uint32_t t = *g.step;
 
     int x = strip * W - (T - 1) + lane;
     const bool own = lane >= T - 1 && lane < 64 - (T - 1) && x < nx;
@@ -925,10 +940,10 @@ static hipError_t launch_march_s(const StepArgs &a, int nblocks, int steps, int 
 }
 
 hipError_t launch_march(const DeviceView &v, const StepItem *items, int nitems, int steps,
-                        int rows, uint32_t step_add, bool noise, hipStream_t s)
+                        int rows, bool noise, hipStream_t s)
 {
     if (rows < 1 || nitems % kMarchWaves) return hipErrorInvalidValue;
-    const StepArgs a = step_args(v, items, step_add);
+    const StepArgs a = step_args(v, items);
     const int nb = nitems / kMarchWaves;
     if (v.storage == kF32) return launch_march_s<kF32>(a, nb, steps, rows, noise, s);
     if (v.storage == kBF16) return launch_march_s<kBF16>(a, nb, steps, rows, noise, s);
@@ -956,6 +971,7 @@ __global__ __launch_bounds__(kPatchThreads) void patch_kernel(StepArgs g, int tw
 {
     using E = typename Codec<S>::T;
     extern __shared__ float buf[];  // two buffers of nine planes of the region
+    advance_counter(g, steps);
     const StepItem it = g.items[blockIdx.x];
     if (it.lattice < 0) return;
     const LatticeParams &P = g.params[it.lattice];
@@ -965,7 +981,7 @@ __global__ __launch_bounds__(kPatchThreads) void patch_kernel(StepArgs g, int tw
     const int halo = steps - 1, w0 = tw + 2 * halo, h0 = th + 2 * halo, RN = w0 * h0;
     const E *__restrict__ src = (const E *)g.src + P.base;
     E *__restrict__ dst = (E *)g.dst + P.base;
-    const uint32_t t = *g.step + g.step_add;
+    const uint32_t t = *g.step;
     for (int s = 0; s < steps; ++s) {
         const int w = w0 - 2 * s, n = w * (h0 - 2 * s);
         const float rw = 1.0f / (float)w;
@@ -1031,9 +1047,9 @@ int patch_lds_bytes(int tw, int th, int steps)
 }
 
 hipError_t launch_patch(const DeviceView &v, const StepItem *items, int nitems, int tw, int th,
-                        int steps, uint32_t step_add, bool noise, hipStream_t s)
+                        int steps, bool noise, hipStream_t s)
 {
-    const StepArgs a = step_args(v, items, step_add);
+    const StepArgs a = step_args(v, items);
     const dim3 grid(nitems), block(kPatchThreads);
     const int lds = patch_lds_bytes(tw, th, steps);
     if (steps < 1 || (tw + 2 * steps) * (th + 2 * steps) > 8192) return hipErrorInvalidValue;
@@ -1053,7 +1069,7 @@ hipError_t launch_patch(const DeviceView &v, const StepItem *items, int nitems, 
 }
 
 // ---------------------------------------------------------------------
-// Step counter
+// Step counter, after the kernels that step in place
 // ---------------------------------------------------------------------
 __global__ void advance_step_kernel(uint32_t *step, uint32_t n)
 {

@@ -601,3 +601,30 @@ def test_library_grouping_equals_one_step_launches(flb, storage, sides, theta):
         b.step(n)
     for i in range(len(sides)):
         assert np.array_equal(a.get_populations(i), b.get_populations(i)), i
+
+
+@pytest.mark.parametrize("nx,ny", [(32, 32), (256, 256), (300, 128), (1024, 768)])
+@pytest.mark.parametrize("n", [2, 6, 10])
+def test_replays_of_captured_steps(flb, nx, ny, n):
+    """A caller's graph of an even number of steps advances state and step
+    counter as plain calls do at each replay, for every grouping of the steps
+    into launches."""
+    import torch
+    note("captured steps", nx, ny, n)
+    g = flb.Lattice(nx, ny, TAU_C1, 1e-3, seed=4)
+    ref = flb.Lattice(nx, ny, TAU_C1, 1e-3, seed=4)
+    s = torch.cuda.Stream()
+    g.set_stream(s)
+    for h in (g, ref):
+        h.thermalize()
+        h.step(n)
+        h.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        g.step(n)
+    for replay in range(3):
+        with torch.cuda.stream(s):
+            graph.replay()
+        ref.step(n)
+        assert np.array_equal(g.get_populations(), ref.get_populations()), replay
+        torch.ones(1000, device="cuda").sum().item()
