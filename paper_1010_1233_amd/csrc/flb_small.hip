@@ -37,19 +37,53 @@ struct SmallArgs {
     uint32_t key0, key1;
 };
 
-// Half spectra of NF real fields [f][ny][nx] along their rows:
+// Division of a task's index x by a count d of the lattice, by a multiply
+// whose factor is made once (the compiler's division is some 25 instructions
+// a task, of about 350; a sample with moments of 512 lattices of 20^2 9.9 and
+// 8.9 us).  Exact where x d < 2^16: a lattice of V <= 1024 sites
+// and sides n <= 64 has at most 6 (V / 4 + n) tasks of d <= n / 2 + 1, and
+// 1024 sites of d <= 64.
+struct SmallDiv {
+    uint32_t d, m;
+    __device__ __forceinline__ explicit SmallDiv(int n)
+        : d((uint32_t)n), m((65535u + (uint32_t)n) / (uint32_t)n)
+    {
+    }
+    __device__ __forceinline__ int div(int x, int &rem) const
+    {
+        const uint32_t q = __umul24((uint32_t)x, m) >> 16;
+        rem = (int)((uint32_t)x - __umul24(q, d));
+        return (int)q;
+    }
+};
+struct SmallDivs {
+    SmallDiv nx, ny, nkx, px, py;  // px, py: tasks per row and per column
+    __device__ __forceinline__ SmallDivs(int x, int y, int k)
+        : nx(x), ny(y), nkx(k), px(direct_tasks(x)), py(direct_tasks(y))
+    {
+    }
+};
+
+// Places from one row of a field to the next: odd, as a wave's tasks read
+// several rows at the same column (32 columns: rows two apart would share
+// their banks; a sample at 32^2 8.5 us without the odd place, 6.7 with it).
+__host__ __device__ inline int small_row(int nx) { return nx | 1; }
+
+// Half spectra of NF real fields [f][ny][small_row(nx)] along their rows:
 // out[(f ny + y) nkx + k], k = 0 .. nx/2; roots[m] = exp(-2 pi i m / nx).
 // A task is a pass over one row of two fields, which share the roots.
 template <int NF>
-__device__ __forceinline__ void small_rows(const float *fld, int V, float2 *out,
-                                           const float2 *roots, int nx, int ny, int nkx)
+__device__ __forceinline__ void small_rows(const float *fld, float2 *out, const float2 *roots,
+                                           int nx, int ny, int nkx, const SmallDivs &by)
 {
     constexpr int G = 2, NG = (NF + G - 1) / G;
-    const int per = direct_tasks(nx), nt = per * ny;
-    for (int task = (int)threadIdx.x; task < NG * nt; task += (int)blockDim.x) {
-        const int grp = task / nt, r = task - grp * nt, y = r / per, k = r - y * per;
+    const int px = small_row(nx), V = px * ny;
+    const int nt = NG * direct_tasks(nx) * ny;
+    for (int task = (int)threadIdx.x; task < nt; task += (int)blockDim.x) {
+        int y, k;
+        const int grp = by.ny.div(by.px.div(task, k), y);
         const int f0 = grp * G, f1 = min(f0 + 1, NF - 1);  // (the last field again, not stored)
-        const float *row[G] = {fld + f0 * V + y * nx, fld + f1 * V + y * nx};
+        const float *row[G] = {fld + f0 * V + y * px, fld + f1 * V + y * px};
         float c[G][2], s[G][2];
         direct_sums<G>(nx, k, roots, [&](int f, int j) { return row[f][j]; }, c, s);
 #pragma unroll
@@ -67,11 +101,12 @@ __device__ __forceinline__ void small_rows(const float *fld, int V, float2 *out,
 // task is a pass over one column of one field.
 template <int NF>
 __device__ __forceinline__ void small_cols(const float2 *in, float2 *out, const float2 *roots,
-                                           int ny, int nkx)
+                                           int ny, int nkx, const SmallDivs &by)
 {
-    const int np = direct_tasks(ny) * nkx;
-    for (int task = (int)threadIdx.x; task < NF * np; task += (int)blockDim.x) {
-        const int f = task / np, r = task - f * np, ky = r / nkx, kx = r - ky * nkx;
+    const int nt = NF * direct_tasks(ny) * nkx;
+    for (int task = (int)threadIdx.x; task < nt; task += (int)blockDim.x) {
+        int kx, ky;
+        const int f = by.py.div(by.nkx.div(task, kx), ky);
         const float2 *col = in + f * ny * nkx + kx;
         float2 *o = out + f * ny * nkx + kx;
         float2 c[1][2], s[1][2];
@@ -143,11 +178,10 @@ __device__ __forceinline__ void small_sum5(double (&v)[5], double (*red)[16], do
 // populations come from.
 struct SmallSite {
     int x, y, src[9];
-    __device__ __forceinline__ SmallSite(int e, int nx, int ny)
+    __device__ __forceinline__ SmallSite(int e, int nx, int ny, const SmallDivs &by)
     {
         const int V = nx * ny;
-        y = e / nx;
-        x = e - y * nx;
+        y = by.nx.div(e, x);
         const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1, rc = y * nx;
         const int rm = (y == 0 ? ny - 1 : y - 1) * nx, rp = (y == ny - 1 ? 0 : y + 1) * nx;
         src[0] = e;
@@ -184,7 +218,7 @@ struct SmallLds {
 __host__ __device__ inline int small_even(int floats) { return (floats + 1) / 2 * 2; }
 __host__ __device__ inline int small_set(int nf, int nx, int ny)
 {
-    const int a = nf * nx * ny, b = 2 * nf * ny * (nx / 2 + 1);
+    const int a = nf * small_row(nx) * ny, b = 2 * nf * ny * (nx / 2 + 1);
     return small_even(a > b ? a : b);
 }
 // (the conservation sums' reduction uses the row spectra's place: 80 doubles)
@@ -198,14 +232,14 @@ __host__ __device__ inline int small_spec(int nf, int nx, int ny)
 // cons: also its conservation sums.
 template <int S, bool MOM>
 __device__ __forceinline__ void small_sample(const SmallArgs &g, const LatticeParams &P,
-                                             const SmallLds &L, bool cons)
+                                             const SmallLds &L, const SmallDivs &by, bool cons)
 {
     using T = typename Codec<S>::T;
     const int nx = P.nx, ny = P.ny, nkx = P.nkx, V = nx * ny, e = fresh_thread();
     float *fld = L.fld, *mom = L.mom;
     double sums[5] = {0, 0, 0, 0, 0};
     if (e < V) {
-        const SmallSite at(e, nx, ny);
+        const SmallSite at(e, nx, ny, by);
         float d[9];
 #pragma unroll
         for (int q = 0; q < 9; ++q) d[q] = Codec<S>::decode((T)L.st[at.src[q]], P, q);
@@ -213,16 +247,17 @@ __device__ __forceinline__ void small_sample(const SmallArgs &g, const LatticePa
         const float jx = (d[1] - d[3]) + (d[5] - d[7]) - (d[6] - d[8]);
         const float jy = (d[2] - d[4]) + (d[5] - d[7]) + (d[6] - d[8]);
         const float ir = __builtin_amdgcn_rcpf(P.rho0 + r);
-        fld[e] = r;
-        fld[V + e] = jx - P.rho0 * P.u0x;
-        fld[2 * V + e] = jy - P.rho0 * P.u0y;
-        fld[3 * V + e] = fmaf(jx, ir, -P.u0x);
-        fld[4 * V + e] = fmaf(jy, ir, -P.u0y);
+        const int pad = small_row(nx) - nx, F = V + ny * pad, o = e + at.y * pad;
+        fld[o] = r;
+        fld[F + o] = jx - P.rho0 * P.u0x;
+        fld[2 * F + o] = jy - P.rho0 * P.u0y;
+        fld[3 * F + o] = fmaf(jx, ir, -P.u0x);
+        fld[4 * F + o] = fmaf(jy, ir, -P.u0y);
         if constexpr (MOM) {
             float M[6];
             moments_of(d, M);
 #pragma unroll
-            for (int q = 0; q < 6; ++q) mom[q * V + e] = M[q];
+            for (int q = 0; q < 6; ++q) mom[q * F + o] = M[q];
         }
         const double Jx = jx, Jy = jy;
         sums[0] = r;
@@ -240,16 +275,16 @@ __device__ __forceinline__ void small_sample(const SmallArgs &g, const LatticePa
     const int64_t kstride = (int64_t)ny * P.kxp;
     // the spectra of a set take the place of its fields
     float2 *z = reinterpret_cast<float2 *>(fld);
-    small_rows<kFields>(fld, V, L.spec, L.rx, nx, ny, nkx);
+    small_rows<kFields>(fld, L.spec, L.rx, nx, ny, nkx, by);
     __syncthreads();
-    small_cols<kFields>(L.spec, z, L.ry, ny, nkx);
+    small_cols<kFields>(L.spec, z, L.ry, ny, nkx, by);
     __syncthreads();
     small_add<kFields>(z, ny, nkx, L.acc, acc, kstride);
     if constexpr (MOM) {
         z = reinterpret_cast<float2 *>(mom);
-        small_rows<kMomentFields>(mom, V, L.spec, L.rx, nx, ny, nkx);
+        small_rows<kMomentFields>(mom, L.spec, L.rx, nx, ny, nkx, by);
         __syncthreads();
-        small_cols<kMomentFields>(L.spec, z, L.ry, ny, nkx);
+        small_cols<kMomentFields>(L.spec, z, L.ry, ny, nkx, by);
         __syncthreads();
         small_add<kMomentFields>(z, ny, nkx, L.acc, acc, kstride);
     }
@@ -275,6 +310,7 @@ __global__ __launch_bounds__(kSmallSites) void small_kernel(SmallArgs g)
     L.ry = nx == ny ? L.rx : L.rx + nx;
     L.acc = g.keep_sums ? reinterpret_cast<double *>(L.ry + ny) : nullptr;
     float *st = L.st;
+    const SmallDivs by(nx, ny, P.nkx);
     const int64_t kstride = (int64_t)ny * P.kxp;
     const bool sampled = g.sample_first || g.every;
     {
@@ -298,11 +334,11 @@ __global__ __launch_bounds__(kSmallSites) void small_kernel(SmallArgs g)
         // steps to the next sample after this one
         const uint32_t next = g.every ? g.every - t % g.every : 0xFFFFFFFFu;
         if (sampled && due)
-            small_sample<S, MOM>(g, P, L, left < next);
+            small_sample<S, MOM>(g, P, L, by, left < next);
         if (!left) break;
         const uint32_t n = min(left, next);
         const int e = fresh_thread();
-        const SmallSite at(e, nx, ny);
+        const SmallSite at(e, nx, ny, by);
         for (uint32_t k = 0; k < n; ++k) {
             float d[9];
             if (e < V)
