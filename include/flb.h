@@ -205,9 +205,7 @@ int flb_accumulate_correlators(flb_t *h);
 /* Copies lattice `lattice`'s raw FP64 sums to out[kind][ky][kx] (host), with
  * kind < flb_num_kinds(h), ky < ny, kx < nx/2+1, and writes the number of
  * samples taken to *nsamples (may be NULL).  n_doubles must be at least
- * flb_num_kinds(h)*ny*(nx/2+1), else FLB_ESIZE.  Synchronises, and takes
- * host memory for one more copy of the lattice's sums (the device keeps them
- * in another order).  The library adds the FP64 products of 32 samples in
+ * flb_num_kinds(h)*ny*(nx/2+1), else FLB_ESIZE.  Synchronises.  The library adds the FP64 products of 32 samples in
  * one pass over the sums and keeps the FP32 spectra of up to 32 samples
  * until then (32 spectrum-sized buffers of 5 x ny x (nx/2+16) complex
  * values per lattice); a read adds those first, so the sums are those of
@@ -253,8 +251,8 @@ int flb_get_populations(flb_t *h, int lattice, double *out, size_t n);
 
 /* For callers that cannot allocate device memory (loops that read the
  * state often and may not call hipMalloc, harnesses that forbid device
- * allocation): flb_get_populations without its per-call staging
- * allocation.  Same arguments, output and errors, plus FLB_ESIZE when
+ * allocation): flb_get_populations without the pinned staging
+ * slots it may allocate.  Same arguments, output and errors, plus FLB_ESIZE when
  * 9*nx*ny exceeds 8388608 values (2^23).  The values pass through a 64 MiB
  * staging array in the library's code object, one per GPU, held until the
  * process ends; the call allocates nothing.  Calls on one GPU share that
@@ -369,8 +367,8 @@ int flb_get_lattice_tiles(flb_t *h, int *tile_w);
 /* Chooses the step kernel's launch shape by timing every supported shape
  * (nsteps >= 1 steps each, HIP events on the handle's stream, in three
  * round-robin passes of which each shape keeps its fastest) on this
- * handle's own lattices, the time-blocked shapes included (per step), and
- * keeps the fastest.  For a batch whose fastest shape is time-blocked, the
+ * handle's own lattices, the time-blocked shapes and the library's own
+ * grouping of the steps included (per step), and keeps the fastest.  For a batch whose fastest shape is time-blocked, the
  * two-step tile is then chosen per size class (the lattices whose sides
  * round up to the same powers of two): each class takes the faster of
  * 32 x 32 and 64 x 16 tiles, timed on its own lattices' tiles (the one with
