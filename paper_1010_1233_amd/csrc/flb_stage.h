@@ -24,7 +24,11 @@ constexpr size_t kStageSlotDoubles = (size_t)1 << 18;  // 2 MiB a slot, two per 
 
 // Every open handle holds a reference; the slots (32 MiB, shared by all
 // handles, one transfer at a time) and the helper threads are made by the
-// first transfer that needs them and given back with the last reference.
+// first transfer that needs them and given back with the last reference.  A
+// transfer that finds them taken goes through two slots of its own (kept
+// likewise, for at most kStageExtra at a time): their holder may be waiting
+// for steps that its stream has still to run.
+constexpr int kStageExtra = 7;
 void stage_retain();
 void stage_release();
 

@@ -92,13 +92,44 @@ void work(Job &j, int seat)
     }
 }
 
+// Pinned slots of a transfer, and flags behind them.
+struct SlotSet {
+    double *slots = nullptr;
+    uint32_t *flags = nullptr;
+    uint32_t seq = 0;   // of the last transfer with flags; 0 is never one's
+    bool busy = false;  // (extra sets; guarded by the pool's mutex m)
+
+    // two slots for each of `workers` threads
+    hipError_t allocate(int workers)
+    {
+        void *mem = nullptr;
+        // portable: the transfers of every device go through the same slots;
+        // coherent: the flags are read while the kernel runs
+        const size_t bytes = 2 * (size_t)workers * kStageSlotDoubles * sizeof(double);
+        const hipError_t e = hipHostMalloc(&mem, bytes + kStageFlags * sizeof(uint32_t),
+                                           hipHostMallocPortable | hipHostMallocCoherent);
+        if (e != hipSuccess) return e;
+        slots = static_cast<double *>(mem);
+        flags = reinterpret_cast<uint32_t *>(static_cast<char *>(mem) + bytes);
+        memset(flags, 0, kStageFlags * sizeof(uint32_t));
+        seq = 0;
+        return hipSuccess;
+    }
+    void release()
+    {
+        if (slots) (void)hipHostFree(slots);
+        slots = nullptr;
+    }
+};
+
 // The helper threads and the slots.  (Never destroyed: helpers of handles
 // still open at the process's end sleep through it.)
 struct Pool {
-    std::mutex use;  // one transfer at a time; guards slots
-    double *slots = nullptr;
-    uint32_t *flags = nullptr;  // (behind the slots)
-    uint32_t seq = 0;           // of the last transfer with flags; 0 is never one's
+    std::mutex use;  // held by the transfer that has `set` and the helpers
+    SlotSet set;
+    // for transfers that find it taken: its holder may be waiting for steps
+    // still to run on its stream (two slots each, no helpers)
+    SlotSet extra[kStageExtra];
     std::mutex m;  // guards the rest
     std::condition_variable wake, done;
     std::vector<std::thread> threads;
@@ -131,6 +162,42 @@ Pool &pool()
     return *p;
 }
 
+// The slots of one transfer: the main set, an extra one, or whichever the
+// main set's holder gives back.
+struct SlotUse {
+    Pool &p;
+    std::unique_lock<std::mutex> lock;
+    bool mine;  // the main set
+    SlotSet &set;
+
+    explicit SlotUse(Pool &pool)
+        : p(pool), lock(p.use, std::try_to_lock), mine(lock.owns_lock()), set(pick())
+    {
+    }
+    ~SlotUse()
+    {
+        if (mine) return;
+        std::lock_guard<std::mutex> l(p.m);
+        set.busy = false;
+    }
+    SlotSet &pick()
+    {
+        if (!mine) {
+            {
+                std::lock_guard<std::mutex> l(p.m);
+                for (SlotSet &x : p.extra)
+                    if (!x.busy) {
+                        x.busy = true;
+                        return x;
+                    }
+            }
+            lock.lock();
+            mine = true;
+        }
+        return p.set;
+    }
+};
+
 // Waits for the flags of all blocks, at most 100 us (the stream may have
 // more work before the kernel): false if some are missing.
 bool all_done(const StageDone &done, size_t blocks)
@@ -151,19 +218,10 @@ hipError_t transfer(int device, hipStream_t s, double *host, size_t n, bool to_h
 {
     if (!n) return hipStreamSynchronize(s);
     Pool &p = pool();
-    std::lock_guard<std::mutex> use(p.use);
-    if (!p.slots) {
-        void *mem = nullptr;
-        // portable: the transfers of every device go through the same slots
-        const size_t bytes = 2 * kStageWorkers * kStageSlotDoubles * sizeof(double);
-        const hipError_t e =
-            hipHostMalloc(&mem, bytes + kStageFlags * sizeof(uint32_t), hipHostMallocPortable);
-        if (e != hipSuccess) return e;
-        p.slots = static_cast<double *>(mem);
-        p.flags = reinterpret_cast<uint32_t *>(static_cast<char *>(mem) + bytes);
-        memset(p.flags, 0, kStageFlags * sizeof(uint32_t));
-        p.seq = 0;
-    }
+    SlotUse use(p);
+    SlotSet &set = use.set;
+    if (!set.slots)
+        if (hipError_t e = set.allocate(use.mine ? kStageWorkers : 1); e != hipSuccess) return e;
     Job j;
     j.device = device;
     j.stream = s;
@@ -172,26 +230,27 @@ hipError_t transfer(int device, hipStream_t s, double *host, size_t n, bool to_h
     j.chunks = (n + kStageSlotDoubles - 1) / kStageSlotDoubles;
     j.to_host = to_host;
     j.kernel = &kernel;
-    j.slots = p.slots;
+    j.slots = set.slots;
     if (j.chunks == 1) {
         const size_t blocks = (n + kStageBlock - 1) / kStageBlock;
         const bool flags = to_host && blocks <= (size_t)kStageFlags;
-        if (!to_host) memcpy(p.slots, host, n * sizeof(double));
+        if (!to_host) memcpy(set.slots, host, n * sizeof(double));
         StageDone done{nullptr, 0};
         if (flags) {
-            done.flag = p.flags;
-            if (++p.seq == 0) p.seq = 1;
-            done.seq = p.seq;
+            done.flag = set.flags;
+            if (++set.seq == 0) set.seq = 1;
+            done.seq = set.seq;
         }
-        hipError_t e = kernel(p.slots, 0, n, done, s);
+        hipError_t e = kernel(set.slots, 0, n, done, s);
         if (e != hipSuccess) return e;
         if (!flags || !all_done(done, blocks))
             if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        if (to_host) memcpy(host, p.slots, n * sizeof(double));
+        if (to_host) memcpy(host, set.slots, n * sizeof(double));
         return hipSuccess;
     }
     // a helper for every two chunks past the caller's own two
-    const int helpers = (int)std::min<size_t>((j.chunks - 1) / 2, kStageWorkers - 1);
+    const int helpers =
+        use.mine ? (int)std::min<size_t>((j.chunks - 1) / 2, kStageWorkers - 1) : 0;
     if (helpers) {
         std::lock_guard<std::mutex> lock(p.m);
         try {
@@ -242,8 +301,8 @@ void stage_release()
         std::lock_guard<std::mutex> lock(p.m);
         p.stop = false;
     }
-    if (p.slots) (void)hipHostFree(p.slots);
-    p.slots = nullptr;
+    p.set.release();
+    for (SlotSet &x : p.extra) x.release();
 }
 
 hipError_t stage_out(int device, hipStream_t s, double *out, size_t n, const StageKernel &kernel)

@@ -101,3 +101,29 @@ def test_transfers_from_two_threads(flb):
     for x in t:
         x.join()
     assert not bad
+
+
+def test_reads_do_not_wait_for_other_handles(flb):
+    """A thread that reads a handle with steps still to run does not hold up
+    another handle's read."""
+    import time
+
+    import torch
+    print("reads beside a busy handle", flush=True)
+    busy = flb.Lattice(2048, 2048, TAU, 1e-4, seed=1)
+    idle = flb.Lattice(64, 64, TAU, 1e-4, seed=2)
+    s = torch.cuda.Stream()
+    busy.set_stream(s)
+    want = idle.get_populations()
+    busy.synchronize()
+    end = torch.cuda.Event()
+    with torch.cuda.stream(s):
+        busy.step(20000)  # about half a second
+        end.record()
+    t = threading.Thread(target=busy.get_populations)
+    t.start()
+    time.sleep(0.05)
+    got = idle.get_populations()
+    early = not end.query()
+    t.join()
+    assert early and np.array_equal(got, want)
