@@ -9,8 +9,10 @@
 //              state at time t (just after streaming) is
 //              f_i(x) = stored_i(x - v_i): every kernel that needs f(x)
 //              gathers, the step kernel streams by gathering ("pull").
-//   step     : one uint32 on the device, the time t of the next step, so
-//              that captured graphs replay with advancing noise counters.
+//   step     : a uint32 on the device for each population buffer: the time t
+//              of the next step of the state in it, written by the launch
+//              that fills the buffer (so a caller's captured steps replay
+//              with advancing noise counters).
 //   spec     : complex64 scratch for the correlator transforms, per lattice
 //              5 fields x ny x kxp in row order (the half spectra of the real
 //              fields after the row transforms; kxp is nkx = nx/2+1 rounded
