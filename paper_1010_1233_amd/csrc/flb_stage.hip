@@ -287,14 +287,16 @@ void stage_retain()
 void stage_release()
 {
     Pool &p = pool();
-    std::lock_guard<std::mutex> use(p.use);
     std::vector<std::thread> threads;
     {
+        // (not p.use: another handle's transfer may hold it for as long as its
+        // stream has steps to run)
         std::lock_guard<std::mutex> lock(p.m);
         if (--p.refs > 0) return;
         p.stop = true;
         threads.swap(p.threads);
     }
+    std::lock_guard<std::mutex> use(p.use);
     p.wake.notify_all();
     for (std::thread &t : threads) t.join();
     {
