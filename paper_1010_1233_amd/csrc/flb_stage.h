@@ -27,7 +27,8 @@ constexpr size_t kStageSlotDoubles = (size_t)1 << 18;  // 2 MiB a slot, two per 
 // first transfer that needs them and given back with the last reference.  A
 // transfer that finds them taken goes through two slots of its own (kept
 // likewise, for at most kStageExtra at a time): their holder may be waiting
-// for steps that its stream has still to run.
+// for steps that its stream has still to run.  Opening and closing a handle
+// waits for no transfer.
 constexpr int kStageExtra = 7;
 void stage_retain();
 void stage_release();

@@ -9,6 +9,7 @@
 #include <mutex>
 #include <system_error>
 #include <thread>
+#include <utility>
 #include <vector>
 
 namespace flbdev {
@@ -122,8 +123,7 @@ struct SlotSet {
     }
 };
 
-// The helper threads and the slots.  (Never destroyed: helpers of handles
-// still open at the process's end sleep through it.)
+// The helper threads and the slots of the handles that are open together.
 struct Pool {
     std::mutex use;  // held by the transfer that has `set` and the helpers
     SlotSet set;
@@ -135,7 +135,19 @@ struct Pool {
     std::vector<std::thread> threads;
     Job *job = nullptr;
     bool stop = false;
-    int refs = 0;
+
+    // No transfer is running: ends the helpers and gives the slots back.
+    void close()
+    {
+        {
+            std::lock_guard<std::mutex> lock(m);
+            stop = true;
+        }
+        wake.notify_all();
+        for (std::thread &t : threads) t.join();
+        set.release();
+        for (SlotSet &x : extra) x.release();
+    }
 
     void helper()
     {
@@ -156,10 +168,26 @@ struct Pool {
     }
 };
 
+// The pool of the open handles.  The last of them takes it along and closes it
+// on its own: a handle opened meanwhile gets another, so that no slot is given
+// back under a transfer.  (Never destroyed: helpers of handles still open at
+// the process's end sleep through it.)
+struct Open {
+    std::mutex m;  // guards the rest
+    int handles = 0;
+    Pool *pool = nullptr;
+};
+Open &open_handles()
+{
+    static Open *o = new Open();
+    return *o;
+}
+// Called for an open handle, whose pool stays for as long as it is open.
 Pool &pool()
 {
-    static Pool *p = new Pool();
-    return *p;
+    Open &o = open_handles();
+    std::lock_guard<std::mutex> lock(o.m);
+    return *o.pool;
 }
 
 // The slots of one transfer: the main set, an extra one, or whichever the
@@ -280,31 +308,23 @@ hipError_t transfer(int device, hipStream_t s, double *host, size_t n, bool to_h
 
 void stage_retain()
 {
-    std::lock_guard<std::mutex> lock(pool().m);
-    ++pool().refs;
+    Open &o = open_handles();
+    std::lock_guard<std::mutex> lock(o.m);
+    if (o.handles == 0) o.pool = new Pool();
+    ++o.handles;
 }
 
 void stage_release()
 {
-    Pool &p = pool();
-    std::vector<std::thread> threads;
+    Open &o = open_handles();
+    Pool *last = nullptr;
     {
-        // (not p.use: another handle's transfer may hold it for as long as its
-        // stream has steps to run)
-        std::lock_guard<std::mutex> lock(p.m);
-        if (--p.refs > 0) return;
-        p.stop = true;
-        threads.swap(p.threads);
+        std::lock_guard<std::mutex> lock(o.m);
+        if (--o.handles > 0) return;
+        std::swap(last, o.pool);
     }
-    std::lock_guard<std::mutex> use(p.use);
-    p.wake.notify_all();
-    for (std::thread &t : threads) t.join();
-    {
-        std::lock_guard<std::mutex> lock(p.m);
-        p.stop = false;
-    }
-    p.set.release();
-    for (SlotSet &x : p.extra) x.release();
+    last->close();
+    delete last;
 }
 
 hipError_t stage_out(int device, hipStream_t s, double *out, size_t n, const StageKernel &kernel)

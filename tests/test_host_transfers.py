@@ -38,7 +38,78 @@ def closing_does_not_wait(s):
     assert not reader.is_alive()
 
 
-CASES = [closing_does_not_wait]
+def last_close_beside_a_new_handle(s):
+    """A handle opened and read while the last one before it closes keeps its
+    slots (freed ones fault when touched)."""
+    def values(g):
+        return g.get_populations()
+
+    def read_new():
+        b = s.flb.Lattice(400, 400, TAU, 1e-4)  # several chunks
+        values(b)
+        done.append(b)
+
+    done = []
+    a = s.flb.Lattice(400, 400, TAU, 1e-4)
+    values(a)
+    s.hold("hipHostFree")
+    closer = _start(a.close)
+    assert s.held("hipHostFree")
+    s.hold("hipEventSynchronize")
+    reader = _start(read_new)
+    assert s.held("hipEventSynchronize")  # its first chunks are under way
+    s.release("hipHostFree")
+    closer.join(5)
+    assert not closer.is_alive()
+    s.release("hipEventSynchronize")
+    reader.join(5)
+    assert done
+    done.pop().close()
+    assert s.L.hs_pinned_now() == 0
+
+
+def many_handles_come_and_go(s):
+    """Threads that open, read and close handles of their own, some of several
+    chunks: nothing is left behind."""
+    bad = []
+
+    def work(i):
+        try:
+            for k in range(30):
+                side = 300 if (i + k) % 3 == 0 else 20
+                g = s.flb.Lattice(side, side, TAU, 1e-4)
+                g.get_populations()
+                g.close()
+        except BaseException as e:  # noqa: B902
+            bad.append(e)
+
+    threads = [_start(lambda i=i: work(i)) for i in range(6)]
+    for t in threads:
+        t.join(60)
+        assert not t.is_alive()
+    assert not bad
+    assert s.L.hs_pinned_now() == 0
+
+
+def more_transfers_than_slot_pairs(s):
+    """Eleven reads at once of handles with steps to run: the main slots, seven
+    pairs more, and three that wait for the main slots; all end."""
+    gs = [s.flb.Lattice(20, 20, TAU, 1e-4) for _ in range(11)]
+    s.hold("hipStreamSynchronize")
+    readers = [_start(g.get_populations) for g in gs]
+    assert s.held("hipStreamSynchronize", 8)
+    assert not s.held("hipStreamSynchronize", 9, 300)
+    s.release("hipStreamSynchronize")
+    for t in readers:
+        t.join(10)
+        assert not t.is_alive()
+    for g in gs:
+        g.close()
+    assert s.L.hs_pinned_now() == 0
+
+
+CASES = [closing_does_not_wait, last_close_beside_a_new_handle, many_handles_come_and_go,
+         more_transfers_than_slot_pairs]
 
 
 @pytest.mark.parametrize("case", [c.__name__ for c in CASES])
