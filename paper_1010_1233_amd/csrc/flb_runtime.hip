@@ -649,13 +649,13 @@ int build_small_items(flb_t *h)
 
 // The resident kernel: nsteps steps of lattices that are all small, the
 // samples inside (see launch_small).
-hipError_t launch_resident(flb_t *h, uint32_t nsteps, uint32_t every,
+hipError_t launch_resident(flb_t *h, uint32_t nsteps, uint32_t every, uint32_t to_sample,
                            bool sample_first, hipStream_t s)
 {
     const bool sampled = every || sample_first;
     const bool keep = h->small_keep && every && nsteps >= 2 * every;
     return launch_small(h->view(), h->d_small, h->n_small, h->small_threads,
-                        h->small_lds[sampled ? (keep ? 2 : 1) : 0], nsteps, every,
+                        h->small_lds[sampled ? (keep ? 2 : 1) : 0], nsteps, every, to_sample,
                         sample_first, keep, h->noise, h->moments, s);
 }
 
@@ -1095,7 +1095,7 @@ int setup_correlators(flb_t *h)
 int enqueue_sample(flb_t *h, hipStream_t s, hipEvent_t ev_read = nullptr)
 {
     const DeviceView v = h->view();
-    if (h->n_small) FLB_HIP(launch_resident(h, 0, 0, true, s));
+    if (h->n_small) FLB_HIP(launch_resident(h, 0, 0, 0, true, s));
     if (h->all_small()) {
         if (ev_read) FLB_HIP(hipEventRecord(ev_read, s));
         return FLB_OK;
@@ -1244,15 +1244,16 @@ int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_sec
 constexpr int64_t kResidentSteps = 4096;
 
 // n steps of lattices that are all small, resident, with a due sample before
-// them and samples at the multiples of `every` (0: none); the device counter
-// is advanced.
+// them and samples where h->t comes to a multiple of `every` (0: none); the
+// device counter is advanced.
 int enqueue_resident(flb_t *h, int64_t n, int every, hipStream_t s)
 {
     for (int64_t k = 0; k < n;) {
         const int64_t m = std::min(n - k, kResidentSteps);
         hipEvent_t stop = nullptr;
         if (int rc = begin_timed(h, (int)m, s, stop)) return rc;
-        FLB_HIP(launch_resident(h, (uint32_t)m, (uint32_t)every, h->due, s));
+        const uint32_t to_sample = every ? (uint32_t)(every - (h->t + k) % every) : 0;
+        FLB_HIP(launch_resident(h, (uint32_t)m, (uint32_t)every, to_sample, h->due, s));
         if (stop) FLB_HIP(hipEventRecord(stop, s));
         h->due = false;
         FLB_HIP(launch_advance_step(h->d_step + h->cur, (uint32_t)m, s));

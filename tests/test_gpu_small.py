@@ -104,3 +104,35 @@ def test_more_lattices_than_compute_units(flb):
         g.run(8200, 41)
     assert np.array_equal(a.get_populations(599), b.get_populations(0))
     assert np.array_equal(a.read_correlators(599)[0], b.read_correlators(0)[0])
+
+
+@pytest.mark.parametrize("nx,ny", [(20, 20), (33, 32)])
+@pytest.mark.parametrize("n", [4, 6])
+def test_samples_follow_the_callers_time_after_replays(flb, nx, ny, n):
+    """Replays of captured steps advance the noise counter, not the handle's
+    time: a run's samples are those of its own time, in count and in place."""
+    import torch
+    print("samples after replays", nx, ny, n, flush=True)
+    got = []
+    for one_step in (False, True):
+        g = _make(flb, nx, ny)
+        if one_step:
+            g.set_time_blocking(1, 64)  # the general step kernels
+        s = torch.cuda.Stream()
+        g.set_stream(s)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            g.step(n)
+        with torch.cuda.stream(s):
+            for _ in range(3):
+                graph.replay()
+        assert g.t == n
+        counts = []
+        for steps, every in ((2, 10), (8, 10), (7, 7), (23, 5)):
+            g.run(steps, every)
+            counts.append(g.read_correlators()[1])
+        assert counts == [(n + 2) // 10, 1, 1 + (n + 17) // 7 - (n + 10) // 7,
+                          1 + (n + 17) // 7 - (n + 10) // 7 + (n + 40) // 5 - (n + 17) // 5]
+        got.append((g.get_populations(), *g.read_correlators(), g.sample_conservation()))
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
