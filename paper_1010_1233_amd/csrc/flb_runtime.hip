@@ -116,6 +116,8 @@ struct flb {
     StepItem *d_patch = nullptr;
     StepItem *d_march[2] = {nullptr, nullptr};
     int n_march[2] = {0, 0}, march_rows[2] = {0, 0};
+    // steps of this handle were captured into a caller's graph (keeps_parity)
+    bool captured = false;
     int64_t t = 0;
 
     // correlators
@@ -1180,6 +1182,17 @@ bool capturing(hipStream_t s)
     return st != hipStreamCaptureStatusNone;
 }
 
+// Whether n steps must flip the buffers as often as n one-step launches, up to
+// pairs.  A graph of captured steps reads the buffer that held the state when
+// it was captured: it can be replayed as long as an even number of steps, taken
+// by any calls in the capture and by any between replays, leaves the state in
+// that buffer.  So from a handle's first capture on, whatever the grouping.
+bool keeps_parity(flb_t *h, hipStream_t s)
+{
+    if (!h->captured && h->own_grouping() && capturing(s)) h->captured = true;
+    return h->captured && h->own_grouping();
+}
+
 // n steps from the device counter's value.  launch_plan says how the steps
 // are grouped. When wait_before_second is given, the second launch (the first
 // to write the buffer that held the state at the start) waits for it.
@@ -1197,10 +1210,11 @@ int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_sec
         h->cur ^= 1;
         return FLB_OK;
     };
+    auto patch_launches = [&](int64_t n) -> int64_t {
+        return h->patch_steps && n > 1 ? (n + h->patch_steps - 1) / h->patch_steps : 0;
+    };
     auto enqueue = [&](int64_t n) -> int {
-        if (h->patch_steps && n > 1) {
-            // launches of (nearly) equal length
-            const int64_t m = (n + h->patch_steps - 1) / h->patch_steps;
+        if (const int64_t m = patch_launches(n)) {  // launches of (nearly) equal length
             for (int64_t i = 0; i < m; ++i) {
                 const int steps = (int)((n * (i + 1)) / m - (n * i) / m);
                 if (int rc = before_launch(steps)) return rc;
@@ -1231,11 +1245,16 @@ int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_sec
             }
         return FLB_OK;
     };
-    // A caller's graph of an even number of steps can be replayed: it leaves
-    // the state in the buffer it found it in, whatever the grouping.
-    if (n > 0 && n % 2 == 0 && h->own_grouping() && capturing(s)) {
-        if (int rc = enqueue(n / 2)) return rc;
-        return enqueue(n / 2);
+    if (n > 1 && keeps_parity(h, s)) {
+        int64_t count = patch_launches(n);
+        if (!count)
+            for (int64_t of : launch_plan(h, n).of) count += of;
+        if ((count - n) % 2 != 0) {  // an odd step alone, the rest in equal halves
+            if (n % 2)
+                if (int rc = enqueue(1)) return rc;
+            if (int rc = enqueue(n / 2)) return rc;
+            return enqueue(n / 2);
+        }
     }
     return enqueue(n);
 }
@@ -1278,9 +1297,14 @@ int settle_due(flb_t *h)
 int enqueue_steps_overlapped(flb_t *h, int64_t n)
 {
     const hipStream_t s = h->stream;
-    if (n >= kResidentMin && h->own_grouping() && h->all_small()) return enqueue_resident(h, n, 0, s);
-    if (!h->due || n <= 0) return enqueue_steps(h, n, s);
     int rc;
+    if (n >= kResidentMin && h->own_grouping() && h->all_small()) {
+        // (in place: an odd step goes from buffer to buffer)
+        const int64_t odd = keeps_parity(h, s) ? n % 2 : 0;
+        if ((rc = enqueue_resident(h, n - odd, 0, s))) return rc;
+        return enqueue_steps(h, odd, s);
+    }
+    if (!h->due || n <= 0) return enqueue_steps(h, n, s);
     if (h->total_sites < kOverlapSites) {
         if ((rc = settle_due(h))) return rc;
         return enqueue_steps(h, n, s);
@@ -1626,16 +1650,18 @@ int flb_run(flb_t *h, int64_t nsteps, int sample_every)
     rc = setup_correlators(h);
     if (rc) return rc;
     if (h->own_grouping() && h->all_small()) {
-        // steps and samples resident (the last sample included)
-        const int64_t samples = (h->t + nsteps) / sample_every - h->t / sample_every;
+        // steps and samples resident (the last sample included), but for a step
+        // that has to go from buffer to buffer, which is left to the loop below
+        const int64_t n = keeps_parity(h, h->stream) ? nsteps - nsteps % 2 : nsteps;
+        const int64_t samples = (h->t + n) / sample_every - h->t / sample_every;
         const bool timing = h->timing;
         h->timing = false;
-        rc = enqueue_resident(h, nsteps, sample_every, h->stream);
+        rc = enqueue_resident(h, n, sample_every, h->stream);
         h->timing = timing;
         if (rc) return rc;
-        h->t += nsteps;
+        h->t += n;
         h->nsamples += samples;
-        return FLB_OK;
+        nsteps -= n;
     }
     // (plain launches: a captured graph per period was slower at every size,
     // 256^2 73 against 60 us a period, 4096^2 1449 against 1406)

@@ -628,3 +628,35 @@ def test_replays_of_captured_steps(flb, nx, ny, n):
         ref.step(n)
         assert np.array_equal(g.get_populations(), ref.get_populations()), replay
         torch.ones(1000, device="cuda").sum().item()
+
+
+@pytest.mark.parametrize("nx,ny", [(32, 32), (256, 256), (700, 500), (2048, 2048)])
+@pytest.mark.parametrize("calls", [(3, 5), (1, 7), (5, 1), (1, 2, 3, 4)])
+def test_replays_of_several_captured_calls(flb, nx, ny, calls):
+    """A caller's graph of several calls, an even number of steps in all, with
+    plain calls of as many between its replays."""
+    import torch
+    note("captured calls", nx, ny, calls)
+    g = flb.Lattice(nx, ny, TAU_C1, 1e-3, seed=4)
+    ref = flb.Lattice(nx, ny, TAU_C1, 1e-3, seed=4)
+    s = torch.cuda.Stream()
+    g.set_stream(s)
+    for h in (g, ref):
+        h.thermalize()
+        h.step(2)
+        h.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        for n in calls:
+            g.step(n)
+    for replay in range(3):
+        with torch.cuda.stream(s):
+            graph.replay()
+        for n in calls:
+            ref.step(n)
+        assert np.array_equal(g.get_populations(), ref.get_populations()), replay
+        torch.ones(1000, device="cuda").sum().item()
+        for h in (g, ref):
+            for n in (4, 3, 9):
+                h.step(n)
+        assert np.array_equal(g.get_populations(), ref.get_populations()), replay

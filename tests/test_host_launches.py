@@ -1,0 +1,69 @@
+"""Which launches the library's host side makes of a caller's calls (no GPU:
+see host_stub)."""
+import pytest
+
+import host_stub
+
+TAU = [1.0] * 9
+# one block's lattice, small tiles, tiles of three and two steps, marching waves
+SIDES = [(20, 20), (256, 256), (700, 500), (2048, 2048)]
+CALLS = (1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 20, 25, 37, 100)
+
+
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    return host_stub.build(tmp_path_factory.mktemp("stub"))
+
+
+def _flips(s, call):
+    """Buffer flips of a call's step launches, each reading what the one
+    before it wrote."""
+    s.take_log()
+    call()
+    steps = s.take_steps()
+    for a, b in zip(steps, steps[1:]):
+        assert a[3] == b[2] and a[2] == b[3]
+    return len(steps)
+
+
+def captured_steps_keep_the_buffers(s):
+    """Each call while a stream is captured, and each one after it (between
+    replays), leaves the state in the buffer that one-step launches would."""
+    for storage in ("f32", "bf16"):
+        for nx, ny in SIDES:
+            g = s.flb.Lattice(nx, ny, TAU, 1e-4, storage=storage)
+            stream = s.stream()
+            g.set_stream(stream)
+            g.reset_correlators()  # set up, which a capture does not allow
+            for capturing in (1, 0):
+                s.L.hs_capture(stream, capturing)
+                for n in CALLS:
+                    assert _flips(s, lambda: g.step(n)) % 2 == n % 2, (nx, storage, capturing, n)
+                    g.accumulate()
+                    assert _flips(s, lambda: g.step(n)) % 2 == n % 2, (nx, storage, capturing, n)
+                    for every in (1, 3, 4, 10):
+                        flips = _flips(s, lambda: g.run(n, every))
+                        assert flips % 2 == n % 2, (nx, storage, capturing, n, every)
+            g.close()
+
+
+def handles_never_captured_are_grouped_freely(s):
+    """Launches of steps from one buffer into the other (resident steps make
+    none)."""
+    for sides, n, launches in ((SIDES[0], 8, 0), (SIDES[0], 3, 1), (SIDES[1], 4, 1),
+                               (SIDES[2], 6, 2), (SIDES[3], 4, 1), (SIDES[3], 15, 3)):
+        g = s.flb.Lattice(*sides, TAU, 1e-4)
+        assert _flips(s, lambda: g.step(n)) == launches, (sides, n)
+        g.close()
+
+
+CASES = [captured_steps_keep_the_buffers, handles_never_captured_are_grouped_freely]
+
+
+@pytest.mark.parametrize("case", [c.__name__ for c in CASES])
+def test_launches(so, case):
+    host_stub.run_case(__file__, case, so)
+
+
+if __name__ == "__main__":
+    host_stub.main({c.__name__: c for c in CASES})
