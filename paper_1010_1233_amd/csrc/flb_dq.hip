@@ -1076,6 +1076,7 @@ struct flb_dq {
     DqParams *d_P = nullptr;
     float *pops[2] = {nullptr, nullptr};
     int cur = 0;
+    bool captured = false;  // steps were captured into a caller's graph
     int64_t t = 0;
     double *d_part = nullptr;   // reduction partials
     double *d_red = nullptr;    // reduction results (means, sums)
@@ -1149,8 +1150,14 @@ int enqueue_steps(flb_dq *h, int64_t n)
 {
     const uint32_t k0 = (uint32_t)(h->seed & 0xFFFFFFFFu), k1 = (uint32_t)(h->seed >> 32);
     if (h->D == 1) {
-        // launches of (nearly) equal numbers of steps
-        const int64_t launches = (n + kLineSteps - 1) / kLineSteps;
+        // Launches of (nearly) equal numbers of steps.  From a handle's first
+        // capture on their number is odd or even as n is: without noise (whose
+        // counters are arguments) a caller's graph of an even number of steps
+        // can be replayed, if these and the calls between replays leave the
+        // state in the buffer they found it in.
+        if (!h->captured && capturing(h->stream)) h->captured = true;
+        int64_t launches = (n + kLineSteps - 1) / kLineSteps;
+        if (h->captured && (launches - n) % 2 != 0) ++launches;
         const unsigned strips = (h->V + kLineCols - 1) / kLineCols;
         const dim3 grid((strips + kLineWaves - 1) / kLineWaves), block(64 * kLineWaves);
         auto kernel = h->noise ? dq_line_kernel<true> : dq_line_kernel<false>;

@@ -197,6 +197,8 @@ hipError_t launch_fill(double *p, size_t n, hipStream_t s);
 // ---------------------------------------------------------------------
 // Records the message returned by flb_last_error(); returns code.
 int set_error(int code, const std::string &msg);
+// Whether the stream is being captured into the caller's graph.
+bool capturing(hipStream_t s);
 
 // Line plans and their tables: the twiddle table first, then the chirp and
 // the transformed chirp kernel of every Bluestein length.

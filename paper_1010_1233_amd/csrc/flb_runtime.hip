@@ -46,6 +46,16 @@ int flbdev::set_error(int code, const std::string &msg)
     return code;
 }
 
+bool flbdev::capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 namespace {
 
 int fail(int code, const std::string &msg) { return set_error(code, msg); }
@@ -1169,17 +1179,6 @@ int begin_timed(flb_t *h, int steps, hipStream_t s, hipEvent_t &stop)
     FLB_HIP(hipEventRecord(ev.first, s));
     stop = ev.second;
     return FLB_OK;
-}
-
-// Whether the stream is being captured into the caller's graph.
-bool capturing(hipStream_t s)
-{
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return st != hipStreamCaptureStatusNone;
 }
 
 // Whether n steps must flip the buffers as often as n one-step launches, up to

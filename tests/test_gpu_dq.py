@@ -262,3 +262,35 @@ def test_line_launches_equal_one_step_launches(flb, n, steps):
                 g.step(1)
         got.append(g.get_populations())
     assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("calls", [(8,), (2,), (1, 7), (3, 4, 9)])
+def test_replays_of_captured_line_steps(flb, calls):
+    """D1Q3 without noise: a caller's graph of an even number of steps goes on
+    from its own result at each replay, with plain calls between."""
+    import torch
+    note("captured line steps", calls)
+    w = flb.dq_tables("D1Q3")[2]
+    f = w.reshape(-1, 1, 1, 1) * (1 + 0.1 * np.random.default_rng(2).normal(size=(3, 1, 1, 3001)))
+    hs = [flb.DqLattice("D1Q3", (3001,), [1.0, 1.0, 0.8], 0.0, u0=[0.03]) for _ in range(2)]
+    g, ref = hs
+    s = torch.cuda.Stream()
+    g.set_stream(s)
+    for h in hs:
+        h.set_populations(f)
+        h.step(1)
+        h.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        for n in calls:
+            g.step(n)
+    for replay in range(3):
+        with torch.cuda.stream(s):
+            graph.replay()
+        for n in calls:
+            ref.step(n)
+        assert np.array_equal(g.get_populations(), ref.get_populations()), replay
+        torch.ones(1000, device="cuda").sum().item()
+        for h in hs:
+            h.step(6)
+        assert np.array_equal(g.get_populations(), ref.get_populations()), replay

@@ -57,7 +57,24 @@ def handles_never_captured_are_grouped_freely(s):
         g.close()
 
 
-CASES = [captured_steps_keep_the_buffers, handles_never_captured_are_grouped_freely]
+def captured_line_steps_keep_the_buffers(s):
+    """The same for the lines that take several steps a launch."""
+    g = s.flb.DqLattice("D1Q3", (3000,), [1.0] * 3, 0.0)
+    stream = s.stream()
+    g.set_stream(stream)
+    assert _flips(s, lambda: g.step(16)) == 2
+    for capturing in (1, 0):
+        s.L.hs_capture(stream, capturing)
+        for n in CALLS:
+            s.take_log()
+            g.step(n)
+            steps = s.take_steps()
+            assert len(steps) % 2 == n % 2 and len(steps) <= n, (capturing, n)
+            assert sum(x[1] for x in steps) == n and all(1 <= x[1] <= 8 for x in steps)
+
+
+CASES = [captured_steps_keep_the_buffers, captured_line_steps_keep_the_buffers,
+         handles_never_captured_are_grouped_freely]
 
 
 @pytest.mark.parametrize("case", [c.__name__ for c in CASES])
