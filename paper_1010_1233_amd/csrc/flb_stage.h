@@ -21,12 +21,15 @@ namespace flbdev {
 
 constexpr int kStageWorkers = 8;  // threads of a transfer, the caller's among them
 constexpr size_t kStageSlotDoubles = (size_t)1 << 18;  // 2 MiB a slot, two per thread
+// Transfers of up to this many values go through a place of 512 KiB of their
+// own: a program that only reads small lattices pins no slots.
+constexpr size_t kStageSmallDoubles = (size_t)1 << 16;
 
-// Every open handle holds a reference; the slots (32 MiB, shared by all
+// Every open handle holds a reference; the slots (up to 32 MiB, shared by all
 // handles, one transfer at a time) and the helper threads are made by the
-// first transfer that needs them and given back with the last reference.  A
-// transfer that finds them taken goes through two slots of its own (kept
-// likewise, for at most kStageExtra at a time): their holder may be waiting
+// first transfer that needs so many and given back with the last reference.
+// A transfer that finds them taken goes through a place or two slots of its
+// own (kept likewise, for at most kStageExtra at a time): their holder may be waiting
 // for steps that its stream has still to run.  Opening and closing a handle
 // waits for no transfer.
 constexpr int kStageExtra = 7;

@@ -6,8 +6,8 @@
 #include <algorithm>
 #include <chrono>
 #include <condition_variable>
+#include <exception>
 #include <mutex>
-#include <system_error>
 #include <thread>
 #include <utility>
 #include <vector>
@@ -24,10 +24,10 @@ struct Job {
     size_t n, chunks;
     bool to_host;
     const StageKernel *kernel;
-    double *slots;
-    int seats = 0;   // threads that may still join (slots left)
-    int active = 0;  // threads at work (guarded by the pool's mutex)
-    int joined = 1;  // slot pairs handed out, the caller's first
+    double *const *pairs;  // two slots of each seat
+    int seats = 0;         // threads that may still join (pairs left)
+    int active = 0;        // threads at work (guarded by the pool's mutex)
+    int joined = 1;        // pairs handed out, the caller's first
     std::mutex m;    // guards next and failed, and orders the launches
     size_t next = 0;
     hipError_t failed = hipSuccess;
@@ -71,7 +71,7 @@ void work(Job &j, int seat)
     size_t chunk[2] = {j.chunks, j.chunks};  // in flight in each slot
     hipError_t e = hipSuccess;
     for (int q = 0; q < 2 && e == hipSuccess; ++q) {
-        slot[q] = j.slots + (size_t)(2 * seat + q) * kStageSlotDoubles;
+        slot[q] = j.pairs[seat] + q * kStageSlotDoubles;
         e = hipEventCreateWithFlags(&ev[q], hipEventDisableTiming);
         if (e == hipSuccess) e = take(j, slot[q], ev[q], chunk[q]);
     }
@@ -93,33 +93,52 @@ void work(Job &j, int seat)
     }
 }
 
-// Pinned slots of a transfer, and flags behind them.
+// Pinned memory of a transfer, made as transfers need it and kept from one to
+// the next (freeing some to make more would wait for the device): a small
+// place with flags, and pairs of slots.
 struct SlotSet {
-    double *slots = nullptr;
+    double *small = nullptr;  // kStageSmallDoubles
     uint32_t *flags = nullptr;
-    uint32_t seq = 0;   // of the last transfer with flags; 0 is never one's
+    uint32_t seq = 0;  // of the last transfer with flags; 0 is never one's
+    double *pairs[kStageWorkers] = {};
+    int npairs = 0;
     bool busy = false;  // (extra sets; guarded by the pool's mutex m)
 
-    // two slots for each of `workers` threads
-    hipError_t allocate(int workers)
+    // portable: the transfers of every device go through the same slots;
+    // coherent: the flags are read while the kernel runs
+    static hipError_t pinned(void **mem, size_t bytes)
     {
+        return hipHostMalloc(mem, bytes, hipHostMallocPortable | hipHostMallocCoherent);
+    }
+    hipError_t make_small()
+    {
+        if (small) return hipSuccess;
         void *mem = nullptr;
-        // portable: the transfers of every device go through the same slots;
-        // coherent: the flags are read while the kernel runs
-        const size_t bytes = 2 * (size_t)workers * kStageSlotDoubles * sizeof(double);
-        const hipError_t e = hipHostMalloc(&mem, bytes + kStageFlags * sizeof(uint32_t),
-                                           hipHostMallocPortable | hipHostMallocCoherent);
-        if (e != hipSuccess) return e;
-        slots = static_cast<double *>(mem);
+        const size_t bytes = kStageSmallDoubles * sizeof(double);
+        if (hipError_t e = pinned(&mem, bytes + kStageFlags * sizeof(uint32_t)); e != hipSuccess)
+            return e;
+        small = static_cast<double *>(mem);
         flags = reinterpret_cast<uint32_t *>(static_cast<char *>(mem) + bytes);
         memset(flags, 0, kStageFlags * sizeof(uint32_t));
-        seq = 0;
+        return hipSuccess;
+    }
+    // at least one pair, and up to `want` of them
+    hipError_t make_pairs(int want)
+    {
+        while (npairs < want) {
+            void *mem = nullptr;
+            if (hipError_t e = pinned(&mem, 2 * kStageSlotDoubles * sizeof(double)); e != hipSuccess) {
+                (void)hipGetLastError();
+                return npairs ? hipSuccess : e;
+            }
+            pairs[npairs++] = static_cast<double *>(mem);
+        }
         return hipSuccess;
     }
     void release()
     {
-        if (slots) (void)hipHostFree(slots);
-        slots = nullptr;
+        if (small) (void)hipHostFree(small);
+        for (int i = 0; i < npairs; ++i) (void)hipHostFree(pairs[i]);
     }
 };
 
@@ -248,8 +267,6 @@ hipError_t transfer(int device, hipStream_t s, double *host, size_t n, bool to_h
     Pool &p = pool();
     SlotUse use(p);
     SlotSet &set = use.set;
-    if (!set.slots)
-        if (hipError_t e = set.allocate(use.mine ? kStageWorkers : 1); e != hipSuccess) return e;
     Job j;
     j.device = device;
     j.stream = s;
@@ -258,33 +275,37 @@ hipError_t transfer(int device, hipStream_t s, double *host, size_t n, bool to_h
     j.chunks = (n + kStageSlotDoubles - 1) / kStageSlotDoubles;
     j.to_host = to_host;
     j.kernel = &kernel;
-    j.slots = set.slots;
+    j.pairs = set.pairs;
     if (j.chunks == 1) {
+        const bool small = n <= kStageSmallDoubles;
+        hipError_t e = small ? set.make_small() : set.make_pairs(1);
+        if (e != hipSuccess) return e;
+        double *slot = small ? set.small : set.pairs[0];
         const size_t blocks = (n + kStageBlock - 1) / kStageBlock;
-        const bool flags = to_host && blocks <= (size_t)kStageFlags;
-        if (!to_host) memcpy(set.slots, host, n * sizeof(double));
+        const bool flags = to_host && small && blocks <= (size_t)kStageFlags;
+        if (!to_host) memcpy(slot, host, n * sizeof(double));
         StageDone done{nullptr, 0};
         if (flags) {
             done.flag = set.flags;
             if (++set.seq == 0) set.seq = 1;
             done.seq = set.seq;
         }
-        hipError_t e = kernel(set.slots, 0, n, done, s);
-        if (e != hipSuccess) return e;
+        if ((e = kernel(slot, 0, n, done, s)) != hipSuccess) return e;
         if (!flags || !all_done(done, blocks))
             if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        if (to_host) memcpy(host, set.slots, n * sizeof(double));
+        if (to_host) memcpy(host, slot, n * sizeof(double));
         return hipSuccess;
     }
     // a helper for every two chunks past the caller's own two
-    const int helpers =
-        use.mine ? (int)std::min<size_t>((j.chunks - 1) / 2, kStageWorkers - 1) : 0;
+    int helpers = use.mine ? (int)std::min<size_t>((j.chunks - 1) / 2, kStageWorkers - 1) : 0;
+    if (hipError_t e = set.make_pairs(1 + helpers); e != hipSuccess) return e;
+    helpers = std::min(helpers, set.npairs - 1);
     if (helpers) {
         std::lock_guard<std::mutex> lock(p.m);
         try {
             while ((int)p.threads.size() < helpers)
                 p.threads.emplace_back([&p] { p.helper(); });
-        } catch (const std::system_error &) {
+        } catch (const std::exception &) {
             // fewer helpers, or none: the caller's thread does the rest
         }
         j.seats = helpers;

@@ -108,7 +108,29 @@ def more_transfers_than_slot_pairs(s):
     assert s.L.hs_pinned_now() == 0
 
 
-CASES = [closing_does_not_wait, last_close_beside_a_new_handle, many_handles_come_and_go,
+def slots_are_made_as_needed(s):
+    """A small read pins little, a large one what it uses (4 MiB a thread), and
+    all of it is kept until the last handle closes."""
+    MiB = 1 << 20
+    a = s.flb.Lattice(20, 20, TAU, 1e-4)
+    assert s.L.hs_pinned_now() == 0
+    a.get_populations()
+    small = s.L.hs_pinned_now()
+    assert 9 * 400 * 8 < small <= MiB
+    a.set_populations(a.get_populations())
+    a.read_correlators()
+    assert s.L.hs_pinned_now() == small
+    for side, pairs in ((100, 1), (200, 1), (256, 2), (2048, 8), (300, 8)):
+        b = s.flb.Lattice(side, side, TAU, 1e-4)
+        b.get_populations()
+        assert s.L.hs_pinned_now() == small + pairs * 4 * MiB, side
+        b.close()
+    assert not any(x.startswith("hipHostFree") for x in s.take_log())
+    a.close()
+    assert s.L.hs_pinned_now() == 0
+
+
+CASES = [slots_are_made_as_needed, closing_does_not_wait, last_close_beside_a_new_handle, many_handles_come_and_go,
          more_transfers_than_slot_pairs]
 
 
