@@ -260,10 +260,31 @@ bool all_done(const StageDone &done, size_t blocks)
     return true;
 }
 
+// The handle's device made the thread's current one, and the caller's again: an
+// event cannot be recorded on another device's stream.
+struct DeviceUse {
+    int was = -1;
+    hipError_t error;
+    explicit DeviceUse(int device)
+    {
+        int cur = device;
+        error = hipGetDevice(&cur);
+        if (error != hipSuccess || cur == device) return;
+        error = hipSetDevice(device);
+        if (error == hipSuccess) was = cur;
+    }
+    ~DeviceUse()
+    {
+        if (was >= 0) (void)hipSetDevice(was);
+    }
+};
+
 hipError_t transfer(int device, hipStream_t s, double *host, size_t n, bool to_host,
                     const StageKernel &kernel)
 {
     if (!n) return hipStreamSynchronize(s);
+    DeviceUse current(device);
+    if (current.error != hipSuccess) return current.error;
     Pool &p = pool();
     SlotUse use(p);
     SlotSet &set = use.set;

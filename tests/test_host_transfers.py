@@ -130,7 +130,23 @@ def slots_are_made_as_needed(s):
     assert s.L.hs_pinned_now() == 0
 
 
-CASES = [slots_are_made_as_needed, closing_does_not_wait, last_close_beside_a_new_handle, many_handles_come_and_go,
+def current_device_of_the_caller(s):
+    """A handle of one device read and written while another is the caller's
+    current one, which stays so."""
+    import ctypes
+    s.L.hipSetDevice(1)
+    gs = [s.flb.Lattice(side, side, TAU, 1e-4) for side in (20, 250, 700)]
+    gs.append(s.flb.DqLattice("D1Q3", (1 << 12,), [1.0] * 3, 1e-4))
+    s.L.hipSetDevice(0)
+    for g in gs:
+        g.set_populations(g.get_populations())
+        g.read_correlators()
+        d = ctypes.c_int(-1)
+        s.L.hipGetDevice(ctypes.byref(d))
+        assert d.value == 0
+
+
+CASES = [current_device_of_the_caller, slots_are_made_as_needed, closing_does_not_wait, last_close_beside_a_new_handle, many_handles_come_and_go,
          more_transfers_than_slot_pairs]
 
 
