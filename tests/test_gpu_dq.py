@@ -14,6 +14,7 @@ import numpy as np
 import pytest
 
 import lyapunov_dq
+from hip_stream import hip_stream
 from paper_1010_1233_amd import workloads
 
 pytestmark = pytest.mark.gpu
@@ -274,23 +275,24 @@ def test_replays_of_captured_line_steps(flb, calls):
     f = w.reshape(-1, 1, 1, 1) * (1 + 0.1 * np.random.default_rng(2).normal(size=(3, 1, 1, 3001)))
     hs = [flb.DqLattice("D1Q3", (3001,), [1.0, 1.0, 0.8], 0.0, u0=[0.03]) for _ in range(2)]
     g, ref = hs
-    s = torch.cuda.Stream()
-    g.set_stream(s)
-    for h in hs:
-        h.set_populations(f)
-        h.step(1)
-        h.synchronize()
-    graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph, stream=s):
-        for n in calls:
-            g.step(n)
-    for replay in range(3):
-        with torch.cuda.stream(s):
-            graph.replay()
-        for n in calls:
-            ref.step(n)
-        assert np.array_equal(g.get_populations(), ref.get_populations()), replay
-        torch.ones(1000, device="cuda").sum().item()
+    with hip_stream(flb) as s:
+        g.set_stream(s)
         for h in hs:
-            h.step(6)
-        assert np.array_equal(g.get_populations(), ref.get_populations()), replay
+            h.set_populations(f)
+            h.step(1)
+            h.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            for n in calls:
+                g.step(n)
+        for replay in range(3):
+            with torch.cuda.stream(s):
+                graph.replay()
+            for n in calls:
+                ref.step(n)
+            assert np.array_equal(g.get_populations(), ref.get_populations()), replay
+            torch.ones(1000, device="cuda").sum().item()
+            for h in hs:
+                h.step(6)
+            assert np.array_equal(g.get_populations(), ref.get_populations()), replay
+        g.set_stream(None)

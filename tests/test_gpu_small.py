@@ -4,6 +4,7 @@ bits; the sums match the oracle."""
 import numpy as np
 import pytest
 
+from hip_stream import hip_stream
 from paper_1010_1233_amd import workloads
 
 pytestmark = pytest.mark.gpu
@@ -118,14 +119,15 @@ def test_samples_follow_the_callers_time_after_replays(flb, nx, ny, n):
         g = _make(flb, nx, ny)
         if one_step:
             g.set_time_blocking(1, 64)  # the general step kernels
-        s = torch.cuda.Stream()
-        g.set_stream(s)
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph, stream=s):
-            g.step(n)
-        with torch.cuda.stream(s):
-            for _ in range(3):
-                graph.replay()
+        with hip_stream(flb) as s:
+            g.set_stream(s)
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=s):
+                g.step(n)
+            with torch.cuda.stream(s):
+                for _ in range(3):
+                    graph.replay()
+            g.set_stream(None)
         assert g.t == n
         counts = []
         for steps, every in ((2, 10), (8, 10), (7, 7), (23, 5)):

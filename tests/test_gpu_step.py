@@ -10,6 +10,7 @@ import sys
 import numpy as np
 import pytest
 
+from hip_stream import hip_stream
 from paper_1010_1233_amd import workloads
 
 pytestmark = pytest.mark.gpu
@@ -639,24 +640,25 @@ def test_replays_of_several_captured_calls(flb, nx, ny, calls):
     note("captured calls", nx, ny, calls)
     g = flb.Lattice(nx, ny, TAU_C1, 1e-3, seed=4)
     ref = flb.Lattice(nx, ny, TAU_C1, 1e-3, seed=4)
-    s = torch.cuda.Stream()
-    g.set_stream(s)
-    for h in (g, ref):
-        h.thermalize()
-        h.step(2)
-        h.synchronize()
-    graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph, stream=s):
-        for n in calls:
-            g.step(n)
-    for replay in range(3):
-        with torch.cuda.stream(s):
-            graph.replay()
-        for n in calls:
-            ref.step(n)
-        assert np.array_equal(g.get_populations(), ref.get_populations()), replay
-        torch.ones(1000, device="cuda").sum().item()
+    with hip_stream(flb) as s:
+        g.set_stream(s)
         for h in (g, ref):
-            for n in (4, 3, 9):
-                h.step(n)
-        assert np.array_equal(g.get_populations(), ref.get_populations()), replay
+            h.thermalize()
+            h.step(2)
+            h.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            for n in calls:
+                g.step(n)
+        for replay in range(3):
+            with torch.cuda.stream(s):
+                graph.replay()
+            for n in calls:
+                ref.step(n)
+            assert np.array_equal(g.get_populations(), ref.get_populations()), replay
+            torch.ones(1000, device="cuda").sum().item()
+            for h in (g, ref):
+                for n in (4, 3, 9):
+                    h.step(n)
+            assert np.array_equal(g.get_populations(), ref.get_populations()), replay
+        g.set_stream(None)
