@@ -175,8 +175,9 @@ int flb_get_sample_overlap(flb_t *h);
  * timed; each timed launch keeps its event pair until it is read.
  * flb_get_launch_timing_kinds reads the same records split by the steps a
  * launch took: launches[q] and total_ms[q] (caller arrays of three) for the
- * launches of q + 1 steps; q = 2 also holds the launches of four and five
- * steps of the library's own grouping (flb_set_time_blocking). */
+ * launches of q + 1 steps; q = 2 also holds the longer launches of the
+ * library's own grouping (flb_set_time_blocking): up to twelve steps, and up
+ * to 4096 on lattices that it keeps inside one compute unit. */
 int flb_set_launch_timing(flb_t *h, int on);
 int flb_get_launch_timing(flb_t *h, int64_t *launches, double *total_ms);
 int flb_get_launch_timing_kinds(flb_t *h, int64_t launches[3], double total_ms[3]);

@@ -1258,6 +1258,16 @@ int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_sec
     return enqueue(n);
 }
 
+// Enqueues a due sample on the work stream.
+int settle_due(flb_t *h)
+{
+    if (!h->due) return FLB_OK;
+    int rc = enqueue_sample(h, h->stream);
+    if (rc) return rc;
+    h->due = false;
+    return FLB_OK;
+}
+
 // Steps per launch of the resident kernel (a launch of a few milliseconds).
 constexpr int64_t kResidentSteps = 4096;
 
@@ -1266,6 +1276,8 @@ constexpr int64_t kResidentSteps = 4096;
 // device counter is advanced.
 int enqueue_resident(flb_t *h, int64_t n, int every, hipStream_t s)
 {
+    if (h->timing && h->due)  // apart from the launches that are timed
+        if (int rc = settle_due(h)) return rc;
     for (int64_t k = 0; k < n;) {
         const int64_t m = std::min(n - k, kResidentSteps);
         hipEvent_t stop = nullptr;
@@ -1277,16 +1289,6 @@ int enqueue_resident(flb_t *h, int64_t n, int every, hipStream_t s)
         FLB_HIP(launch_advance_step(h->d_step + h->cur, (uint32_t)m, s));
         k += m;
     }
-    return FLB_OK;
-}
-
-// Enqueues a due sample on the work stream.
-int settle_due(flb_t *h)
-{
-    if (!h->due) return FLB_OK;
-    int rc = enqueue_sample(h, h->stream);
-    if (rc) return rc;
-    h->due = false;
     return FLB_OK;
 }
 
@@ -1648,25 +1650,30 @@ int flb_run(flb_t *h, int64_t nsteps, int sample_every)
     if (sample_every == 0) return flb_step(h, nsteps);
     rc = setup_correlators(h);
     if (rc) return rc;
-    if (h->own_grouping() && h->all_small()) {
-        // steps and samples resident (the last sample included), but for a step
-        // that has to go from buffer to buffer, which is left to the loop below
-        const int64_t n = keeps_parity(h, h->stream) ? nsteps - nsteps % 2 : nsteps;
-        const int64_t samples = (h->t + n) / sample_every - h->t / sample_every;
-        const bool timing = h->timing;
-        h->timing = false;
-        rc = enqueue_resident(h, n, sample_every, h->stream);
-        h->timing = timing;
-        if (rc) return rc;
-        h->t += n;
-        h->nsamples += samples;
-        nsteps -= n;
-    }
     // (plain launches: a captured graph per period was slower at every size,
     // 256^2 73 against 60 us a period, 4096^2 1449 against 1406)
     const bool timing = h->timing;
     while (nsteps > 0 && !rc) {
         const int64_t to_sample = sample_every - h->t % sample_every;
+        if (h->own_grouping() && h->all_small()) {
+            // steps and samples resident (the last sample included), but for
+            // what launch timing takes and a step that has to go from buffer
+            // to buffer
+            int64_t n = nsteps, unit = 1;
+            if (timing) {
+                unit = sample_every;
+                n = to_sample == unit ? nsteps / unit * unit : 0;
+            }
+            if (n % 2 && keeps_parity(h, h->stream)) n -= unit;
+            if (n > 0) {
+                h->timing = false;
+                if ((rc = enqueue_resident(h, n, sample_every, h->stream))) break;
+                h->nsamples += (h->t + n) / sample_every - h->t / sample_every;
+                h->t += n;
+                nsteps -= n;
+                continue;
+            }
+        }
         const int64_t n = std::min(nsteps, to_sample);
         // launch timing leaves out whole periods
         h->timing = timing && n < sample_every;

@@ -185,6 +185,8 @@ int hipLaunchKernel(const void *fn, Dim grid, Dim, void **args, size_t, void *st
                 break;
             }
     }
+    const std::string anonymous = "(anonymous namespace)::";
+    for (size_t at; (at = name.find(anonymous)) != std::string::npos;) name.erase(at, anonymous.size());
     name = name.substr(0, name.find('('));
     const size_t at = name.find("flbdev::");
     if (at != std::string::npos) name = name.substr(at + 8);

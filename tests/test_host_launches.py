@@ -73,7 +73,34 @@ def captured_line_steps_keep_the_buffers(s):
             assert sum(x[1] for x in steps) == n and all(1 <= x[1] <= 8 for x in steps)
 
 
-CASES = [captured_steps_keep_the_buffers, captured_line_steps_keep_the_buffers,
+def timed_launches(s):
+    """Launch timing counts the launches of a run outside its whole periods, and
+    no sample's."""
+    s.cost("small_kernel<0, true, false>", 1.0)
+    s.cost("patch_kernel", 1.0)
+    s.cost("corr_rows", 100.0)
+    for sides in SIDES[:2]:
+        g = s.flb.Lattice(*sides, TAU, 1e-4)
+        g.set_launch_timing(True)
+        for steps, every, launches in ((7, 10, 1), (3, 10, 1), (30, 10, 0), (2, 10, 1),
+                                       (8, 10, 1), (25, 10, 1), (14, 20, 2)):
+            t = g.t
+            g.run(steps, every)
+            n, ms = g.launch_timing()
+            assert n == launches and ms == launches, (sides, steps, every, t, n, ms)
+            assert g.t == t + steps
+        g.accumulate()
+        s.take_log()
+        g.step(8)
+        small = [x for x in s.take_log() if "launch small_kernel" in x]
+        n, ms = g.launch_timing()
+        assert (n, ms) == (1, 1.0) and len(small) == (2 if sides == SIDES[0] else 0)
+        g.set_launch_timing(False)
+        g.run(100, 10)
+        assert g.launch_timing() == (0, 0.0)
+
+
+CASES = [timed_launches, captured_steps_keep_the_buffers, captured_line_steps_keep_the_buffers,
          handles_never_captured_are_grouped_freely]
 
 
