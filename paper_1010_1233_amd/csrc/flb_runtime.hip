@@ -102,11 +102,38 @@ struct flb {
     int nitems = 0;
     // time blocking: steps per launch (1, 2 or 3; 0 while no shape was set or
     // tuned: the library's own grouping, see launch_plan; negative: that
-    // grouping by a tuning call, -tblock what the handle reports) and the
+    // grouping by a tuning call, -tblock and `reported` what the handle reports,
+    // the fastest shape that can be set) and the
     // two- and three-step kernels' tile width; tile2 = 0: each lattice has its
     // own, log2 of it in ltile (5 or 6)
     int tblock = 0, tile2 = 64;
     bool own_grouping() const { return tblock <= 0; }
+    // The shape that the own grouping's one-, two- and three-step launches have
+    // is the one the handle was made with, whatever it reports: the one a tuning
+    // call times.
+    struct Settable {
+        int tile_w = 256, sites = 1;
+        bool nontemporal = false;
+        int tile2 = 64;
+    };
+    Settable made, reported;
+    Settable shape() const
+    {
+        return tblock < 0 ? reported : Settable{tile_w, sites, nontemporal, tile2};
+    }
+    void set_shape(const Settable &c)
+    {
+        tile_w = c.tile_w;
+        sites = c.sites;
+        nontemporal = c.nontemporal;
+        tile2 = c.tile2;
+    }
+    // a caller names (part of) a shape: the reported one becomes the handle's
+    void leave_own_grouping()
+    {
+        set_shape(shape());
+        if (own_grouping()) tblock = std::max(1, -tblock);
+    }
     std::vector<int8_t> ltile;
     StepItem *d_items2 = nullptr;
     int nitems2 = 0;
@@ -1379,6 +1406,7 @@ flb_t *create_impl(int n, const flb_lattice_spec *specs, uint64_t seed, int stor
         h->tile_w = 128;
         h->sites = 4;
     }
+    h->made = h->shape();
 
     auto bail = [&](int rc) -> flb_t * {
         (void)rc;
@@ -1952,10 +1980,10 @@ int flb_set_step_config(flb_t *h, int tile_w, int sites, int nontemporal)
     if (check_handle(h)) return FLB_EINVAL;
     if (!step_tile_supported(tile_w, sites)) return fail(FLB_EINVAL, "unsupported step tile");
     FLB_HIP(hipStreamSynchronize(h->stream));
+    h->leave_own_grouping();
     h->tile_w = tile_w;
     h->sites = sites;
     h->nontemporal = nontemporal != 0;
-    if (h->own_grouping()) h->tblock = std::max(1, -h->tblock);  // the shape asked for
     return build_step_items(h);
 }
 
@@ -1966,6 +1994,7 @@ int flb_set_time_blocking(flb_t *h, int steps_per_launch, int tile_w)
         return fail(FLB_EINVAL, "steps_per_launch must be 1, 2 or 3");
     if (!step2_tile_supported(tile_w)) return fail(FLB_EINVAL, "unsupported two-step tile");
     FLB_HIP(hipStreamSynchronize(h->stream));
+    h->leave_own_grouping();
     h->tblock = steps_per_launch;
     h->tile2 = tile_w;
     return build_step_items(h);
@@ -1975,7 +2004,7 @@ int flb_get_time_blocking(flb_t *h, int *steps_per_launch, int *tile_w)
 {
     if (check_handle(h)) return FLB_EINVAL;
     if (steps_per_launch) *steps_per_launch = std::max(1, std::abs(h->tblock));
-    if (tile_w) *tile_w = h->tile2;
+    if (tile_w) *tile_w = h->shape().tile2;
     return FLB_OK;
 }
 
@@ -1990,6 +2019,7 @@ int flb_set_lattice_tiles(flb_t *h, const int *tile_w)
         lt[l] = tile_w[l] == 32 ? 5 : 6;
     }
     FLB_HIP(hipStreamSynchronize(h->stream));
+    h->leave_own_grouping();
     h->tblock = 2;
     h->tile2 = 0;
     h->ltile = lt;
@@ -2000,17 +2030,18 @@ int flb_get_lattice_tiles(flb_t *h, int *tile_w)
 {
     if (check_handle(h)) return FLB_EINVAL;
     if (!tile_w) return fail(FLB_EINVAL, "tile_w must not be NULL");
-    for (size_t l = 0; l < h->params.size(); ++l)
-        tile_w[l] = h->tile2 ? h->tile2 : 1 << h->ltile[l];
+    const int tile2 = h->shape().tile2;
+    for (size_t l = 0; l < h->params.size(); ++l) tile_w[l] = tile2 ? tile2 : 1 << h->ltile[l];
     return FLB_OK;
 }
 
 int flb_get_step_config(flb_t *h, int *tile_w, int *sites, int *nontemporal)
 {
     if (check_handle(h)) return FLB_EINVAL;
-    if (tile_w) *tile_w = h->tile_w;
-    if (sites) *sites = h->sites;
-    if (nontemporal) *nontemporal = h->nontemporal ? 1 : 0;
+    const flb_t::Settable c = h->shape();
+    if (tile_w) *tile_w = c.tile_w;
+    if (sites) *sites = c.sites;
+    if (nontemporal) *nontemporal = c.nontemporal ? 1 : 0;
     return FLB_OK;
 }
 
@@ -2027,12 +2058,11 @@ struct StepShape {
 
 static void apply_shape(flb_t *h, const StepShape &c)
 {
-    h->tile_w = c.tw;
-    h->sites = c.sv;
-    h->nontemporal = c.nt != 0;
+    const flb_t::Settable named{c.tw, c.sv, c.nt != 0, c.t2};
     h->tblock = c.tb;
-    h->tile2 = c.t2;
-    h->ltile = c.t2 == 0 ? c.lt : std::vector<int8_t>();
+    h->reported = named;
+    h->set_shape(c.tb <= 0 ? h->made : named);
+    h->ltile = h->tile2 == 0 ? c.lt : std::vector<int8_t>();
 }
 
 static std::string tune_key(const flb_t *h, const char *kind, int every)
@@ -2118,7 +2148,8 @@ template <typename F> static int with_saved_state(flb_t *h, F body)
     const int cur0 = h->cur;
     const int64_t t0 = h->t;
     const bool timing0 = h->timing;
-    const StepShape shape0{h->tile_w, h->sites, h->nontemporal ? 1 : 0, h->tblock, h->tile2,
+    const flb_t::Settable c0 = h->shape();
+    const StepShape shape0{c0.tile_w, c0.sites, c0.nontemporal ? 1 : 0, h->tblock, c0.tile2,
                            h->ltile};
     h->timing = false;
     hipError_t e = hipMemcpyAsync(saved, h->pops[cur0], bytes, hipMemcpyDeviceToDevice, h->stream);
@@ -2179,8 +2210,9 @@ static int time_shapes(flb_t *h, int nsteps, const std::vector<StepShape> &shape
 }
 
 // Every supported launch shape timed alone, fastest first.  The library's own
-// grouping carries the fastest of the others, as what the handle reports: a
-// program that copies a tuned shape to another handle sets that one.
+// grouping carries the fastest of the others, as what the handle reports (not
+// what it runs, see apply_shape): a program that copies a tuned shape to
+// another handle sets that one.
 static int time_every_shape(flb_t *h, int nsteps, std::vector<std::pair<float, StepShape>> &out)
 {
     std::vector<StepShape> shapes;
@@ -2190,7 +2222,8 @@ static int time_every_shape(flb_t *h, int nsteps, std::vector<std::pair<float, S
     for (int tb : {2, 3})
         for (int t2 : {32, 64, 128})
             for (int nt = 0; nt < 2; ++nt) shapes.push_back({h->tile_w, h->sites, nt, tb, t2, {}});
-    shapes.push_back({h->tile_w, h->sites, h->nontemporal ? 1 : 0, 0, 64, {}});
+    shapes.push_back({h->made.tile_w, h->made.sites, h->made.nontemporal ? 1 : 0, 0,
+                      h->made.tile2, {}});
     std::vector<float> best;
     if (int rc = time_shapes(h, nsteps, shapes, best)) return rc;
     out.clear();

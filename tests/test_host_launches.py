@@ -100,7 +100,43 @@ def timed_launches(s):
         assert g.launch_timing() == (0, 0.0)
 
 
-CASES = [timed_launches, captured_steps_keep_the_buffers, captured_line_steps_keep_the_buffers,
+def a_tuned_grouping_runs_what_was_timed(s):
+    """The tuner keeps the library's own grouping: its launches stay those that
+    it timed, while the handle reports the fastest shape that can be set, which
+    is what it runs once a caller names one."""
+    s.cost("march_kernel", 0.01)
+    s.cost("patch_kernel", 0.01)
+    s.cost("step3_kernel<0, true, true, 128", 0.5)
+    s.cost("step", 1.0)
+    for sides in SIDES[1:2] + SIDES[3:]:
+        plain, tuned, other = (s.flb.Lattice(*sides, TAU, 1e-4) for _ in range(3))
+        other.autotune(12)
+        for tune in (lambda: tuned.autotune(12), lambda: tuned.autotune_path(12, 10)):
+            tune()
+            s.take_log()
+            got = []
+            for g in (plain, tuned):
+                names = []
+                for n in (1, 2, 3, 6, 10, 11):
+                    s.take_log()
+                    g.step(n)
+                    names += [x.split(" stream=")[0] for x in s.take_log()]
+                got.append(names)
+            assert got[0] == got[1]
+            assert tuned.time_blocking() == (3, 128) and tuned.step_config()[2]
+            assert list(tuned.lattice_tiles()) == [128]
+        shape = tuned.step_config()
+        tuned.set_time_blocking(2, 32)
+        assert tuned.step_config() == shape and tuned.time_blocking() == (2, 32)
+        shape = other.step_config()
+        other.set_step_config(*shape)
+        assert other.step_config() == shape and other.time_blocking() == (3, 128)
+        s.take_log()
+        other.step(3)
+        assert [x[0] for x in s.take_steps()] == ["step3_kernel"]
+
+
+CASES = [a_tuned_grouping_runs_what_was_timed, timed_launches, captured_steps_keep_the_buffers, captured_line_steps_keep_the_buffers,
          handles_never_captured_are_grouped_freely]
 
 
