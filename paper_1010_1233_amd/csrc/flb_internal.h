@@ -163,7 +163,7 @@ bool step2_tile_supported(int tw);
 // 128, the same items).
 hipError_t launch_step3(const DeviceView &v, const StepItem *items, int nitems, int tile_w,
                         bool nontemporal, bool noise, hipStream_t s);
-// Four or five steps per launch by waves marching along y: strips of
+// Four or (FP32 storage) five steps per launch by waves marching along y: strips of
 // march_cols(steps) columns, segments of `rows` rows; item tile = strip +
 // segment * strips, items in groups of kMarchWaves (one block each).
 constexpr int kMarchWaves = 4;

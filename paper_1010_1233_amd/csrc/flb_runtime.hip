@@ -145,8 +145,8 @@ struct flb {
     int small_lds[3] = {0, 0, 0};  // steps only, samples, samples and their sums
     bool small_keep = false;       // launches of several samples keep the sums in LDS
     bool all_small() const { return n_small == (int)params.size(); }
-    // marching launches of 4 and 5 steps ([0], [1]), in the library's own
-    // grouping of lattices large enough for them
+    // marching launches of 4 and (FP32 storage) 5 steps ([0], [1]), in the
+    // library's own grouping of lattices large enough for them
     bool march = false;
     // ... or launches of up to patch_steps steps on small tiles (0: not these)
     int patch_steps = 0, patch_w = 0, patch_h = 0, n_patch = 0;
@@ -516,6 +516,7 @@ int build_march_items(flb_t *h)
         if (rows < kMarchMinRows) return FLB_OK;
         if (q == (h->storage == kF32) && march_overhead(h, steps, rows) > march_gain(h) * tile_overhead(h))
             return FLB_OK;
+        if (steps == 5 && h->storage != kF32) break;  // launch_plan has none
         h->march_rows[q] = rows;
         const std::vector<StepItem> items = march_items(h, steps, rows);
         h->n_march[q] = (int)items.size();

@@ -926,16 +926,21 @@ static hipError_t launch_march_s(const StepArgs &a, int nblocks, int steps, int 
                                  hipStream_t s)
 {
     const dim3 grid(nblocks), block(64 * kMarchWaves);
-    if (steps == 5 && noise)
-        hipLaunchKernelGGL((march_kernel<S, true, 5>), grid, block, 0, s, a, rows);
-    else if (steps == 5)
-        hipLaunchKernelGGL((march_kernel<S, false, 5>), grid, block, 0, s, a, rows);
-    else if (steps == 4 && noise)
+    if constexpr (S == kF32) {  // (16-bit storage: four steps are the faster)
+        if (steps == 5 && noise) {
+            hipLaunchKernelGGL((march_kernel<S, true, 5>), grid, block, 0, s, a, rows);
+            return hipGetLastError();
+        }
+        if (steps == 5) {
+            hipLaunchKernelGGL((march_kernel<S, false, 5>), grid, block, 0, s, a, rows);
+            return hipGetLastError();
+        }
+    }
+    if (steps != 4) return hipErrorInvalidValue;
+    if (noise)
         hipLaunchKernelGGL((march_kernel<S, true, 4>), grid, block, 0, s, a, rows);
-    else if (steps == 4)
-        hipLaunchKernelGGL((march_kernel<S, false, 4>), grid, block, 0, s, a, rows);
     else
-        return hipErrorInvalidValue;
+        hipLaunchKernelGGL((march_kernel<S, false, 4>), grid, block, 0, s, a, rows);
     return hipGetLastError();
 }
 
