@@ -969,7 +969,8 @@ hipError_t launch_march(const DeviceView &v, const StepItem *items, int nitems, 
 // VALU of the compute units that have a block, 0.28 us for every four waves
 // of a step.  So the tile is small enough to give every compute unit one,
 // and the rings, which grow with steps squared, are cheaper than another
-// launch: 256^2, ten steps in one launch of 16 x 16 tiles.
+// launch: 256^2, up to nine steps in one launch of 16 x 16 tiles (ten are two
+// launches of five, 18.7 us; 30 in tiles of three and two steps).
 // ---------------------------------------------------------------------
 template <int S, bool NOISE>
 __global__ __launch_bounds__(kPatchThreads) void patch_kernel(StepArgs g, int tw, int th, int steps)
