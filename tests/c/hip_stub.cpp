@@ -270,6 +270,7 @@ int hipEventRecord(void *e, void *s)
 {
     Event *ev = static_cast<Event *>(e);
     if (s && static_cast<Stream *>(s)->device != ev->device) return kInvalidHandle;
+    note("record stream=%p event=%p", s, e);
     std::lock_guard<std::mutex> lock(st().m);
     ev->ms = st().clock;
     return kOk;

@@ -136,7 +136,58 @@ def a_tuned_grouping_runs_what_was_timed(s):
         assert [x[0] for x in s.take_steps()] == ["step3_kernel"]
 
 
-CASES = [a_tuned_grouping_runs_what_was_timed, timed_launches, captured_steps_keep_the_buffers, captured_line_steps_keep_the_buffers,
+def samples_beside_the_steps(s):
+    """From 2^21 sites on a sample runs on a second stream: behind the work
+    before it, read before the second step launch writes its state, and done
+    before the step call's work is.  Smaller lattices' samples come before the
+    steps, on their stream."""
+    def events(lines, kind, stream):
+        return [(i, x.split("event=")[1]) for i, x in enumerate(lines)
+                if x.startswith(f"{kind} stream={stream:#x}")]
+
+    def launches(lines, part, stream):
+        return [i for i, x in enumerate(lines)
+                if x.startswith("launch " + part) and f"stream={stream:#x} " in x]
+
+    for sides, blocking in ((SIDES[3], 0), (SIDES[3], 1), (SIDES[3], 2), (SIDES[3], 3),
+                            (SIDES[2], 0)):
+        g = s.flb.Lattice(*sides, TAU, 1e-4, moments=True)
+        if blocking:
+            g.set_time_blocking(blocking, 64)
+        main = s.stream()
+        g.set_stream(main)
+        for n in (1, 5, 10, 16):
+            g.accumulate()
+            s.take_log()
+            g.step(n)
+            lines = s.take_log()
+            steps = [i for p in ("step", "march") for i in launches(lines, p, main)]
+            steps.sort()
+            other = {int(x.split("stream=")[1].split()[0], 16) for x in lines if "stream=" in x}
+            other.discard(main)
+            if sides != SIDES[3]:
+                assert not other
+                assert max(launches(lines, "corr_", main)) < min(steps)
+                continue
+            (aux,) = other
+            rows = launches(lines, "corr_", aux)
+            assert rows and not launches(lines, "corr_", main)
+            (fork, e0), (back, e0b) = events(lines, "record", main)[0], events(lines, "wait", aux)[0]
+            assert e0 == e0b and fork < back < min(rows)
+            (read, e1), (done, e2) = events(lines, "record", aux)
+            # every kernel that reads the state comes before the first record
+            readers = [i for i in rows if "moment_fields" in lines[i] or "corr_rows" in lines[i]]
+            assert readers and max(readers) < read and max(rows) < done
+            waits = events(lines, "wait", main)
+            assert waits[-1][1] == e2 and waits[-1][0] > max(steps)
+            assert len(waits) == (2 if len(steps) > 1 else 1)
+            if len(steps) > 1:
+                assert waits[0][1] == e1 and steps[0] < waits[0][0] < steps[1]
+                assert read < waits[0][0]
+        g.close()
+
+
+CASES = [samples_beside_the_steps, a_tuned_grouping_runs_what_was_timed, timed_launches, captured_steps_keep_the_buffers, captured_line_steps_keep_the_buffers,
          handles_never_captured_are_grouped_freely]
 
 
