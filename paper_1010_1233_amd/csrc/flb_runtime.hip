@@ -153,7 +153,9 @@ struct flb {
     StepItem *d_patch = nullptr;
     StepItem *d_march[2] = {nullptr, nullptr};
     int n_march[2] = {0, 0}, march_rows[2] = {0, 0};
-    // steps of this handle were captured into a caller's graph (keeps_parity)
+    // Steps of this handle were captured into a caller's graph: calls keep the
+    // buffers' parity (keeps_parity), and replays may have advanced the device's
+    // step counter past t
     bool captured = false;
     int64_t t = 0;
 
@@ -689,13 +691,13 @@ int build_small_items(flb_t *h)
 
 // The resident kernel: nsteps steps of lattices that are all small, the
 // samples inside (see launch_small).
-hipError_t launch_resident(flb_t *h, uint32_t nsteps, uint32_t every, uint32_t to_sample,
+hipError_t launch_resident(flb_t *h, uint32_t nsteps, uint32_t every,
                            bool sample_first, hipStream_t s)
 {
     const bool sampled = every || sample_first;
     const bool keep = h->small_keep && every && nsteps >= 2 * every;
     return launch_small(h->view(), h->d_small, h->n_small, h->small_threads,
-                        h->small_lds[sampled ? (keep ? 2 : 1) : 0], nsteps, every, to_sample,
+                        h->small_lds[sampled ? (keep ? 2 : 1) : 0], nsteps, every,
                         sample_first, keep, h->noise, h->moments, s);
 }
 
@@ -1135,7 +1137,7 @@ int setup_correlators(flb_t *h)
 int enqueue_sample(flb_t *h, hipStream_t s, hipEvent_t ev_read = nullptr)
 {
     const DeviceView v = h->view();
-    if (h->n_small) FLB_HIP(launch_resident(h, 0, 0, 0, true, s));
+    if (h->n_small) FLB_HIP(launch_resident(h, 0, 0, true, s));
     if (h->all_small()) {
         if (ev_read) FLB_HIP(hipEventRecord(ev_read, s));
         return FLB_OK;
@@ -1209,16 +1211,18 @@ int begin_timed(flb_t *h, int steps, hipStream_t s, hipEvent_t &stop)
     return FLB_OK;
 }
 
+// Called where steps are enqueued: notes a handle's first capture.
+void note_capture(flb_t *h)
+{
+    if (!h->captured && capturing(h->stream)) h->captured = true;
+}
+
 // Whether n steps must flip the buffers as often as n one-step launches, up to
 // pairs.  A graph of captured steps reads the buffer that held the state when
 // it was captured: it can be replayed as long as an even number of steps, taken
 // by any calls in the capture and by any between replays, leaves the state in
 // that buffer.  So from a handle's first capture on, whatever the grouping.
-bool keeps_parity(flb_t *h, hipStream_t s)
-{
-    if (!h->captured && h->own_grouping() && capturing(s)) h->captured = true;
-    return h->captured && h->own_grouping();
-}
+bool keeps_parity(const flb_t *h) { return h->captured && h->own_grouping(); }
 
 // n steps from the device counter's value.  launch_plan says how the steps
 // are grouped. When wait_before_second is given, the second launch (the first
@@ -1272,7 +1276,7 @@ int enqueue_steps(flb_t *h, int64_t n, hipStream_t s, hipEvent_t wait_before_sec
             }
         return FLB_OK;
     };
-    if (n > 1 && keeps_parity(h, s)) {
+    if (n > 1 && keeps_parity(h)) {
         int64_t count = patch_launches(n);
         if (!count)
             for (int64_t of : launch_plan(h, n).of) count += of;
@@ -1300,8 +1304,8 @@ int settle_due(flb_t *h)
 constexpr int64_t kResidentSteps = 4096;
 
 // n steps of lattices that are all small, resident, with a due sample before
-// them and samples where h->t comes to a multiple of `every` (0: none); the
-// device counter is advanced.
+// them and samples at the multiples of `every` (0: none); the device counter,
+// which those go by, is advanced.
 int enqueue_resident(flb_t *h, int64_t n, int every, hipStream_t s)
 {
     if (h->timing && h->due)  // apart from the launches that are timed
@@ -1310,8 +1314,7 @@ int enqueue_resident(flb_t *h, int64_t n, int every, hipStream_t s)
         const int64_t m = std::min(n - k, kResidentSteps);
         hipEvent_t stop = nullptr;
         if (int rc = begin_timed(h, (int)m, s, stop)) return rc;
-        const uint32_t to_sample = every ? (uint32_t)(every - (h->t + k) % every) : 0;
-        FLB_HIP(launch_resident(h, (uint32_t)m, (uint32_t)every, to_sample, h->due, s));
+        FLB_HIP(launch_resident(h, (uint32_t)m, (uint32_t)every, h->due, s));
         if (stop) FLB_HIP(hipEventRecord(stop, s));
         h->due = false;
         FLB_HIP(launch_advance_step(h->d_step + h->cur, (uint32_t)m, s));
@@ -1329,7 +1332,7 @@ int enqueue_steps_overlapped(flb_t *h, int64_t n)
     int rc;
     if (n >= kResidentMin && h->own_grouping() && h->all_small()) {
         // (in place: an odd step goes from buffer to buffer)
-        const int64_t odd = keeps_parity(h, s) ? n % 2 : 0;
+        const int64_t odd = keeps_parity(h) ? n % 2 : 0;
         if ((rc = enqueue_resident(h, n - odd, 0, s))) return rc;
         return enqueue_steps(h, odd, s);
     }
@@ -1593,6 +1596,7 @@ int flb_step(flb_t *h, int64_t nsteps)
     if (check_handle(h)) return FLB_EINVAL;
     int rc = check_time(h, nsteps);
     if (rc) return rc;
+    note_capture(h);
     rc = enqueue_steps_overlapped(h, nsteps);
     if (rc) return rc;
     h->t += nsteps;
@@ -1679,21 +1683,19 @@ int flb_run(flb_t *h, int64_t nsteps, int sample_every)
     if (sample_every == 0) return flb_step(h, nsteps);
     rc = setup_correlators(h);
     if (rc) return rc;
+    note_capture(h);
+    // Small lattices: steps and samples resident (the last sample included), but
+    // for what launch timing takes.  The kernel's samples go by the device's
+    // counter, so not where that may not be t.
+    const bool resident = h->own_grouping() && h->all_small() && !h->captured;
     // (plain launches: a captured graph per period was slower at every size,
     // 256^2 73 against 60 us a period, 4096^2 1449 against 1406)
     const bool timing = h->timing;
     while (nsteps > 0 && !rc) {
         const int64_t to_sample = sample_every - h->t % sample_every;
-        if (h->own_grouping() && h->all_small()) {
-            // steps and samples resident (the last sample included), but for
-            // what launch timing takes and a step that has to go from buffer
-            // to buffer
-            int64_t n = nsteps, unit = 1;
-            if (timing) {
-                unit = sample_every;
-                n = to_sample == unit ? nsteps / unit * unit : 0;
-            }
-            if (n % 2 && keeps_parity(h, h->stream)) n -= unit;
+        if (resident) {
+            int64_t n = nsteps;
+            if (timing) n = to_sample == sample_every ? nsteps / sample_every * sample_every : 0;
             if (n > 0) {
                 h->timing = false;
                 if ((rc = enqueue_resident(h, n, sample_every, h->stream))) break;

@@ -26,11 +26,11 @@ int small_lds_bytes(int nx, int ny, bool sampled, bool moments, bool keep_sums);
 
 // nsteps steps of the nlat lattices listed (in place in v.pops[v.cur], one
 // block of `threads` >= sites each), with a sample of their state before
-// them if sample_first, and with every > 0 after step to_sample (1 .. every)
-// and each `every` steps from there.  keep_sums: the sums stay in LDS from the
-// first sample of the launch to its end.
+// them if sample_first, and after every step that reaches a time divisible
+// by `every` (0: none).  keep_sums: the sums stay in LDS from the first
+// sample of the launch to its end.
 hipError_t launch_small(const DeviceView &v, const int32_t *lattices, int nlat, int threads,
-                        int lds_bytes, uint32_t nsteps, uint32_t every, uint32_t to_sample,
+                        int lds_bytes, uint32_t nsteps, uint32_t every,
                         bool sample_first, bool keep_sums, bool noise, bool moments,
                         hipStream_t s);
 

@@ -32,7 +32,7 @@ struct SmallArgs {
     const uint32_t *step;
     double *acc;
     double *csum_part;
-    uint32_t nsteps, every, to_sample;
+    uint32_t nsteps, every;
     int sample_first, keep_sums;
     uint32_t key0, key1;
 };
@@ -291,9 +291,8 @@ __device__ __forceinline__ void small_sample(const SmallArgs &g, const LatticePa
 }
 
 // One block per lattice of the list.  nsteps steps; a sample of the state
-// before them (sample_first) and, with every > 0, after step to_sample and
-// each `every` steps from there.  (Not by the device's counter t, which replays
-// of a caller's captured steps advance past the time its samples go by.)
+// before them (sample_first) and, with every > 0, after each step that
+// reaches a time divisible by it.
 template <int S, bool NOISE, bool MOM>
 __global__ __launch_bounds__(kSmallSites) void small_kernel(SmallArgs g)
 {
@@ -330,9 +329,10 @@ __global__ __launch_bounds__(kSmallSites) void small_kernel(SmallArgs g)
     }
     __syncthreads();
     uint32_t t = *g.step, left = g.nsteps;
-    uint32_t next = g.every ? g.to_sample : 0xFFFFFFFFu;  // steps to the next sample
     bool due = g.sample_first != 0;
     for (;;) {
+        // steps to the next sample after this one
+        const uint32_t next = g.every ? g.every - t % g.every : 0xFFFFFFFFu;
         if (sampled && due)
             small_sample<S, MOM>(g, P, L, by, left < next);
         if (!left) break;
@@ -354,9 +354,7 @@ __global__ __launch_bounds__(kSmallSites) void small_kernel(SmallArgs g)
         }
         t += n;
         left -= n;
-        next -= n;
-        due = next == 0;
-        if (due) next = g.every;
+        due = n == next;
     }
     if (g.nsteps) {
         const int e = fresh_thread(), y = e / nx, x = e - y * nx;
@@ -397,7 +395,7 @@ int small_lds_bytes(int nx, int ny, bool sampled, bool moments, bool keep_sums)
 }
 
 hipError_t launch_small(const DeviceView &v, const int32_t *lattices, int nlat, int threads,
-                        int lds_bytes, uint32_t nsteps, uint32_t every, uint32_t to_sample,
+                        int lds_bytes, uint32_t nsteps, uint32_t every,
                         bool sample_first, bool keep_sums, bool noise, bool moments,
                         hipStream_t s)
 {
@@ -411,13 +409,11 @@ hipError_t launch_small(const DeviceView &v, const int32_t *lattices, int nlat, 
     a.csum_part = v.csum_part;
     a.nsteps = nsteps;
     a.every = every;
-    a.to_sample = to_sample;
     a.sample_first = sample_first;
     a.keep_sums = keep_sums;
     a.key0 = (uint32_t)(v.seed & 0xFFFFFFFFu);
     a.key1 = (uint32_t)(v.seed >> 32);
     if (threads < 64 || threads > kSmallSites || threads % 64) return hipErrorInvalidValue;
-    if (every && (to_sample < 1 || to_sample > every)) return hipErrorInvalidValue;
 #define FLB_SEL(S_)                                                                          \
     if (v.storage == S_)                                                                     \
         return noise ? launch_small_m<S_, true>(a, nlat, threads, lds_bytes, moments, s)     \
