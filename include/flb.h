@@ -183,7 +183,13 @@ int flb_get_launch_timing(flb_t *h, int64_t *launches, double *total_ms);
 int flb_get_launch_timing_kinds(flb_t *h, int64_t launches[3], double total_ms[3]);
 
 /* Advances every lattice of the handle by nsteps >= 0 steps of Eq. (5) with
- * streaming (Eq. 1).  Enqueues only. */
+ * streaming (Eq. 1).  Enqueues only.
+ * On a stream that the caller captures, a graph of steps can be replayed
+ * while the library groups the steps itself or takes one per launch: each
+ * replay advances the lattices and the noise counter (not flb_get_step's t)
+ * as the calls would, if an even number of steps is captured and an even
+ * number is taken by other calls between replays (the state alternates
+ * between two buffers). */
 int flb_step(flb_t *h, int64_t nsteps);
 
 /* Advances by nsteps and, after every step that reaches a time t with
@@ -276,8 +282,10 @@ int flb_conservation(flb_t *h, int lattice, double out[5]);
 /* The same five sums, for the state of the most recent correlator sample:
  * every sample's row transforms leave FP64 partial sums of its fluctuation
  * fields (FP32 per site) at no extra pass over the populations, and this
- * call adds them up.  FLB_ESTATE if no sample was taken since creation or
- * the last reset.  Synchronises. */
+ * call adds them up (which rows share a partial sum depends on all lattices
+ * of the handle, so the last bits can differ from those of a lattice alone).
+ * FLB_ESTATE if no sample was taken since creation or the last reset.
+ * Synchronises. */
 int flb_sample_conservation(flb_t *h, int lattice, double out[5]);
 
 /* As flb_conservation, but enqueue-only: the five sums are written to
